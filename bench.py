@@ -137,9 +137,9 @@ MEASURED_TRAFFIC_Q2 = [
 
 # The same for the 2-D stage kernel on the 22500-triangle disk trap (P3, FP32).
 MEASURED_TRAFFIC_2D = {
-    "kernels_sha256": "1e4fa0faed3d3bee44654fa8b73c89c99f3c0e16ad84b3f16579f81e44a68dfa",
+    "kernels_sha256": "48024d5b6ace747553a004c71e87732cbef354189cb311888bbd10efa2fc04cf",
     "kernel": "k_stage2d<float,3,true>", "K": 22500,
-    "fetch_kib": 5077.52, "fetch_scale": 2.0000, "write_kib": 4944.12, "write_scale": 1.0000,
+    "fetch_kib": 5075.75, "fetch_scale": 2.0000, "write_kib": 4944.12, "write_scale": 1.0000,
 }
 
 
@@ -600,7 +600,7 @@ def trap2d_bench(a):
         M, dt = cmcg.cmcg_problem_steps(p, opts)
         U0 = torch.randn((K, 3, Np), dtype=torch.float64, device=dev) * 1e-3
         UT = torch.empty_like(U0)
-        cmcg.cmcg_debug_period(p, U0, UT, 1, False, opts=opts)  # builds the period's graph (untimed)
+        cmcg.cmcg_debug_period(p, U0, UT, 1, False, opts=opts)  # first period of the problem (untimed)
         for _ in range(a.warmup):
             cmcg.cmcg_solve(p, opts)
         torch.cuda.synchronize()
@@ -611,17 +611,24 @@ def trap2d_bench(a):
         el = (time.perf_counter() - t0) / a.steps
         st = cmcg.cmcg_result_stats(r)
         stream = torch.cuda.current_stream()
-        ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        ev0.record(stream)
-        for _ in range(a.kernel_periods):
-            cmcg.cmcg_debug_period(p, U0, UT, 1, False, opts=opts)
-        ev1.record(stream)
-        torch.cuda.synchronize()
-        per_launch = ev0.elapsed_time(ev1) / 1e3 / (a.kernel_periods * 4 * M)
-        res[prec] = dict(el=el, st=st, K=K, Np=Np, M=M, per_launch=per_launch,
+
+        def per_stage(o):
+            ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            ev0.record(stream)
+            for _ in range(a.kernel_periods):
+                cmcg.cmcg_debug_period(p, U0, UT, 1, False, opts=o)
+            ev1.record(stream)
+            torch.cuda.synchronize()
+            return ev0.elapsed_time(ev1) / 1e3 / (a.kernel_periods * 4 * M)
+
+        # the periods of the solve (one launch each when the mesh fits on the
+        # device, k_period2d), and stage launches (k_stage2d)
+        period_stage = per_stage(opts)
+        per_launch = per_stage(cmcg.cmcg_options_default(use_graph=0))
+        res[prec] = dict(el=el, st=st, K=K, Np=Np, M=M, per_launch=per_launch, period_stage=period_stage,
                          rate=st["dof_updates"] / st["seconds"] if st["seconds"] > 0 else 0.0)
-        log(f"2-D trap prec={prec} K={K} M={M}: {st['iters']} iters, {el:.3f} s, stage launch "
-            f"{per_launch * 1e6:.2f} us (includes the field conversions of the period)")
+        log(f"2-D trap prec={prec} K={K} M={M}: {st['iters']} iters, {el:.3f} s, {period_stage * 1e6:.2f} us per "
+            f"stage of a period, stage launch {per_launch * 1e6:.2f} us (with the period's field conversions)")
     f32, f64 = res[cmcg.CMCG_FP32], res[cmcg.CMCG_FP64]
     K = f32["K"]
     bpe = stage2d_bytes_per_element(3, 4)
@@ -642,7 +649,8 @@ def trap2d_bench(a):
                         "traffic": measured_traffic("k_stage2d<float,3,true>", K, MEASURED_TRAFFIC_2D, "kernels2d.hip"),
                         "kernel": "k_stage2d<float,3,true>",
                         "avg_launch_us": f32["per_launch"] * 1e6, "bytes_per_launch": bpe * K,
-                        "fp64_avg_launch_us": f64["per_launch"] * 1e6}}
+                        "fp64_avg_launch_us": f64["per_launch"] * 1e6},
+           "period_us_per_stage": f32["period_stage"] * 1e6, "fp64_period_us_per_stage": f64["period_stage"] * 1e6}
     if not a.no_cpu:
         out["cpu_baseline"] = cpu_baseline_2d(w, max(a.cpu_steps, 20))
     print(json.dumps(out), flush=True)

@@ -96,7 +96,11 @@ typedef struct cmcg_options {
                             cubic-Hermite filter                                */
     int flux;            /* CMCG_FLUX_UPWIND (the paper's) or _CENTRED (tests);
                             impedance faces are always upwind                   */
-    int use_graph;       /* 1: replay each period from a captured hipGraph      */
+    int use_graph;       /* 1: run each period as one launch (single-frequency
+                            problems whose element blocks fit on the device at
+                            once, outside the serving engine) or replay it
+                            from a captured hipGraph; 0: launch its stages one
+                            by one.  The results are the same, bit for bit      */
     int residual_refresh;/* > 0: every this many iterations replace R by the
                             true gradient (costs two periods); <= 0 = never.
                             FP32 fields keep the state compensated (FP32 +

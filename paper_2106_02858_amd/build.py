@@ -37,7 +37,7 @@ def hipcc() -> str:
 
 
 def _scratch_kernels(remarks: str):
-    """Stage kernels that the compiler's resource-usage remarks show using
+    """Stage and period kernels that the compiler's resource-usage remarks show using
     per-lane scratch memory (a spill, or a dynamically indexed local array)."""
     bad, name = [], None
     for line in remarks.splitlines():
@@ -46,7 +46,7 @@ def _scratch_kernels(remarks: str):
             name = m.group(1)
             continue
         m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
-        if m and name and "k_stage" in name and int(m.group(1)) > 0:
+        if m and name and ("k_stage" in name or "k_period" in name) and int(m.group(1)) > 0:
             bad.append(f"{name} ({m.group(1)} B/lane)")
     return bad
 

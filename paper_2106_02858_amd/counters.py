@@ -58,8 +58,9 @@ def main() -> int:
               flush=True)
         U0 = torch.randn((K, 3, Np), dtype=torch.float64, device=dev) * 1e-3
         UT = torch.empty_like(U0)
+        opts = cmcg.cmcg_options_default(use_graph=0)  # stage launches (with use_graph the period is one launch)
         for _ in range(a.periods):
-            cmcg.cmcg_debug_period(p, U0, UT, 1, False)
+            cmcg.cmcg_debug_period(p, U0, UT, 1, False, opts=opts)
         torch.cuda.synchronize()
         return copy_calibration(a, dev)
     if a.batched:

@@ -35,6 +35,10 @@ struct Batch {
     hipStream_t cap = nullptr;
     std::map<int, hipGraphExec_t> graphs;
     bool no_capture = false;  // periods without a captured graph run eagerly
+    bool resident_ok = false;  // periods may run as one launch
+    DevBuf order;              // the active members
+    int nactive = 0;
+    std::unique_ptr<Resident> resident;
     ~Batch() {
         for (auto& kv : graphs) (void)hipGraphExecDestroy(kv.second);
         if (cap) (void)hipStreamDestroy(cap);
@@ -50,71 +54,9 @@ void build_table(Batch& bt, hipStream_t st) {
     const int B = bt.B, S = bt.S;
     std::vector<double> tab((size_t)(bt.Mmax + 1) * S * B * kMemberParams, 0.0);
     std::vector<double> fwr(B), fwi(B);
-    const double two_pi = 2.0 * M_PI;
     for (int b = 0; b < B; ++b) {
-        const StepCfg& c = bt.cfg[b];
-        const int M = c.M;
-        const double dt = c.dt;
-        const double twoT = 2.0 / c.T;
-        std::complex<double> xi[4];
-        if (bt.scheme == 4) hermite_weights(bt.P[b]->omega, dt, xi);
-        auto ph = [&](double m) { return std::complex<double>(std::cos(two_pi * m / M), -std::sin(two_pi * m / M)); };
-        for (int m = 0; m <= bt.Mmax; ++m) {
-            for (int s = 0; s < S; ++s) {
-                double* p = &tab[(((size_t)m * S + s) * B + b) * kMemberParams];
-                double cs = 0;  // stage time offset in steps
-                if (bt.scheme == 2) {
-                    if (s == 0) {
-                        p[0] = 0.5 * dt;
-                    } else {
-                        p[2] = dt;
-                        cs = 0.5;
-                    }
-                } else {
-                    if (s == 0) {
-                        p[0] = 0.5 * dt;
-                        p[1] = dt / 6.0;
-                    } else if (s == 1) {
-                        p[0] = 0.5 * dt;
-                        p[1] = dt / 3.0;
-                        cs = 0.5;
-                    } else if (s == 2) {
-                        p[0] = dt;
-                        p[1] = dt / 3.0;
-                        cs = 0.5;
-                    } else {
-                        p[2] = dt / 6.0;
-                        cs = 1.0;
-                    }
-                }
-                const int mm = m < M ? m : M;  // the extra row holds level M_b
-                const double phase = two_pi * (mm + cs) / M;
-                p[3] = std::cos(phase);
-                p[4] = std::sin(phase);
-                if (s == 0) {
-                    std::complex<double> wa, wb;
-                    if (m < M) {
-                        if (bt.scheme == 2) {
-                            wa = ph(m) * ((m == 0 ? 1.0 : 2.0) / M);
-                        } else {
-                            wa = twoT * ph(m) * xi[0];
-                            wb = twoT * ph(m) * xi[2];
-                            if (m >= 1) {
-                                wa += twoT * ph(m - 1) * xi[1];
-                                wb += twoT * ph(m - 1) * xi[3];
-                            }
-                        }
-                    } else if (bt.scheme == 4) {  // level M_b: interval [t_{M-1}, t_M] only
-                        wa = twoT * ph(M - 1) * xi[1];
-                        wb = twoT * ph(M - 1) * xi[3];
-                    }
-                    p[5] = wa.real();
-                    p[6] = wa.imag();
-                    p[7] = wb.real();
-                    p[8] = wb.imag();
-                }
-            }
-        }
+        const int M = bt.cfg[b].M;
+        fill_step_table(tab, B, b, bt.Mmax, bt.cfg[b], bt.P[b]->omega);
         fwr[b] = 1.0 / M;  // trapezoid weight of U_M (e^{-i w T} = 1)
         fwi[b] = 0.0;
     }
@@ -260,19 +202,63 @@ void run_batch_period(Batch& bt, bool src, bool filt, bool use_graph, hipStream_
     CMCG_HIP(hipGraphLaunch(batch_graph(bt, src, filt), st));
 }
 
+// The period of every active member as one launch; false when it has to run
+// by stage launches.
+bool resident_batch_period(Batch& bt, bool src, bool filt, bool use_graph, hipStream_t st) {
+    if (!use_graph || !bt.resident_ok || (bt.resident && bt.resident->off) || !resident_variant(*bt.sp)) return false;
+    if (!bt.resident) bt.resident.reset(new Resident());
+    PeriodArgs a{};
+    a.U = bt.U.p;
+    a.Ulo = bt.Ulo.p;
+    a.geo = bt.geo.p;
+    a.conn = bt.sp->conn.as<int>();
+    a.Sre = bt.Sre.p;
+    a.Sim = bt.Sim.p;
+    a.smask = bt.smask.as<uint32_t>();
+    a.Fre = bt.Fre.as<double>();
+    a.Fim = bt.Fim.as<double>();
+    a.K = bt.sp->K;
+    a.scheme = bt.scheme;
+    a.M = bt.Mmax;
+    a.members = bt.B;
+    a.src_rows = src ? bt.src_rows : 0;
+    a.filter = filt ? 1 : 0;
+    a.msteps = bt.msteps.as<int>();
+    a.order = bt.order.as<int>();
+    a.mtab = bt.mtab.as<double>();
+    a.bstride = bt.n();
+    a.gstride = bt.shared_geo ? 0 : (int64_t)geo_values(*bt.sp) * bt.sp->K;
+    a.sstride = bt.n();
+    if (filt) {
+        launch_zero(bt.Fre.p, bt.Fre.bytes, st);
+        launch_zero(bt.Fim.p, bt.Fim.bytes, st);
+    }
+    if (!run_resident(*bt.resident, *bt.sp, a, bt.nactive, st)) return false;
+    if (filt && bt.scheme == 2)
+        launch_filter_add_batch(bt.sp->precision, bt.U.p, bt.fw_re.as<double>(), bt.fw_im.as<double>(),
+                                bt.Fre.as<double>(), bt.Fim.as<double>(), bt.n(), bt.B, st);
+    return true;
+}
+
 // Y_b = S^d P_b S^d X_b - sub_b for every member (X == nullptr: zero state)
 void batch_apply(Batch& bt, const cmcg_options* o, const double* X, double* Yo, const double* sub, int direction,
                  bool src, bool filt, hipStream_t st) {
     const SpaceData& s = *bt.sp;
     const int flip = direction < 0 ? 1 : 0;
     const int64_t N = bt.n() * bt.B;
-    if (X) {
-        to_field_dim(s, X, bt.U.p, bt.Ulo.p, N, flip, st);
-    } else {
-        launch_zero(bt.U.p, bt.U.bytes, st);
-        if (bt.Ulo.p) launch_zero(bt.Ulo.p, bt.Ulo.bytes, st);
+    auto start = [&] {
+        if (X) {
+            to_field_dim(s, X, bt.U.p, bt.Ulo.p, N, flip, st);
+        } else {
+            launch_zero(bt.U.p, bt.U.bytes, st);
+            if (bt.Ulo.p) launch_zero(bt.Ulo.p, bt.Ulo.bytes, st);
+        }
+    };
+    start();
+    if (!resident_batch_period(bt, src && direction > 0, filt, o->use_graph != 0, st)) {
+        if (bt.resident && bt.resident->off) start();  // a launch that gave up left no state
+        run_batch_period(bt, src && direction > 0, filt, o->use_graph != 0, st);
     }
-    run_batch_period(bt, src && direction > 0, filt, o->use_graph != 0, st);
     if (Yo) from_field_dim(s, bt.U.p, bt.Ulo.p, Yo, sub, N, flip, st);
 }
 
@@ -306,6 +292,13 @@ void batch_axpby(Batch& bt, const std::vector<double>& a, const double* x, const
 
 void set_active(Batch& bt, const std::vector<int>& act, hipStream_t st) {
     CMCG_HIP(hipMemcpyAsync(bt.active.p, act.data(), bt.B * sizeof(int), hipMemcpyHostToDevice, st));
+    std::vector<int> order;
+    for (int b = 0; b < bt.B; ++b)
+        if (act[b]) order.push_back(b);
+    bt.nactive = (int)order.size();
+    bt.order.alloc(bt.B * sizeof(int));
+    if (bt.nactive)
+        CMCG_HIP(hipMemcpyAsync(bt.order.p, order.data(), order.size() * sizeof(int), hipMemcpyHostToDevice, st));
     CMCG_HIP(hipStreamSynchronize(st));
 }
 
@@ -635,6 +628,7 @@ void solve_batch(cmcg_problem* const* probs, int B, const cmcg_options* o, hipSt
     if (!probs || B < 1 || !out) fail(CMCG_ERR_ARG, "solve_batch: NULL argument or empty batch");
     Batch bt;
     setup_batch(bt, probs, B, o, st);
+    bt.resident_ok = true;
     solve_prepared(bt, o, st, out);
 }
 

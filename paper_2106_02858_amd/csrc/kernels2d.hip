@@ -18,10 +18,12 @@
 #include <algorithm>
 #include <string>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
 #include "launch.h"
+#include "tagged.h"
 
 namespace cmcg {
 
@@ -171,6 +173,23 @@ __device__ __forceinline__ bool member_args2d(const StageArgs& in, StageArgs& a)
     if (in.Sre) a.Sre = (const T*)in.Sre + (int64_t)b * in.sstride;
     if (in.Sim) a.Sim = (const T*)in.Sim + (int64_t)b * in.sstride;
     return true;
+}
+
+// The arithmetic shared by the stage and the period kernel is written with
+// explicit fma(): left to the compiler, the two contracted the same
+// expressions differently and their results parted in the last bit.
+//
+// Upwind flux (e, h1, h2) at one edge node, g = the edge's normal and flux
+// coefficients.
+template <typename T>
+__device__ __forceinline__ void upwind2d(const T* g, T em, T h1m, T h2m, T ep, T h1p, T h2p, T (&fl)[3]) {
+    const T n0 = g[0], n1 = g[1];
+    const T cE1 = g[2], cE2 = g[3], cH1 = g[4], cH2 = g[5];
+    const T de = ep - em, dh1 = h1p - h1m, dh2 = h2p - h2m;
+    const T ndh = fma(n0, dh1, n1 * dh2);
+    fl[0] = fma(cE1, de, -cE2 * fma(n0, dh2, -n1 * dh1));
+    fl[1] = fma(cH1, fma(-ndh, n0, dh1), cH2 * (n1 * de));
+    fl[2] = fma(cH1, fma(-ndh, n1, dh2), -cH2 * (n0 * de));
 }
 
 template <typename T, int Q, bool EARLY>
@@ -343,15 +362,13 @@ __global__ __launch_bounds__(64) void k_stage2d(StageArgs args, int64_t per) {
     for (int i = 0; i < NP; ++i) {
         const T A = __shfl(d1[i], srcA);
         const T B = __shfl(d2[i], srcB);
-        acc[i] = sa * A + sb * B;
+        acc[i] = fma(sa, A, sb * B);
     }
 
     // ---- upwind flux of the lane's component on each edge, lifted
     auto face = [&](int f, const T (&tr)[NFP][3]) {
         const int code = sC[elc * 3 + f];
         const T* g = &gg[4 + 6 * f];
-        const T n0 = g[0], n1 = g[1];
-        const T cE1 = g[2], cE2 = g[3], cH1 = g[4], cH2 = g[5];
         T fl[NFP];
 #pragma unroll
         for (int k = 0; k < NFP; ++k) {
@@ -365,12 +382,13 @@ __global__ __launch_bounds__(64) void k_stage2d(StageArgs args, int64_t per) {
                 h1p = h1m;
                 h2p = h2m;
             }  // impedance ghost (homogeneous part): zero exterior state, as gathered
-            const T de = ep - em, dh1 = h1p - h1m, dh2 = h2p - h2m;
-            if (c == 0) {
-                fl[k] = cE1 * de - cE2 * (n0 * dh2 - n1 * dh1);
+            T v[3];
+            if (c == 0) {  // branches: one component is needed, and selects cost registers
+                upwind2d(g, em, h1m, h2m, ep, h1p, h2p, v);
+                fl[k] = v[0];
             } else {
-                const T ndh = n0 * dh1 + n1 * dh2;
-                fl[k] = c == 1 ? cH1 * (dh1 - ndh * n0) + cH2 * (n1 * de) : cH1 * (dh2 - ndh * n1) - cH2 * (n0 * de);
+                upwind2d(g, em, h1m, h2m, ep, h1p, h2p, v);
+                fl[k] = c == 1 ? v[1] : v[2];
             }
         }
 #pragma unroll
@@ -409,7 +427,7 @@ __global__ __launch_bounds__(64) void k_stage2d(StageArgs args, int64_t per) {
     if (src) {
         const T scos = (T)a.scos, ssin = (T)a.ssin;
 #pragma unroll
-        for (int i = 0; i < NP; ++i) kv[i] += scos * sr[i] - ssin * si[i];
+        for (int i = 0; i < NP; ++i) kv[i] = fma(scos, sr[i], fma(-ssin, si[i], kv[i]));
         // further harmonics of a several-frequency source (single launches only,
         // so the kernel arguments hold this problem's tables; they are indexed
         // there, not in the local copy, which would go to scratch)
@@ -482,8 +500,8 @@ __global__ __launch_bounds__(64) void k_stage2d(StageArgs args, int64_t per) {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const double ud = (double)y[i], kd = (double)kv[i];
-            fr[i] += a.fa_re * ud + a.fb_re * kd;
-            fi[i] += a.fa_im * ud + a.fb_im * kd;
+            fr[i] = fma(a.fa_re, ud, fma(a.fb_re, kd, fr[i]));
+            fi[i] = fma(a.fa_im, ud, fma(a.fb_im, kd, fi[i]));
         }
 #pragma unroll 1
         for (int h = 1; h < args.nharm; ++h) {  // each harmonic filtered at its own frequency
@@ -497,6 +515,414 @@ __global__ __launch_bounds__(64) void k_stage2d(StageArgs args, int64_t per) {
             }
         }
     }
+}
+
+// FP32 products of small matrices with one column per lane on
+// v_mfma_f32_4x4x1_16b_f32: with the A operand of one of the 16 blocks
+// broadcast to all of them (cbsz = 4, abid = the block) an instruction adds
+// A[4 g .. 4 g + 3][k] * column[k] to four rows of every lane's column, in the
+// order and with the rounding of an fma() per row (checked on the GPU).  A
+// register holds the operands of 16 instructions, so the matrices of an order
+// take a few registers instead of LDS reads, four rows a time instead of one.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <int NK, int G, typename F>
+__device__ __forceinline__ void mfma_operand(float (&m)[(NK * G + 15) / 16], int lane, F at) {
+#pragma unroll
+    for (int v = 0; v < (NK * G + 15) / 16; ++v) {
+        const int q = 16 * v + lane / 4;
+        m[v] = q < NK * G ? at(4 * (q % G) + lane % 4, q / G) : 0.f;
+    }
+}
+template <int NK, int G, int NX, size_t... I>
+__device__ __forceinline__ void mfma_steps(const float (&m)[(NK * G + 15) / 16], const float (&x)[NX], f32x4 (&acc)[G],
+                                           std::index_sequence<I...>) {
+    ((acc[I % G] = __builtin_amdgcn_mfma_f32_4x4x1f32(m[I / 16], x[I / G], acc[I % G], 4, I % 16, 0)), ...);
+}
+template <int NK, int G, int NX>
+__device__ __forceinline__ void mfma_rows(const float (&m)[(NK * G + 15) / 16], const float (&x)[NX], f32x4 (&acc)[G]) {
+    static_assert(NX >= NK, "a column value per K step");
+    mfma_steps<NK, G>(m, x, acc, std::make_index_sequence<NK * G>());
+}
+
+// ---------------------------------------------------------------------------
+// A whole period in one launch (PeriodArgs in launch.h): every workgroup keeps
+// its 21 triangles resident -- state, stage combination and low parts in
+// registers, stage input, geometry and matrices in LDS -- and the stages run
+// in a loop, so no stage pays a launch or reads its state back.  The traces
+// of edges between workgroups go through mailboxes of (value, epoch) pairs
+// (tagged.h): after its update a workgroup writes its traces into its
+// neighbours' mailboxes, and polls its own, which lie next to each other,
+// until they carry the stage's epoch.  Two buffers alternate between epochs; a
+// workgroup overwrites an epoch's mailbox two stages later, after it has read
+// that neighbour's next epoch, which the neighbour wrote after reading this
+// one.
+//
+// Four waves share a block: lanes own rows (triangle, component) as in
+// k_stage2d, each wave a quarter of the nodes for the volume, lift and update
+// work, and the threads together the 63 (q + 1) edge nodes of the flux, one
+// each.  What bounds it: one stage is one exchange (0.4-0.6 us between a store
+// and the poll that sees it) and one wave's chain of LDS round trips and
+// arithmetic (a wave alone on its SIMD issues one VALU instruction in about 8
+// clocks, so a single-wave form took twice as long).  Whole solves, per stage:
+// 22500 triangles P3 FP32 9.2 us by stage launches, 3.8 here; 4096 triangles P1
+// FP64 4.9 and 2.2; 20 members of 3600 triangles P3 FP32 22.3 and 13.6.
+// Publishing whole rows and gathering them lane by lane took 42 us a stage at
+// 22500 triangles: requests, not bytes, are what the exchange pays for.  The
+// arithmetic is that of k_stage2d, term by term, so results agree bit for bit.
+template <typename T, int Q>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 3, 8)))
+void k_period2d(PeriodArgs a, int64_t per) {
+    constexpr int NP = Dim2<Q>::NP, NFP = Dim2<Q>::NFP, NF3 = 3 * NFP;
+    constexpr bool COMP = std::is_same<T, float>::value;
+    using X = Tagged<T>;
+    constexpr int W = 4, NTH = 64 * W, ROWS = EPB * 3;
+    constexpr int NW = (NP + W - 1) / W;                     // nodes of a row per wave
+    constexpr int GD = (2 * NW + 3) / 4, GL = (NW + 3) / 4;  // groups of four output rows (D_1 and D_2; LIFT)
+    static_assert(ROWS * NFP <= NTH, "one flux node per thread");
+    // rows in LDS, padded to whole 16-byte groups: stage input and D [.][DR],
+    // flux [row][FR], LIFT [NP][FR]
+    constexpr int PV = 16 / (int)sizeof(T);
+    constexpr int DR = (NP + PV - 1) / PV * PV, FR = (NF3 + PV - 1) / PV * PV;
+    constexpr int TO = ROWS * DR;      // received traces, then the flux, behind the staged block
+    typedef T VM __attribute__((ext_vector_type(PV)));
+    // stage input [row][DR]; traces [edge][component][edge node], replaced by the flux [row][FR]
+    __shared__ __align__(16) T sS[TO + ROWS * FR];
+    __shared__ __align__(16) T sD[COMP ? 1 : 2 * NP * DR];  // FP32: in registers
+    __shared__ __align__(16) T sL[COMP ? 1 : NP * FR];
+    __shared__ T sG[EPB * kGeo2];
+    __shared__ int sX[ROWS];          // mailbox j: its edge, and the neighbour's mailbox
+    __shared__ uint8_t sE[ROWS];
+    __shared__ int sStop;
+
+    const int mem = a.order ? a.order[a.first + blockIdx.y] : 0;
+    const int64_t bx = blockIdx.x;
+    const int64_t blk = (bx & 7) * per + (bx >> 3);  // consecutive blocks on one XCD
+    const int64_t e0 = blk * EPB;
+    if (e0 >= a.K) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ne = (int)((a.K - e0) < EPB ? (a.K - e0) : EPB);
+    const int M = a.msteps ? a.msteps[mem] : a.M;
+    const int S = a.scheme == 2 ? 2 : 4;
+    const int el = lane / 3;
+    const int c = lane - 3 * el;
+    const bool act = el < ne;
+    const int elc = act ? el : 0;
+    const int row = elc * 3 + c;
+    const int base = 3 * elc;
+    const int i0 = wave * NW;  // this wave's nodes i0 .. i0 + NW - 1 (those below NP)
+    const int64_t fo = (int64_t)mem * a.bstride;
+    const int64_t grow = fo + (e0 * 3 + row) * NP + i0;
+    const int x0 = a.xstart[blk];
+    const int nitem = (a.xstart[blk + 1] - x0) * NF3;
+    const T* gm = mats2<T>() + mat2_off(Q);
+    // FP32: the wave's matrix rows as broadcast operands (mfma_rows), D's
+    // rows being D_1 at the wave's nodes, then D_2
+    float mD[(NP * GD + 15) / 16], mL[(NF3 * GL + 15) / 16];
+    if constexpr (COMP) {
+        mfma_operand<NP, GD>(mD, lane, [&](int rr, int k) {
+            const int d = rr / NW, i = i0 + rr % NW;
+            return d < 2 && i < NP ? (float)gm[(d * NP + i) * NP + k] : 0.f;
+        });
+        mfma_operand<NF3, GL>(mL, lane, [&](int u, int k) {
+            return u < NW && i0 + u < NP ? (float)gm[2 * NP * NP + (i0 + u) * NF3 + k] : 0.f;
+        });
+    }
+    {
+        const T* geo = (const T*)a.geo + (int64_t)mem * a.gstride + e0 * kGeo2;
+        for (int i = tid; i < ne * kGeo2; i += NTH) sG[i] = geo[i];
+        if constexpr (!COMP) {
+            for (int i = tid; i < 2 * NP * DR; i += NTH) sD[i] = i % DR < NP ? gm[i / DR * NP + i % DR] : T(0);
+            for (int i = tid; i < NP * FR; i += NTH)
+                sL[i] = i % FR < NF3 ? gm[2 * NP * NP + i / FR * NF3 + i % FR] : T(0);
+        }
+        for (int i = tid; i < TO + ROWS * FR; i += NTH) sS[i] = T(0);
+        if (tid == 0) sStop = 0;
+        if (tid < ne * 3) {
+            const int id = a.xslot[e0 * 3 + tid];
+            const int cd = a.conn[e0 * 3 + tid];
+            if (id >= 0) {
+                sE[id - x0] = (uint8_t)tid;
+                sX[id - x0] = a.xslot[(int64_t)(cd >> 5) * 3 + ((cd >> 3) & 3)];
+            }
+        }
+    }
+    // own state: nodes i0 + u of the lane's row
+    T up[NW], yo[NW], ap[NW];
+    float lo[COMP ? NW : 1];
+    bool mine[NW];
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+        mine[u] = act && i0 + u < NP;
+        up[u] = mine[u] ? ((const T*)a.U)[grow + u] : T(0);
+        yo[u] = up[u];
+        ap[u] = T(0);
+        if constexpr (COMP) lo[u] = mine[u] ? from_bf16(((const uint16_t*)a.Ulo)[grow + u]) : 0.f;
+    }
+    __syncthreads();
+
+    // this thread's flux node, node k of edge t: LDS offsets of the own trace
+    // and of the neighbour's (in the staged block, or received; a boundary's:
+    // the own), packed; the place of the edge's geometry (12 bits) and of the
+    // flux (12 bits) with what the neighbour is (8 bits): the offset between
+    // its components, 0 on a wall with the PEC ghost, 1 with the impedance ghost
+    static_assert(TO + ROWS * FR < 65536 && EPB * kGeo2 < 4096 && ROWS * FR < 4096 && NFP > 1 && DR < 256,
+                  "packed offsets");
+    uint32_t trace, place;
+    {
+        const int t = tid < ROWS * NFP ? tid / NFP : 0, k = tid < ROWS * NFP ? tid % NFP : 0;
+        const int e = t / 3, f = t - 3 * e;
+        const int code = t < ne * 3 ? a.conn[e0 * 3 + t] : -2;
+        const int64_t nb = code >> 5;
+        const int nf = (code >> 3) & 3, kk = (code & 7) ? NFP - 1 - k : k;
+        const bool in = nb >= e0 && nb < e0 + ne;
+        const int own = e * 3 * DR + edge_node<Q>(f, k);
+        const int nbo = code < 0 ? own : in ? (int)(nb - e0) * 3 * DR + edge_node<Q>(nf, kk) : TO + t * NF3 + kk;
+        const int what = code == -1 ? 0 : code < 0 ? 1 : in ? DR : NFP;
+        trace = (uint32_t)own | ((uint32_t)nbo << 16);
+        place = (uint32_t)(e * kGeo2 + 4 + 6 * f) | ((uint32_t)(e * 3 * FR + f * NFP + k) << 12) |
+                ((uint32_t)what << 24);
+    }
+    // mailbox value i: its LDS source, its place with the neighbour, and where
+    // the value received in its stead goes; a thread's first one is kept packed
+    auto mail = [&](int i, int& src, uint32_t& dst, int& rcv) {
+        const int j = i / NF3, r = i - j * NF3;
+        const int cc = r / NFP, k = r - cc * NFP;
+        const int t = sE[j], f = t % 3;
+        src = (t - f + cc) * DR + edge_node<Q>(f, k);
+        dst = (uint32_t)(sX[j] * NF3 + r) * X::W;
+        rcv = TO + t * NF3 + r;
+    };
+    uint32_t mlds = 0, mdst = 0;
+    if (tid < nitem) {
+        int src, rcv;
+        mail(tid, src, mdst, rcv);
+        mlds = (uint32_t)src | ((uint32_t)rcv << 16);
+    }
+
+    uint32_t epoch = a.epoch;
+    const int64_t half = (int64_t)a.members * a.next * (NF3 * X::W);  // words of one buffer
+    unsigned long long* const xch = a.xch + (int64_t)mem * a.next * (NF3 * X::W);
+    const unsigned long long* const inbox = xch + (int64_t)x0 * (NF3 * X::W);
+    auto publish = [&]() {  // the stage input for this epoch, to LDS and to the neighbours
+#pragma unroll
+        for (int u = 0; u < NW; ++u)
+            if (mine[u]) sS[row * DR + i0 + u] = yo[u];
+        __syncthreads();
+        unsigned long long* const q = xch + (epoch & 1) * half;
+        if (tid < nitem) X::put(q + mdst, sS[mlds & 0xffffu], epoch);
+        for (int i = tid + NTH; i < nitem; i += NTH) {
+            int src, rcv;
+            uint32_t dst;
+            mail(i, src, dst, rcv);
+            X::put(q + dst, sS[src], epoch);
+        }
+    };
+    publish();
+
+    const int srcA = c == 0 ? base + 2 : base;
+    const int srcB = c == 0 ? base + 1 : base;
+    const T sa = c == 1 ? T(0) : T(-1);
+    const T sb = c == 2 ? T(0) : T(1);
+    const bool src = c < a.src_rows;
+    // RK4 with the filter ends with one more right-hand side at the last level
+    const bool tail = a.filter && S == 4;
+    for (int m = 0; m < M + (tail ? 1 : 0); ++m) {
+        const int ns = m < M ? S : 1;
+        for (int s = 0; s < ns; ++s) {
+            // an offset of zero that the compiler cannot see: matrices and
+            // geometry are read from LDS in every stage (hoisted out of the
+            // loop they would take every register), and packed words are
+            // unpacked there
+            int z = 0;
+            asm volatile("" : "+v"(z));
+            asm volatile("" : "+v"(trace), "+v"(place), "+v"(mlds), "+v"(mdst));
+            const double* tab = a.mtab + (((int64_t)(m < M ? m : a.M) * S + s) * a.members + mem) * kMemberParams;
+            const T cy = (T)tab[0], ca = (T)tab[1], cu = (T)tab[2], scos = (T)tab[3], ssin = (T)tab[4];
+            // request the neighbours' traces; they travel during the volume work
+            const unsigned long long* const in = inbox + (epoch & 1) * half;
+            Inbox<T, 1, NTH> box;
+            box.request(in, 0, nitem, tid);
+
+            // ---- volume: physical derivatives of the lane's component at the
+            // wave's nodes, exchanged between the triangle's lanes
+            const T* gg = &sG[elc * kGeo2 + z];
+            T acc[NW];
+            {
+                T y[DR], r0[NW], r1[NW];
+                const T* yr = &sS[row * DR + z];
+                const T g00 = gg[0], g01 = gg[1], g10 = gg[2], g11 = gg[3];
+#pragma unroll
+                for (int v = 0; v < DR / PV; ++v) {
+                    const VM t = *reinterpret_cast<const VM*>(yr + v * PV);
+#pragma unroll
+                    for (int u = 0; u < PV; ++u) y[v * PV + u] = t[u];
+                }
+                if constexpr (COMP) {
+                    f32x4 d[GD] = {};
+                    mfma_rows<NP, GD>(mD, y, d);
+#pragma unroll
+                    for (int u = 0; u < NW; ++u) {
+                        r0[u] = d[u / 4][u % 4];
+                        r1[u] = d[(NW + u) / 4][(NW + u) % 4];
+                    }
+                } else {
+                    int zr[2] = {z, z};
+#pragma unroll
+                    for (int u = 0; u < NW; ++u) {
+                        const int i = i0 + u < NP ? i0 + u : NP - 1;
+                        const T* D = sD + zr[u & 1];
+                        r0[u] = r1[u] = T(0);
+#pragma unroll
+                        for (int v = 0; v < DR / PV; ++v) {
+                            const VM m0 = *reinterpret_cast<const VM*>(D + i * DR + v * PV);
+                            const VM m1 = *reinterpret_cast<const VM*>(D + (NP + i) * DR + v * PV);
+#pragma unroll
+                            for (int w = 0; w < PV; ++w)
+                                if (v * PV + w < NP) {
+                                    r0[u] = fma(m0[w], y[v * PV + w], r0[u]);
+                                    r1[u] = fma(m1[w], y[v * PV + w], r1[u]);
+                                }
+                        }
+                        // the matrix rows of u + 2 are requested when u is done:
+                        // all of them at once would take every register
+                        asm volatile("" : "+v"(zr[u & 1]) : "v"(r1[u]));
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < NW; ++u) {
+                    const T d1 = fma(g00, r0[u], g10 * r1[u]);
+                    const T d2 = fma(g01, r0[u], g11 * r1[u]);
+                    const T A = __shfl(d1, srcA);
+                    const T B = __shfl(d2, srcB);
+                    acc[u] = fma(sa, A, sb * B);
+                }
+            }
+
+            if (!box.settle(in, nitem, tid, epoch, a, [&](int i, int r, T v) {
+                    int src, rcv = (int)(mlds >> 16);
+                    uint32_t dst;
+                    if (r > 0) mail(i, src, dst, rcv);
+                    sS[rcv] = v;
+                }))
+                sStop = 1;
+            __syncthreads();
+            if (sStop) return;
+
+            // ---- upwind flux, all three components at the thread's edge node
+            T fx[3];
+            {
+                const T* g = &sG[(place & 4095u) + z];
+                const T* om = &sS[trace & 0xffffu];
+                const T* np = &sS[trace >> 16];
+                const int what = place >> 24;
+                const int st = what > 1 ? what : DR;
+                const T em = om[0], h1m = om[DR], h2m = om[2 * DR];
+                T ep = np[0], h1p = np[st], h2p = np[2 * st];
+                if (what == 0) ep = -em;  // PEC ghost: e+ = -e-, h+ = h-
+                if (what == 1) ep = h1p = h2p = T(0);  // impedance ghost (homogeneous part): zero exterior state
+                upwind2d(g, em, h1m, h2m, ep, h1p, h2p, fx);
+            }
+            __syncthreads();  // every trace is read
+            if (tid < ROWS * NFP) {
+                T* o = &sS[TO + ((place >> 12) & 4095u)];
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) o[cc * FR] = fx[cc];
+            }
+            __syncthreads();
+
+            // ---- lift and update of the wave's nodes
+            {
+                T fl[FR];
+                const T* fr = &sS[TO + row * FR];
+#pragma unroll
+                for (int v = 0; v < FR / PV; ++v) {
+                    const VM t = *reinterpret_cast<const VM*>(fr + v * PV);
+#pragma unroll
+                    for (int w = 0; w < PV; ++w) fl[v * PV + w] = t[w];
+                }
+                if constexpr (COMP) {
+                    f32x4 d[GL] = {};
+#pragma unroll
+                    for (int u = 0; u < NW; ++u) d[u / 4][u % 4] = acc[u];
+                    mfma_rows<NF3, GL>(mL, fl, d);
+#pragma unroll
+                    for (int u = 0; u < NW; ++u) acc[u] = d[u / 4][u % 4];
+                } else {
+                    int zr[2] = {z, z};
+#pragma unroll
+                    for (int u = 0; u < NW; ++u) {
+                        const int i = i0 + u < NP ? i0 + u : NP - 1;
+                        const T* L = sL + zr[u & 1];
+#pragma unroll
+                        for (int v = 0; v < FR / PV; ++v) {
+                            const VM t = *reinterpret_cast<const VM*>(L + i * FR + v * PV);
+#pragma unroll
+                            for (int w = 0; w < PV; ++w)
+                                if (v * PV + w < NF3) acc[u] = fma(t[w], fl[v * PV + w], acc[u]);
+                        }
+                        asm volatile("" : "+v"(zr[u & 1]) : "v"(acc[u]));
+                    }
+                }
+            }
+            const T inv = gg[c == 0 ? 22 : 23];
+            const T sig = c == 0 ? gg[24] : T(0);
+            T kv[NW];
+#pragma unroll
+            for (int u = 0; u < NW; ++u) kv[u] = fma(inv, acc[u], -sig * yo[u]);
+            if (src) {
+                const int64_t so = (int64_t)mem * a.sstride + (e0 * 3 + row) * NP + i0;
+#pragma unroll
+                for (int u = 0; u < NW; ++u)
+                    if (mine[u])
+                        kv[u] = fma(scos, ((const T*)a.Sre)[so + u], fma(-ssin, ((const T*)a.Sim)[so + u], kv[u]));
+            }
+            if (a.filter && s == 0) {
+                const double fa_re = tab[5], fa_im = tab[6], fb_re = tab[7], fb_im = tab[8];
+                double* fr = a.Fre + grow;
+                double* fi = a.Fim + grow;
+#pragma unroll
+                for (int u = 0; u < NW; ++u)
+                    if (mine[u]) {
+                        const double ud = (double)yo[u], kd = (double)kv[u];
+                        fr[u] = fma(fa_re, ud, fma(fb_re, kd, fr[u]));
+                        fi[u] = fma(fa_im, ud, fma(fb_im, kd, fi[u]));
+                    }
+            }
+            if (m >= M) break;  // the last level's right-hand side: filter only
+            const bool last = s == S - 1;
+            if (!last) {
+#pragma unroll
+                for (int u = 0; u < NW; ++u) {
+                    if (S == 4) ap[u] = s > 0 ? fma(ca, kv[u], ap[u]) : COMP ? ca * kv[u] : fma(ca, kv[u], yo[u]);
+                    yo[u] = fma(cy, kv[u], up[u]);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < NW; ++u) {
+                    if constexpr (COMP) {
+                        float sum, e;
+                        two_sum(up[u], S == 4 ? fma(cu, kv[u], ap[u]) + lo[u] : fma(cu, kv[u], lo[u]), sum, e);
+                        up[u] = sum;
+                        lo[u] = from_bf16(to_bf16(e));
+                    } else {
+                        up[u] = fma(cu, kv[u], S == 4 ? ap[u] : up[u]);
+                    }
+                    yo[u] = up[u];
+                }
+            }
+            if (m + 1 < M || !last || tail) {
+                ++epoch;
+                publish();
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < NW; ++u)
+        if (mine[u]) {
+            ((T*)a.U)[grow + u] = up[u];
+            if constexpr (COMP) ((uint16_t*)a.Ulo)[grow + u] = to_bf16(lo[u]);
+        }
 }
 
 template <typename T>
@@ -673,6 +1099,11 @@ void stage2d(const StageArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((k_stage2d<T, Q, false>), grid, dim3(64), 0, s, a, per);
 }
 
+template <typename T, int Q>
+bool period2d(const PeriodArgs& a, int n, hipStream_t s) {
+    return launch_resident(k_period2d<T, Q>, (a.K + EPB - 1) / EPB, n, 256, a, s);
+}
+
 }  // namespace
 
 void upload_constants2d(int q, const double* D, const double* LIFT, const double* M, const int* fnode) {
@@ -706,6 +1137,15 @@ void launch_stage2d(int q, int precision, const StageArgs& a, hipStream_t s) {
         else stage2d<float, 3>(a, s);
     }
     check2();
+}
+
+bool launch_period2d(int q, int precision, const PeriodArgs& a, int n, hipStream_t s) {
+    if (precision == CMCG_FP64) {
+        if (q == 1) return period2d<double, 1>(a, n, s);
+        return q == 2 ? period2d<double, 2>(a, n, s) : period2d<double, 3>(a, n, s);
+    }
+    if (q == 1) return period2d<float, 1>(a, n, s);
+    return q == 2 ? period2d<float, 2>(a, n, s) : period2d<float, 3>(a, n, s);
 }
 
 void launch_to_field2d(int precision, int Np, const double* X, void* U, void* Ulo, int64_t n, int flipH,

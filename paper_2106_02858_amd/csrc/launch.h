@@ -103,6 +103,45 @@ constexpr int kMaxHarm = 8;
 // per-member scalars of a batched stage: cy, ca, cu, scos, ssin, fa_re, fa_im, fb_re, fb_im
 constexpr int kMemberParams = 9;
 
+// A whole period in one launch, for meshes whose element blocks all fit on the
+// device at once (kernels2d.hip k_period2d): U (and Ulo) advance M steps in
+// place.  Member b of a batch (grid.y) offsets fields, source and filter by
+// b * bstride / sstride and the geometry by b * gstride.
+struct PeriodArgs {
+    void* U;
+    void* Ulo;               // FP32 fields: bfloat16 low parts
+    const void* geo;
+    const int* conn;
+    const void *Sre, *Sim;   // read when src_rows > 0
+    const uint32_t* smask;   // 3-D: source element mask (nullable)
+    double *Fre, *Fim;       // filter accumulators, added to when filter is set
+    int64_t K;
+    int scheme, M, members;  // M: steps per period (the most of any member)
+    int src_rows, filter;
+    const int* msteps;       // steps per member (nullable: M)
+    const int* order;        // the members that run, in launch order (nullable: member 0)
+    int first;               // of the launch, in order
+    const double* mtab;      // stage scalars [step 0..M][stage][member][kMemberParams]; row M: last filter level
+    int64_t bstride, gstride, sstride;
+    // exchange between workgroups.  Face f of element e whose neighbour is in
+    // another element block has mailbox xslot[e][f] (-1: none), the mailboxes
+    // of block b being xstart[b] .. xstart[b + 1] - 1 of next; a mailbox holds
+    // the neighbour's trace, [component][face node] in the neighbour's node
+    // order, as (value, epoch) pairs.  xch: two buffers of members * next
+    // mailboxes, for odd and even epochs; epochs epoch, epoch + 1, ... are
+    // this launch's and appear nowhere in the buffers yet.
+    const int *xslot, *xstart;
+    int64_t next;
+    unsigned long long* xch;
+    uint32_t epoch;
+    uint32_t* abort;         // device word: the epoch of a launch that gives up
+    int* failed;             // host-visible: set to 1 when the launch gave up (its output is then void)
+    unsigned long long limit;  // longest wait for a neighbour, in wall-clock ticks
+};
+constexpr int64_t kPeriodMaxValues = 1 << 26;  // exchanged values of one buffer (32-bit offsets)
+// Elements of one workgroup of the stage and period kernels.
+inline int element_block(int dim) { return dim == 2 ? 21 : 10; }
+
 // Source element mask (StageArgs::smask) of a [nharm][K][6][Np] source: one
 // 32-bit word per element block; only exact zeros clear a bit, so skipping the
 // source of a cleared element changes no value.
@@ -187,6 +226,10 @@ void launch_nonfinite(const double* X, int64_t n, int* out_dev, hipStream_t s);
 // member, StageArgs::mtab non-null) as in 3-D, without the source mask.
 void upload_constants2d(int q, const double* D, const double* LIFT, const double* M, const int* fnode);
 void launch_stage2d(int q, int precision, const StageArgs& a, hipStream_t s);
+// One period of the n members of a.order in one launch, or a launch per group
+// of members that fits on the device at once; false (nothing launched) when
+// one member does not.
+bool launch_period2d(int q, int precision, const PeriodArgs& a, int n, hipStream_t s);
 void launch_to_field2d(int precision, int Np, const double* X, void* U, void* Ulo, int64_t n, int flipH,
                        hipStream_t s);
 void launch_from_field2d(int precision, int Np, const void* U, const void* Ulo, double* Y, const double* sub,

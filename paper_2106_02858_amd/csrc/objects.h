@@ -7,6 +7,7 @@
 #include <functional>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -65,6 +66,11 @@ struct SpaceData {
     int64_t K = 0, ndof = 0;
     std::vector<int32_t> conn_h;
     DevBuf conn;
+    // mailboxes of the one-launch periods (PeriodArgs::xslot, xstart), built
+    // when the first such period runs on the space
+    std::once_flag x_once;
+    DevBuf xslot, xstart;
+    int64_t next = 0;
     size_t esize() const { return precision == CMCG_FP64 ? 8 : 4; }
 };
 
@@ -100,6 +106,17 @@ struct StepCfg {
     double alpha = 1.0;  // flux parameter
     double cq = 0;       // CFL constant of the step rule
     int lts = 1;         // > 1: local time stepping with lts fine substeps (lts.cpp)
+    bool resident = false;  // periods may run as one launch (Resident): calls that run alone on their thread
+};
+
+// What the one-launch periods of a problem or batch keep: the exchange
+// buffers, the stage scalar table of a single problem, and the running epoch.
+struct Resident {
+    DevBuf xch, mtab;
+    HostPinned failed{1};    // [0]: set by a launch that gave up
+    uint32_t epoch = 0;      // the last one used
+    int tab_M = 0, tab_scheme = 0;
+    bool off = false;        // does not fit on this device, or a launch has given up
 };
 
 }  // namespace cmcg
@@ -132,6 +149,7 @@ struct cmcg_problem {
     int64_t lts_fine = 0, lts_nhb = 0, lts_nh2b = 0;
     std::map<int64_t, hipGraphExec_t> lts_graphs;  // captured LTS periods
     std::unique_ptr<cmcg::HostPinned> pinned;
+    std::unique_ptr<cmcg::Resident> resident;
     hipStream_t cap_stream = nullptr;
     std::map<int64_t, hipGraphExec_t> graphs;
     ~cmcg_problem() {
@@ -165,6 +183,7 @@ struct CgRun {
     int phase = kDone;
     int64_t n = 0;
     int it = 0, periods = 0, refresh = 0, limit = 0;
+    bool resident = false;  // set before start(): nothing else of this thread waits while a period runs
     bool fixed = false, stopped = false, diverged = false;
     double rr = 0, rr0 = 0, rel = 1, t6 = -1, J0 = 0, best = 0;
     std::chrono::steady_clock::time_point t0;
@@ -200,6 +219,18 @@ int current_device();
 StepCfg step_config(const cmcg_problem* p, const cmcg_options* o);
 void hermite_weights(double omega, double dt, std::complex<double> xi[4]);
 void build_geo(cmcg_problem* p, double alpha);
+// Stage scalars of one member for every (step, stage) of a period, plus one
+// row (step Mmax, stage 0) with its last filter level, into rows
+// [step][stage][member][kMemberParams] of tab (StageArgs::mtab, PeriodArgs::mtab).
+void fill_step_table(std::vector<double>& tab, int B, int b, int Mmax, const StepCfg& c, double omega);
+// One period of a.M steps of n members as one launch on st (PeriodArgs), waited for: true when the
+// launch ran to its end (a.U then holds the result); false when nothing ran
+// or the launch gave up (a.U is then void, r.off is set).  a's exchange
+// fields are filled in here.
+bool run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t st);
+// Whether the current stage variant of a space leaves its periods to
+// run_resident (none chosen by hand, and the arithmetic is the same).
+bool resident_variant(const SpaceData& s);
 // local time stepping (lts.cpp): work buffers and fine mask for c, and one
 // period on p->U (direction +1: forward, with source / filter as asked;
 // -1: the adjoint of the homogeneous period, in S-flipped variables)

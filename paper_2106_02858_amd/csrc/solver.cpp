@@ -80,6 +80,70 @@ void hermite_weights(double omega, double dt, std::complex<double> xi[4]) {
     xi[3] = std::complex<double>(h * h * (mu[3] - mu[2]));
 }
 
+void fill_step_table(std::vector<double>& tab, int B, int b, int Mmax, const StepCfg& c, double omega) {
+    const int S = c.scheme == 2 ? 2 : 4, M = c.M;
+    const double dt = c.dt, two_pi = 2.0 * M_PI, twoT = 2.0 / c.T;
+    std::complex<double> xi[4];
+    if (c.scheme == 4) hermite_weights(omega, dt, xi);
+    auto ph = [&](double m) { return std::complex<double>(std::cos(two_pi * m / M), -std::sin(two_pi * m / M)); };
+    for (int m = 0; m <= Mmax; ++m) {
+        for (int s = 0; s < S; ++s) {
+            double* p = &tab[(((size_t)m * S + s) * B + b) * kMemberParams];
+            double cs = 0;  // stage time offset in steps
+            if (c.scheme == 2) {
+                if (s == 0) {
+                    p[0] = 0.5 * dt;
+                } else {
+                    p[2] = dt;
+                    cs = 0.5;
+                }
+            } else {
+                if (s == 0) {
+                    p[0] = 0.5 * dt;
+                    p[1] = dt / 6.0;
+                } else if (s == 1) {
+                    p[0] = 0.5 * dt;
+                    p[1] = dt / 3.0;
+                    cs = 0.5;
+                } else if (s == 2) {
+                    p[0] = dt;
+                    p[1] = dt / 3.0;
+                    cs = 0.5;
+                } else {
+                    p[2] = dt / 6.0;
+                    cs = 1.0;
+                }
+            }
+            const int mm = m < M ? m : M;  // the extra row holds level M_b
+            const double phase = two_pi * (mm + cs) / M;
+            p[3] = std::cos(phase);
+            p[4] = std::sin(phase);
+            if (s == 0) {
+                std::complex<double> wa, wb;
+                if (m < M) {
+                    if (c.scheme == 2) {
+                        wa = ph(m) * ((m == 0 ? 1.0 : 2.0) / M);
+                    } else {
+                        wa = twoT * ph(m) * xi[0];
+                        wb = twoT * ph(m) * xi[2];
+                        if (m >= 1) {
+                            wa += twoT * ph(m - 1) * xi[1];
+                            wb += twoT * ph(m - 1) * xi[3];
+                        }
+                    }
+                } else if (c.scheme == 4) {  // level M_b: interval [t_{M-1}, t_M] only
+                    wa = twoT * ph(M - 1) * xi[1];
+                    wb = twoT * ph(M - 1) * xi[3];
+                }
+                p[5] = wa.real();
+                p[6] = wa.imag();
+                p[7] = wb.real();
+                p[8] = wb.imag();
+            }
+        }
+    }
+}
+
 }  // namespace cmcg
 
 namespace cmcg {
@@ -601,6 +665,148 @@ static void run_period(cmcg_problem* p, const StepCfg& c, bool src, bool filt, b
     CMCG_HIP(hipGraphLaunch(it->second, st));
 }
 
+// ------------------------------------------------- periods as one launch
+namespace {
+// One-launch periods of a device run one after another, whatever streams they
+// are on: each needs all of its workgroups resident at once.  `last` marks
+// the end of the newest.
+struct ResidentTurn {
+    std::mutex mu;
+    hipEvent_t last = nullptr;
+};
+ResidentTurn g_resident[64];
+constexpr double kResidentWait = 2.0;  // seconds a workgroup waits for a neighbour before it gives up
+}  // namespace
+
+bool resident_variant(const SpaceData& s) {
+    return s.dim == 2;
+}
+
+// Numbers the faces whose neighbour lies in another element block, block by
+// block (each block's mailboxes are contiguous).
+static void build_mailboxes(SpaceData& s, hipStream_t st) {
+    const int nf = s.dim + 1, eb = element_block(s.dim);
+    const int64_t nb = (s.K + eb - 1) / eb;
+    std::vector<int> slot(nf * s.K, -1), start(nb + 1, 0);
+    int64_t n = 0;
+    for (int64_t b = 0; b < nb; ++b) {
+        start[b] = (int)n;
+        for (int64_t i = b * eb * nf; i < std::min((b + 1) * eb, s.K) * nf; ++i)
+            if (s.conn_h[i] >= 0 && (s.conn_h[i] >> 5) / eb != b) slot[i] = (int)n++;
+    }
+    start[nb] = (int)n;
+    s.xslot.alloc(slot.size() * 4);
+    s.xstart.alloc(start.size() * 4);
+    CMCG_HIP(hipMemcpyAsync(s.xslot.p, slot.data(), slot.size() * 4, hipMemcpyHostToDevice, st));
+    CMCG_HIP(hipMemcpyAsync(s.xstart.p, start.data(), start.size() * 4, hipMemcpyHostToDevice, st));
+    CMCG_HIP(hipStreamSynchronize(st));
+    s.next = n;
+}
+
+bool run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t st) {
+    if (r.off) return false;
+    const int nf = s.dim + 1;
+    // more faces than any device holds at once: no mailboxes are numbered
+    if (s.K * nf * a.members > kPeriodMaxValues / 8) {
+        r.off = true;
+        return false;
+    }
+    std::call_once(s.x_once, [&] { build_mailboxes(s, st); });
+    const size_t vals = (size_t)a.members * s.next * (s.dim == 2 ? 3 : 6) * s.Nfp;
+    if (vals > (size_t)kPeriodMaxValues) {
+        r.off = true;
+        return false;
+    }
+    const size_t pairs = 2 * vals * (s.precision == CMCG_FP64 ? 2 : 1);
+    const uint64_t need = (uint64_t)a.M * 4 + 8;
+    if (!r.xch.p || r.epoch + need > 0xffffffffull) {  // no pair may carry an epoch to come
+        try {
+            r.xch.alloc(pairs * 8 + 64);
+        } catch (const Error&) {
+            r.off = true;  // no room for the exchange: stage launches need none
+            return false;
+        }
+        launch_zero(r.xch.p, r.xch.bytes, st);
+        r.epoch = 0;
+    }
+    int khz = 0;
+    CMCG_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, s.device));
+    volatile int* failed = (volatile int*)r.failed.p;
+    *failed = 0;
+    a.xslot = s.xslot.as<int>();
+    a.xstart = s.xstart.as<int>();
+    a.next = s.next;
+    a.xch = r.xch.as<unsigned long long>();
+    a.abort = (uint32_t*)(a.xch + pairs);
+    a.failed = (int*)r.failed.p;
+    a.epoch = r.epoch + 1;
+    a.limit = (unsigned long long)(kResidentWait * 1e3 * khz);
+    r.epoch += (uint32_t)need;
+    {
+        ResidentTurn& turn = g_resident[s.device];
+        std::lock_guard<std::mutex> lk(turn.mu);
+        if (!turn.last)
+            CMCG_HIP(hipEventCreateWithFlags(&turn.last, hipEventDisableTiming));
+        else
+            CMCG_HIP(hipStreamWaitEvent(st, turn.last, 0));
+        const bool ran = s.dim == 2 && launch_period2d(s.q, s.precision, a, n, st);
+        if (!ran) {
+            r.off = true;
+            return false;
+        }
+        CMCG_HIP(hipEventRecord(turn.last, st));
+    }
+    CMCG_HIP(hipStreamSynchronize(st));
+    r.off = *failed != 0;
+    return !r.off;
+}
+
+// One period of p as one launch; false when it has to run by stage launches.
+static bool resident_period(cmcg_problem* p, const StepCfg& c, bool src, bool filt, bool use_graph, hipStream_t st) {
+    SpaceData& s = *p->sp;
+    if (!c.resident || !use_graph || p->nharm != 1 || (p->resident && p->resident->off) || !resident_variant(s))
+        return false;
+    if (!p->resident) p->resident.reset(new Resident());
+    Resident& r = *p->resident;
+    if (r.tab_M != c.M || r.tab_scheme != c.scheme) {
+        const int S = c.scheme == 2 ? 2 : 4;
+        std::vector<double> tab((size_t)(c.M + 1) * S * kMemberParams, 0.0);
+        fill_step_table(tab, 1, 0, c.M, c, p->omega);
+        r.tab_M = 0;
+        r.mtab.alloc(tab.size() * 8);
+        CMCG_HIP(hipMemcpyAsync(r.mtab.p, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, st));
+        CMCG_HIP(hipStreamSynchronize(st));
+        r.tab_M = c.M;
+        r.tab_scheme = c.scheme;
+    }
+    PeriodArgs a{};
+    a.U = p->U.p;
+    a.Ulo = p->Ulo.p;
+    a.geo = p->geo.p;
+    a.conn = s.conn.as<int>();
+    a.Sre = p->Sre.p;
+    a.Sim = p->Sim.p;
+    a.smask = p->smask.as<uint32_t>();
+    a.Fre = p->Fre.as<double>();
+    a.Fim = p->Fim.as<double>();
+    a.K = s.K;
+    a.scheme = c.scheme;
+    a.M = c.M;
+    a.members = 1;
+    a.src_rows = src ? p->src_rows : 0;
+    a.filter = filt ? 1 : 0;
+    a.mtab = r.mtab.as<double>();
+    a.bstride = a.sstride = s.ndof;
+    if (filt) {
+        launch_zero(p->Fre.p, p->Fre.bytes, st);
+        launch_zero(p->Fim.p, p->Fim.bytes, st);
+    }
+    if (!run_resident(r, s, a, 1, st)) return false;
+    if (filt && c.scheme == 2)  // last level t_M = T: e^{-i w T} = 1
+        launch_filter_add(s.precision, p->U.p, 1.0 / c.M, 0.0, p->Fre.as<double>(), p->Fim.as<double>(), s.ndof, st);
+    return true;
+}
+
 // One LTS period (forward with or without source and filter, or the adjoint).
 // A forward period is replayed from a captured graph when use_graph (one
 // host call for its thousands of launches; as fast as the eager launches on
@@ -654,13 +860,19 @@ void apply_period(cmcg_problem* p, const StepCfg& c, const cmcg_options* o, cons
         if (Yo) from_field_dim(s, p->U.p, nullptr, Yo, sub, s.ndof, flip, st);
         return;
     }
-    if (X) {
-        to_field_dim(s, X, p->U.p, p->Ulo.p, s.ndof, flip, st);
-    } else {
-        launch_zero(p->U.p, p->U.bytes, st);
-        if (p->Ulo.p) launch_zero(p->Ulo.p, p->Ulo.bytes, st);
+    auto start = [&] {
+        if (X) {
+            to_field_dim(s, X, p->U.p, p->Ulo.p, s.ndof, flip, st);
+        } else {
+            launch_zero(p->U.p, p->U.bytes, st);
+            if (p->Ulo.p) launch_zero(p->Ulo.p, p->Ulo.bytes, st);
+        }
+    };
+    start();
+    if (!resident_period(p, c, src && direction > 0, filt, o->use_graph != 0, st)) {
+        if (c.resident && p->resident && p->resident->off) start();  // a launch that gave up left no state
+        run_period(p, c, src && direction > 0, filt, o->use_graph != 0, st);
     }
-    run_period(p, c, src && direction > 0, filt, o->use_graph != 0, st);
     if (Yo) from_field_dim(s, p->U.p, p->Ulo.p, Yo, sub, s.ndof, flip, st);
 }
 
@@ -800,6 +1012,7 @@ void CgRun::start(cmcg_problem* pr, const cmcg_options* opt, const double* u0_, 
     u0 = u0_;
     if (o.runup < 0) fail(CMCG_ERR_ARG, "options: runup must be >= 0");
     c = step_config(p, &o);
+    c.resident = resident;
     prepare(p, c);
     maybe_autotune(p, &o, c, st);
     const SpaceData& s = *p->sp;
@@ -968,7 +1181,8 @@ void CgRun::complete() {
 // at the period starts; the approximation F_psi U_0^(l) comes from one final
 // period with the filter, so the filter's FP64 accumulation is paid once.
 cmcg_result* fw_solve(cmcg_problem* p, const cmcg_options* o, const double* u0, hipStream_t st) {
-    const StepCfg c = step_config(p, o);
+    StepCfg c = step_config(p, o);
+    c.resident = true;
     prepare(p, c);
     maybe_autotune(p, o, c, st);
     const SpaceData& s = *p->sp;
@@ -1035,6 +1249,7 @@ cmcg_result* fw_solve(cmcg_problem* p, const cmcg_options* o, const double* u0, 
 
 cmcg_result* solve(cmcg_problem* p, const cmcg_options* o, const double* u0, hipStream_t st) {
     CgRun run;
+    run.resident = true;
     run.start(p, o, u0, st);
     while (!run.done()) {
         CMCG_HIP(hipStreamSynchronize(st));
@@ -1484,6 +1699,7 @@ int cmcg_debug_period(cmcg_problem* p, const cmcg_options* o, int direction, int
     cmcg_options_default(&def);
     if (!o) o = &def;
     StepCfg c = step_config(p, o);
+    c.resident = true;
     prepare(p, c);
     const bool filt = f_re || f_im;
     apply_period(p, c, o, u0, ut, nullptr, direction, with_source != 0, filt, stream);
