@@ -89,55 +89,40 @@ def parse():
 # FETCH_SIZE / WRITE_SIZE per dispatch (KiB) of the stage kernel on the
 # 48000-tet P3 FP32 problem, with the scales a 1 GiB copy gives each counter;
 # valid only for the kernel source they were taken on (SHA-256 below).
+_SHA_3D = "81523165ddc92a8d82c4cb960db3867453aea65aa336fe1e269871073474a489"
 MEASURED_TRAFFIC = [
-    {"kernels_sha256": "95f2693eedc0bcfb1df99161361c7df1cf804e6b22fdb00f46db1035fc9af466",
-     "kernel": "k_stage_mfma<float,3,true,false,2,false,true>", "K": 48000,
-     "fetch_kib": 41696.72, "fetch_scale": 2.0000, "write_kib": 42197.84, "write_scale": 1.0000},
-    {"kernels_sha256": "95f2693eedc0bcfb1df99161361c7df1cf804e6b22fdb00f46db1035fc9af466",
-     "kernel": "k_stage_mfma<float,3,true,false,4>", "K": 48000,
-     "fetch_kib": 41006.57, "fetch_scale": 2.0000, "write_kib": 42187.65, "write_scale": 1.0000},
+    {"kernels_sha256": _SHA_3D, "kernel": "k_stage_col<3,false,false>", "K": 48000,
+     "fetch_kib": 40871.78, "fetch_scale": 2.0000, "write_kib": 42187.53, "write_scale": 1.0000},
 ]
 
 
 # The same for the FP64 stage kernel of the plain FP64 solve (48000 tets, P3):
 # the two forms its autotuner keeps (two and four waves per block).
 MEASURED_TRAFFIC_FP64 = [
-    {"kernels_sha256": "95f2693eedc0bcfb1df99161361c7df1cf804e6b22fdb00f46db1035fc9af466",
-     "kernel": "k_stage_mfma<double,3,true,false,2>", "K": 48000,
-     "fetch_kib": 81060.19, "fetch_scale": 2.0000, "write_kib": 78750.00, "write_scale": 1.0000},
-    {"kernels_sha256": "95f2693eedc0bcfb1df99161361c7df1cf804e6b22fdb00f46db1035fc9af466",
-     "kernel": "k_stage_mfma<double,3,true,false,4>", "K": 48000,
-     "fetch_kib": 75600.09, "fetch_scale": 2.0000, "write_kib": 78750.00, "write_scale": 1.0000},
+    {"kernels_sha256": _SHA_3D, "kernel": k, "K": 48000,
+     "fetch_kib": fe, "fetch_scale": 2.0000, "write_kib": wr, "write_scale": 1.0000}
+    for k, fe, wr in (("k_stage_mfma<3,true,false,2>", 80891.66, 78750.00),
+                      ("k_stage_mfma<3,true,false,4>", 75507.63, 78750.00))
 ]
 
 
 # The same for the P2 FP32 stage kernels of the large launches: the
-# 1,572,864-tet scatterer (variants 3 and 2, the two its autotuner keeps) and the
-# batched launch of 64 members on the 10368-tet mesh, every member active
-# (K = members x elements; every variant the batched autotuner times).
-_SHA_Q2 = "95f2693eedc0bcfb1df99161361c7df1cf804e6b22fdb00f46db1035fc9af466"
+# 1,572,864-tet scatterer and the batched launch of 64 members on the 10368-tet
+# mesh, every member active (K = members x elements; every kernel the batched
+# autotuner times).
 MEASURED_TRAFFIC_Q2 = [
-    {"kernels_sha256": _SHA_Q2, "kernel": "k_stage_mfma<float,2,true,false,1>", "K": 1572864,
-     "fetch_kib": 826087.99, "fetch_scale": 2.0000, "write_kib": 696403.27, "write_scale": 1.0000},
-    {"kernels_sha256": _SHA_Q2, "kernel": "k_stage_mfma<float,2,false,false,1>", "K": 1572864,
-     "fetch_kib": 841445.58, "fetch_scale": 2.0000, "write_kib": 696003.22, "write_scale": 1.0000},
-] + [
-    {"kernels_sha256": _SHA_Q2, "kernel": k, "K": 64 * 10368,
+    {"kernels_sha256": _SHA_3D, "kernel": k, "K": K,
      "fetch_kib": fe, "fetch_scale": 2.0000, "write_kib": wr, "write_scale": 1.0000}
-    for k, fe, wr in (("k_stage_mfma<float,2,true,false,1>", 261308.21, 293151.86),
-                      ("k_stage_mfma<float,2,false,false,1>", 265477.60, 293033.53),
-                      ("k_stage<float,2,false,false>", 284333.38, 292218.74),
-                      ("k_stage<float,2,true,false>", 252748.48, 291670.07),
-                      ("k_stage_mfma<float,2,true,false,2>", 247271.13, 291747.63),
-                      ("k_stage_mfma<float,2,true,false,2,true>", 245780.23, 291612.83),
-                      ("k_stage_mfma<float,2,true,false,4>", 245653.31, 291603.04),
-                      ("k_stage_mfma<float,2,true,false,4,true>", 245600.44, 291600.09))
+    for k, K, fe, wr in (("k_stage_col<2,false,false>", 1572864, 772943.21, 691300.82),
+                         ("k_stage_col<2,false,false>", 64 * 10368, 245625.16, 291610.99),
+                         ("k_stage<float,2,false,false>", 64 * 10368, 284170.39, 292219.03),
+                         ("k_stage<float,2,true,false>", 64 * 10368, 252674.47, 291668.46))
 ]
 
 
 # The same for the 2-D stage kernel on the 22500-triangle disk trap (P3, FP32).
 MEASURED_TRAFFIC_2D = {
-    "kernels_sha256": "48024d5b6ace747553a004c71e87732cbef354189cb311888bbd10efa2fc04cf",
+    "kernels_sha256": "6f0bf95eeb576004fa376c2a335602ad33a1bdfacc2bbecf0b4647296d971b04",
     "kernel": "k_stage2d<float,3,true>", "K": 22500,
     "fetch_kib": 5075.75, "fetch_scale": 2.0000, "write_kib": 4944.12, "write_scale": 1.0000,
 }
@@ -164,12 +149,12 @@ def measured_traffic(kernel: str, K: int, table=None, source: str = "kernels.hip
 
 # single-frequency instantiations (the MH template argument selects the several-frequency code)
 STAGE_KERNEL = {0: "k_stage<float,{q},false,false>", 1: "k_stage<float,{q},true,false>",
-                2: "k_stage_mfma<float,{q},false,false,1>", 3: "k_stage_mfma<float,{q},true,false,1>",
-                4: "k_stage_mfma<float,{q},true,false,2>", 5: "k_stage_mfma<float,{q},true,false,2,true>",
-                6: "k_stage_mfma<float,{q},true,false,2,false,true>",
-                7: "k_stage_mfma<float,{q},true,false,2,true,true>",
-                8: "k_stage_mfma<float,{q},true,false,4>", 9: "k_stage_mfma<float,{q},true,false,4,true>"}
-STAGE_KERNEL64 = {v: k.replace("float", "double") for v, k in STAGE_KERNEL.items()}
+                **dict.fromkeys(range(2, 10), "k_stage_col<{q},false,false>")}
+STAGE_KERNEL64 = {0: "k_stage<double,{q},false,false>", 1: "k_stage<double,{q},true,false>",
+                  2: "k_stage_mfma<{q},false,false,1>", 3: "k_stage_mfma<{q},true,false,1>",
+                  4: "k_stage_mfma<{q},true,false,2>", 5: "k_stage_mfma<{q},true,false,2,true>",
+                  6: "k_stage_mfma<{q},true,false,2,false,true>", 7: "k_stage_mfma<{q},true,false,2,true,true>",
+                  8: "k_stage_mfma<{q},true,false,4>", 9: "k_stage_mfma<{q},true,false,4,true>"}
 
 
 def stage_bytes_per_element(q: int, esize: int) -> float:

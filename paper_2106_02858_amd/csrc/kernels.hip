@@ -24,6 +24,8 @@
 
 #include "internal.h"
 #include "launch.h"
+#include "mfma_cols.h"
+#include "tagged.h"
 
 namespace cmcg {
 
@@ -325,6 +327,29 @@ template <typename T, int Q, int RF> struct TraceGather {
     }
 };
 
+// Arithmetic that the stage and the period kernels share is written with
+// explicit fma(): left to the compiler, they may contract the same expression
+// differently, and their results would part in the last bit.
+//
+// Upwind flux (E, then H rows) at one face node, g = the face's normal and
+// flux coefficients.
+template <typename T>
+__device__ __forceinline__ void upwind3(const T* g, const T (&Em)[3], const T (&Hm)[3], const T (&Ep)[3],
+                                        const T (&Hp)[3], T (&o)[6]) {
+    const T n0 = g[0], n1 = g[1], n2 = g[2];
+    const T cE1 = g[3], cE2 = g[4], cH1 = g[5], cH2 = g[6];
+    const T dE0 = Ep[0] - Em[0], dE1 = Ep[1] - Em[1], dE2 = Ep[2] - Em[2];
+    const T dH0 = Hp[0] - Hm[0], dH1 = Hp[1] - Hm[1], dH2 = Hp[2] - Hm[2];
+    const T ndE = fma(n0, dE0, fma(n1, dE1, n2 * dE2));
+    const T ndH = fma(n0, dH0, fma(n1, dH1, n2 * dH2));
+    o[0] = fma(cE1, fma(-ndE, n0, dE0), -cE2 * fma(n1, dH2, -n2 * dH1));
+    o[1] = fma(cE1, fma(-ndE, n1, dE1), -cE2 * fma(n2, dH0, -n0 * dH2));
+    o[2] = fma(cE1, fma(-ndE, n2, dE2), -cE2 * fma(n0, dH1, -n1 * dH0));
+    o[3] = fma(cH1, fma(-ndH, n0, dH0), cH2 * fma(n1, dE2, -n2 * dE1));
+    o[4] = fma(cH1, fma(-ndH, n1, dH1), cH2 * fma(n2, dE0, -n0 * dE2));
+    o[5] = fma(cH1, fma(-ndH, n2, dH2), cH2 * fma(n0, dE1, -n1 * dE0));
+}
+
 // PIPE: request the next face's neighbour traces (and, before the last face,
 // the update operands) one face ahead.  Without it every face gathers and
 // consumes in turn, which needs fewer registers.
@@ -473,22 +498,11 @@ __global__ __launch_bounds__(64) void k_stage(StageArgs args, int64_t per) {
                     Hp[cc] = T(0);
                 }
             }
-            const T* g = &sG[fe * kGeo + 9 + 7 * f];
-            const T n0 = g[0], n1 = g[1], n2 = g[2];
-            const T cE1 = g[3], cE2 = g[4], cH1 = g[5], cH2 = g[6];
-            const T dE0 = Ep[0] - Em[0], dE1 = Ep[1] - Em[1], dE2 = Ep[2] - Em[2];
-            const T dH0 = Hp[0] - Hm[0], dH1 = Hp[1] - Hm[1], dH2 = Hp[2] - Hm[2];
-            const T ndE = n0 * dE0 + n1 * dE1 + n2 * dE2;
-            const T ndH = n0 * dH0 + n1 * dH1 + n2 * dH2;
-            const T xH0 = n1 * dH2 - n2 * dH1, xH1 = n2 * dH0 - n0 * dH2, xH2 = n0 * dH1 - n1 * dH0;
-            const T xE0 = n1 * dE2 - n2 * dE1, xE1 = n2 * dE0 - n0 * dE2, xE2 = n0 * dE1 - n1 * dE0;
+            T fx[6];
+            upwind3(&sG[fe * kGeo + 9 + 7 * f], Em, Hm, Ep, Hp, fx);
             T* o = &sF[k * FS + fe * 6];
-            o[0] = cE1 * (dE0 - ndE * n0) - cE2 * xH0;
-            o[1] = cE1 * (dE1 - ndE * n1) - cE2 * xH1;
-            o[2] = cE1 * (dE2 - ndE * n2) - cE2 * xH2;
-            o[3] = cH1 * (dH0 - ndH * n0) + cH2 * xE0;
-            o[4] = cH1 * (dH1 - ndH * n1) + cH2 * xE1;
-            o[5] = cH1 * (dH2 - ndH * n2) + cH2 * xE2;
+#pragma unroll
+            for (int cc = 0; cc < 6; ++cc) o[cc] = fx[cc];
         }
         __syncthreads();
         T fl[NFP];
@@ -524,7 +538,7 @@ __global__ __launch_bounds__(64) void k_stage(StageArgs args, int64_t per) {
         Row<T, NP>::load((const T*)a.Sim + grow, si);
         const T scos = (T)a.scos, ssin = (T)a.ssin;
 #pragma unroll
-        for (int i = 0; i < NP; ++i) kv[i] += scos * sr[i] - ssin * si[i];
+        for (int i = 0; i < NP; ++i) kv[i] = fma(scos, sr[i], fma(-ssin, si[i], kv[i]));
 #pragma unroll 1
         // further harmonics of a several-frequency source (single launches, so the
         // kernel arguments hold the tables; indexing the local copy put it in scratch)
@@ -679,8 +693,8 @@ __global__ __launch_bounds__(64) void k_stage(StageArgs args, int64_t per) {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const double ud = (double)y[i], kd = (double)kv[i];
-            fr[i] += a.fa_re * ud + a.fb_re * kd;
-            fi[i] += a.fa_im * ud + a.fb_im * kd;
+            fr[i] = fma(a.fa_re, ud, fma(a.fb_re, kd, fr[i]));
+            fi[i] = fma(a.fa_im, ud, fma(a.fb_im, kd, fi[i]));
         }
 #pragma unroll 1
         for (int h = 1; MH && h < a.nharm; ++h) {
@@ -697,7 +711,7 @@ __global__ __launch_bounds__(64) void k_stage(StageArgs args, int64_t per) {
 }
 
 // ---------------------------------------------------------------------------
-// FP32 stage kernel on the matrix cores (q = 2, 3).
+// FP64 stage kernel on the matrix cores (q = 2, 3).
 //
 // Per 64-lane workgroup (10 elements, columns n = element * 6 + s):
 //   volume:  C[i][n] = sum_{a,j} D_a[i][j] W_a[j][n],  W_a = sgn (grad xi_a x V)_m,
@@ -705,7 +719,7 @@ __global__ __launch_bounds__(64) void k_stage(StageArgs args, int64_t per) {
 //            m = s mod 3 -- i.e. curl V = sum_a D_a (grad xi_a x V) for an affine
 //            element, so the product already is the curl column;
 //   lift:    C[i][n] += sum_{f,k} LIFT[i][f Nfp + k] flux_f[k][n], face by face;
-// with v_mfma_f32_16x16x4f32: A = the reference matrices, held as register
+// with v_mfma_f64_16x16x4f64: A = the reference matrices, held as register
 // fragments (lane l holds A[l % 16][l / 16] of each 16x4 block, read once from a
 // lane-ordered table), B = W or flux values from LDS, D rows per Mfma<T>::row.
 // The volume's K steps are axis-major: step ks covers axis a = ks / NJ and
@@ -724,11 +738,7 @@ __host__ __device__ constexpr int frag_off(int q) {
     return q <= 2 ? 0 : frag_off(q - 1) + 64 * MfmaDim<2>::NFRAG;
 }
 constexpr int kFragTotal = 64 * (MfmaDim<2>::NFRAG + MfmaDim<3>::NFRAG);
-__device__ float gFrag[kFragTotal];
 __device__ double gFrag64[kFragTotal];
-template <typename T> __device__ __forceinline__ const T* frags();
-template <> __device__ __forceinline__ const float* frags<float>() { return gFrag; }
-template <> __device__ __forceinline__ const double* frags<double>() { return gFrag64; }
 
 // One 16x16x4 matrix-core product D = A B + C in the field precision:
 // v_mfma_f32_16x16x4f32 or v_mfma_f64_16x16x4f64.  Both take A[l % 16][l / 16]
@@ -752,8 +762,9 @@ template <> struct Mfma<double> {
     static __device__ __forceinline__ int row(int q4, int r) { return 4 * r + q4; }
 };
 
-template <typename T, int Q, int NB = 1>
+template <int Q, int NB = 1>
 struct MfmaShared {
+    using T = double;
     static constexpr int NP = Dim<Q>::NP, NFP = Dim<Q>::NFP;
     static constexpr int RS = NP + 1;
     static constexpr int KF = 4 * MfmaDim<Q>::KSF;
@@ -800,276 +811,23 @@ template <typename T, int Q, int NTH = 64, bool LTSM = false> struct MfmaUpdateI
     }
 };
 
-// PIPE: the next face's neighbour traces are requested before this face's
-// flux (more registers, the gather latency hides behind the lift).
-// W: waves per workgroup.  W = 2 gives each wave half the output tiles: P3
-// one of its two 16-row tiles (both waves build the same B operands), P2 two
-// of the four 16-column tiles (each wave builds only its own); each runs half
-// the MFMAs, the flux items and the update pass are shared by 128 threads.  A
-// block's dependent chain gets shorter at 6 waves per SIMD (76 registers),
-// which pays where the launch ends in a partial round of workgroups.  Register
-// allocation is held to 4 waves per SIMD (128 registers; the FP32 LDS tiles
-// of MfmaShared<float, 3> stay under 10 KB so 16 workgroups fit a compute
-// unit).  Requesting the update operands earlier (with the staging loads, or
-// before the last face) was measured slower: the registers cost occupancy
-// (P2) or spill (P3).  T = double runs the same data flow on
-// v_mfma_f64_16x16x4f64 with FP64 fields (no compensated state).
-// EAGER: the neighbour traces of all four faces are requested right after
-// the staging (four faces' loads in flight during the volume product instead
-// of one), and faces alternate between two flux tiles, so a face needs one
-// barrier instead of two.  CSPLIT (P3, two waves): the waves split the output
-// by column tiles, each building only its own B operands and running both
-// row tiles.  W = 4: each wave one row tile and two column tiles (P3) or one
-// column tile (P2), a quarter of the MFMAs and fewer registers per wave.
-template <typename T, int Q, bool PIPE, bool MH, int W, bool EAGER = false, bool CSPLIT = false, bool LTSM = false>
-__global__ __launch_bounds__(64 * W)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (W == 4 ? (EAGER ? 5 : Q == 3 ? 7 : 8) : W == 1 || (EAGER && Q == 3) ? 4 : (EAGER || CSPLIT ? 5 : 6))
-                                                   : (W == 4 ? (EAGER ? 2 : 4) : W == 1 || EAGER || CSPLIT ? 2 : 3), 8)))
-void k_stage_mfma(StageArgs args, int64_t per) {
-    using MD = MfmaDim<Q>;
-    using acc_t = typename Mfma<T>::acc_t;
+// Stage update of a block: one coalesced pass over its contiguous rows
+// (16-byte groups v = PV (tid + NTH t)), kvals(v, kv) giving the scaled
+// right-hand side of a group and upd its operands.
+template <typename T, int Q, int NTH, bool MH, bool LTSM, typename KV>
+__device__ __forceinline__ void stage_update(const StageArgs& args, const StageArgs& a,
+                                             const MfmaUpdateIn<T, Q, NTH, LTSM>& upd, int64_t blk, int64_t base,
+                                             int nvv, int tid, KV kvals) {
     constexpr bool COMP = std::is_same<T, float>::value;  // compensated state U + Ulo
-    constexpr int NP = MD::NP, NFP = MD::NFP, MT = MD::MT, KSV = MD::KSV, KSF = MD::KSF;
-    constexpr int RS = NP + 1;
-    constexpr int KF = 4 * KSF;
-    constexpr int NTH = 64 * W;                      // threads of the workgroup
-    constexpr int RF = (EPW * NFP + NTH - 1) / NTH;  // flux items per thread and face
-    // two waves split the output tiles: by rows when there are two row tiles
-    // (P3, unless CSPLIT), by the four 16-column tiles otherwise; four waves
-    // split by rows (P3) and by columns
-    static_assert(W == 1 || W == 2 || W == 4, "one, two or four waves per block");
-    constexpr bool ROWS = (W == 2 && MT == 2 && !CSPLIT) || (W == 4 && MT == 2);
-    constexpr bool COLS = (W == 2 && (MT == 1 || CSPLIT)) || W == 4;
-    constexpr int NB = EAGER ? 2 : 1;  // flux tiles
-    using Sh = MfmaShared<T, Q, NB>;
-    constexpr int MW = ROWS ? 1 : MT;  // output row tiles of one wave
-    constexpr int CWAVES = COLS ? (ROWS ? W / 2 : W) : 1;  // waves across the column tiles
-    constexpr int NW = 4 / CWAVES;                          // output column tiles of one wave
-    static_assert(W == 1 || ((ROWS || COLS) && RF == 1), "several waves per block need one flux item per thread");
-    __shared__ Sh sh;
-
-    StageArgs a;
-    if (!member_args<T>(args, a)) return;  // uniform per workgroup
-    int64_t blk = xcd_block(per);
-    if (a.blist) {  // only the listed element blocks
-        if (blk >= a.nblist) return;
-        blk = a.blist[blk];
-    }
-    const int64_t e0 = blk * EPW;
-    if (e0 >= a.K) return;  // uniform per workgroup
-    const T* __restrict__ Y = (const T*)a.Y;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int mt0 = ROWS ? (wave & 1) : 0;                           // first output row tile of this wave
-    const int nt0 = COLS ? NW * (ROWS ? wave >> 1 : wave) : 0;  // first output column tile of this wave
-    const int ne = (int)((a.K - e0) < EPW ? (a.K - e0) : EPW);
-    const int64_t base = e0 * 6 * NP;
-    constexpr int PV = 16 / (int)sizeof(T);  // values per 16-byte group
-    const int nvv = ne * 6 * NP / PV;        // 16-byte groups of the chunk (6 NP ne is a multiple of 4)
-
-    // matrix fragments (coalesced: fragment-major, lane-minor); lift
-    // fragments one face at a time, requested one face ahead
-    const T* fr = frags<T>() + frag_off(Q);
-    T afV[MW][KSV], afL[MW][KSF], afN[MW][KSF];
-    auto lift_frags = [&](int f, T (&d)[MW][KSF]) {
-#pragma unroll
-        for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-            for (int ks = 0; ks < KSF; ++ks) d[mt][ks] = fr[(MT * KSV + (f * MT + mt + mt0) * KSF + ks) * 64 + lane];
-    };
-
-    // ---- staging: chunk fields, geometry, connectivity, face-node tables;
-    // the volume and face-0 lift fragments are requested right behind the
-    // chunk's loads, so their latency hides behind the staging wait
-    const uint32_t keep = a.imask ? (a.imask[blk] ^ (a.imask_inv ? 0xffffffffu : 0u)) : 0xffffffffu;
-    {
-        ChunkIn<T, Q, NTH> in;
-        in.fetch(Y, (const T*)a.geo, a.conn, e0, ne, tid);
-#pragma unroll
-        for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-            for (int ks = 0; ks < KSV; ++ks) afV[mt][ks] = fr[((mt + mt0) * KSV + ks) * 64 + lane];
-        lift_frags(0, afL);
-        for (int v = tid; v < NB * KF * Sh::FS; v += NTH) sh.sF[v] = T(0);
-        in.put(sh.sY, sh.sG, sh.sC, sh.sT, ne, tid, keep);
-    }
-    __syncthreads();
-
-    // face 0's neighbour traces (EAGER: every face's) in flight during the volume product
-    FluxItems<Q, RF> itm;
-    itm.init(ne, tid);
-    TraceGather<T, Q, RF> cur, nxt;
-    TraceGather<T, Q, RF> all[EAGER ? 4 : 1];
-    if constexpr (EAGER) {
-#pragma unroll
-        for (int f = 0; f < 4; ++f) all[f].issue(Y, sh.sC, sh.sT, itm, f, e0, ne, a.imask, a.imask_inv);
-    } else {
-        cur.issue(Y, sh.sC, sh.sT, itm, 0, e0, ne, a.imask, a.imask_inv);
-    }
-
-    const int q4 = lane >> 4;   // K row within a 4-row block / output row group
-    const int l16 = lane & 15;  // output column within a 16-column tile
-    acc_t acc[MW][NW];
-#pragma unroll
-    for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NW; ++nt) acc[mt][nt] = acc_t{T(0), T(0), T(0), T(0)};
-
-    // ---- volume product: B[(a, j)][n] = sgn (g_a[m1] V_m2(j) - g_a[m2] V_m1(j));
-    // padded columns read element 0 (their results are never stored)
-#pragma unroll
-    for (int nt = 0; nt < NW; ++nt) {
-        const int n = (nt + nt0) * 16 + l16;
-        const int e = n < 6 * ne ? n / 6 : 0;
-        const int s = n - 6 * (n / 6);
-        const int m = s < 3 ? s : s - 3;
-        const int m1 = m == 2 ? 0 : m + 1, m2 = m == 0 ? 2 : m - 1;  // (m+1)%3, (m+2)%3
-        const int vb = e * 6 + (s < 3 ? 3 : 0);
-        const T sgn = s < 3 ? T(-1) : T(1);
-        const T* gE = &sh.sG[e * kGeo];
-        T g1[3], g2[3];
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            g1[ax] = sgn * gE[3 * ax + m1];
-            g2[ax] = sgn * gE[3 * ax + m2];
-        }
-        const T* v1 = &sh.sY[(vb + m1) * RS];
-        const T* v2 = &sh.sY[(vb + m2) * RS];
-        constexpr int NJ = MD::NJ;
-        T r1[NJ], r2[NJ];
-#pragma unroll
-        for (int t = 0; t < NJ; ++t) {
-            const int j = q4 + 4 * t;
-            const bool in = NP % 4 == 0 || j < NP;  // j >= Np: zero fragment, zero operand
-            r1[t] = in ? v1[in ? j : 0] : T(0);
-            r2[t] = in ? v2[in ? j : 0] : T(0);
-        }
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax)
-#pragma unroll
-            for (int t = 0; t < NJ; ++t) {
-                const T b = g1[ax] * r2[t] - g2[ax] * r1[t];
-#pragma unroll
-                for (int mt = 0; mt < MW; ++mt)
-                    acc[mt][nt] = Mfma<T>::mma(afV[mt][ax * NJ + t], b, acc[mt][nt]);
-            }
-    }
-
-    // ---- upwind flux and lift, one face at a time
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        if (!EAGER && PIPE && f < 3) nxt.issue(Y, sh.sC, sh.sT, itm, f + 1, e0, ne, a.imask, a.imask_inv);
-        if (f < 3) lift_frags(f + 1, afN);
-        T* tile = sh.sF + (EAGER ? (f & 1) * KF * Sh::FS : 0);
-        const TraceGather<T, Q, RF>& gat = EAGER ? all[f] : cur;
-#pragma unroll
-        for (int r = 0; r < RF; ++r) {
-            if (!itm.on[r]) continue;
-            const int k = itm.k[r];
-            const int fe = itm.fe[r];
-            const int own = sh.sT[f * NFP + k];
-            T Em[3], Hm[3], Ep[3], Hp[3];
-#pragma unroll
-            for (int cc = 0; cc < 3; ++cc) {
-                Em[cc] = sh.sY[(fe * 6 + cc) * RS + own];
-                Hm[cc] = sh.sY[(fe * 6 + 3 + cc) * RS + own];
-            }
-            const int code = gat.code[r];
-            if (code >= 0) {
-                gat.values(sh.sY, r, Ep, Hp);
-            } else if (code == -1) {  // PEC ghost: E+ = -E-, H+ = H-
-#pragma unroll
-                for (int cc = 0; cc < 3; ++cc) {
-                    Ep[cc] = -Em[cc];
-                    Hp[cc] = Hm[cc];
-                }
-            } else {  // impedance ghost (homogeneous part): zero exterior state
-#pragma unroll
-                for (int cc = 0; cc < 3; ++cc) {
-                    Ep[cc] = T(0);
-                    Hp[cc] = T(0);
-                }
-            }
-            const T* g = &sh.sG[fe * kGeo + 9 + 7 * f];
-            const T n0 = g[0], n1 = g[1], n2 = g[2];
-            const T cE1 = g[3], cE2 = g[4], cH1 = g[5], cH2 = g[6];
-            const T dE0 = Ep[0] - Em[0], dE1 = Ep[1] - Em[1], dE2 = Ep[2] - Em[2];
-            const T dH0 = Hp[0] - Hm[0], dH1 = Hp[1] - Hm[1], dH2 = Hp[2] - Hm[2];
-            const T ndE = n0 * dE0 + n1 * dE1 + n2 * dE2;
-            const T ndH = n0 * dH0 + n1 * dH1 + n2 * dH2;
-            const T xH0 = n1 * dH2 - n2 * dH1, xH1 = n2 * dH0 - n0 * dH2, xH2 = n0 * dH1 - n1 * dH0;
-            const T xE0 = n1 * dE2 - n2 * dE1, xE1 = n2 * dE0 - n0 * dE2, xE2 = n0 * dE1 - n1 * dE0;
-            T* o = &tile[k * Sh::FS + fe * 6];
-            o[0] = cE1 * (dE0 - ndE * n0) - cE2 * xH0;
-            o[1] = cE1 * (dE1 - ndE * n1) - cE2 * xH1;
-            o[2] = cE1 * (dE2 - ndE * n2) - cE2 * xH2;
-            o[3] = cH1 * (dH0 - ndH * n0) + cH2 * xE0;
-            o[4] = cH1 * (dH1 - ndH * n1) + cH2 * xE1;
-            o[5] = cH1 * (dH2 - ndH * n2) + cH2 * xE2;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < KSF; ++ks) {
-            T b[NW];
-#pragma unroll
-            for (int nt = 0; nt < NW; ++nt) b[nt] = tile[(ks * 4 + q4) * Sh::FS + (nt + nt0) * 16 + l16];
-#pragma unroll
-            for (int nt = 0; nt < NW; ++nt)
-#pragma unroll
-                for (int mt = 0; mt < MW; ++mt)
-                    acc[mt][nt] = Mfma<T>::mma(afL[mt][ks], b[nt], acc[mt][nt]);
-        }
-        // one tile: it is rewritten by the next face; two tiles: the next face
-        // writes the other one, and the face after it only once every thread
-        // has passed the next face's barrier (so has finished this lift)
-        if (!EAGER) __syncthreads();
-        if (f < 3) {
-            if (!EAGER) {
-                if (!PIPE) nxt.issue(Y, sh.sC, sh.sT, itm, f + 1, e0, ne, a.imask, a.imask_inv);
-                cur = nxt;
-            }
-#pragma unroll
-            for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-                for (int ks = 0; ks < KSF; ++ks) afL[mt][ks] = afN[mt][ks];
-        }
-    }
-
-    // ---- scaled right-hand side (1/eps or 1/mu, conductivity) into the
-    // staging tile, in place: every value is read and written by one lane
-#pragma unroll
-    for (int nt = 0; nt < NW; ++nt) {
-        const int n = (nt + nt0) * 16 + l16;
-        if (n >= 6 * ne) continue;
-        const int e = n / 6;
-        const int s = n - 6 * e;
-        const T inv = s < 3 ? sh.sG[e * kGeo + 37] : sh.sG[e * kGeo + 38];
-        const T sig = s < 3 ? sh.sG[e * kGeo + 39] : T(0);
-#pragma unroll
-        for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = (mt + mt0) * 16 + Mfma<T>::row(q4, r);
-                if (i < NP) {
-                    T* p = &sh.sY[n * RS + i];
-                    *p = fma(inv, acc[mt][nt][r], -sig * *p);
-                }
-            }
-    }
-    __syncthreads();
-
-    // ---- stage update: one coalesced pass over the chunk's contiguous rows
+    constexpr int NP = Dim<Q>::NP, PV = 16 / (int)sizeof(T);
+    using UIn = MfmaUpdateIn<T, Q, NTH, LTSM>;
+    using V = typename UIn::V;
     const int mode = a.mode;
     const T scos = (T)a.scos, ssin = (T)a.ssin;
     const T cy = (T)a.cy, ca = (T)a.ca, cu = (T)a.cu;
     // elements whose source is zero (and H rows of an interior source) read none
     const uint32_t sm = a.smask ? a.smask[blk] : 0xffffffffu;
     auto takes_src = [&](int row) { return row - 6 * (row / 6) < a.src_rows && ((sm >> (row / 6)) & 1u); };
-    using UIn = MfmaUpdateIn<T, Q, NTH, LTSM>;
-    using V = typename UIn::V;
-    UIn upd;
-    upd.fetch(a, base, nvv, tid);
     auto ldv = [](const void* p, int64_t o, T (&r)[PV]) {
         const V v = *reinterpret_cast<const V*>((const T*)p + o);
         const T* t = reinterpret_cast<const T*>(&v);
@@ -1083,8 +841,7 @@ void k_stage_mfma(StageArgs args, int64_t per) {
         const int v = PV * vv;
         const int64_t gi = base + v;
         T kv[PV];
-#pragma unroll
-        for (int u = 0; u < PV; ++u) kv[u] = sh.sY[v + u + (v + u) / NP];
+        kvals(v, kv);
         if (a.src_rows > 0 && (takes_src(v / NP) || takes_src((v + PV - 1) / NP))) {
             T srv[PV], siv[PV];
             ldv(a.Sre, gi, srv);
@@ -1092,7 +849,7 @@ void k_stage_mfma(StageArgs args, int64_t per) {
 #pragma unroll
             for (int u = 0; u < PV; ++u) {
                 const int row = (v + u) / NP;
-                if (takes_src(row)) kv[u] += scos * srv[u] - ssin * siv[u];
+                if (takes_src(row)) kv[u] = fma(scos, srv[u], fma(-ssin, siv[u], kv[u]));
             }
 #pragma unroll 1
             // further harmonics (tables read from the kernel arguments, as in k_stage)
@@ -1280,8 +1037,8 @@ void k_stage_mfma(StageArgs args, int64_t per) {
 #pragma unroll
             for (int u = 0; u < PV; ++u) {
                 const double ud = (double)x0[u], kd = (double)kv[u];
-                a.Fre[gi + u] += a.fa_re * ud + a.fb_re * kd;
-                a.Fim[gi + u] += a.fa_im * ud + a.fb_im * kd;
+                a.Fre[gi + u] = fma(a.fa_re, ud, fma(a.fb_re, kd, a.Fre[gi + u]));
+                a.Fim[gi + u] = fma(a.fa_im, ud, fma(a.fb_im, kd, a.Fim[gi + u]));
             }
 #pragma unroll 1
             for (int h = 1; MH && h < a.nharm; ++h)
@@ -1292,6 +1049,1277 @@ void k_stage_mfma(StageArgs args, int64_t per) {
                     args.Fim[h * args.hstride + gi + u] += args.hfa_im[h] * ud + args.hfb_im[h] * kd;
                 }
         }
+    }
+}
+
+// PIPE: the next face's neighbour traces are requested before this face's
+// flux (more registers, the gather latency hides behind the lift).
+// W: waves per workgroup.  W = 2 gives each wave half the output tiles: P3
+// one of its two 16-row tiles (both waves build the same B operands), P2 two
+// of the four 16-column tiles (each wave builds only its own); each runs half
+// the MFMAs, the flux items and the update pass are shared by 128 threads.  A
+// block's dependent chain gets shorter, which pays where the launch ends in a
+// partial round of workgroups.
+// EAGER: the neighbour traces of all four faces are requested right after
+// the staging (four faces' loads in flight during the volume product instead
+// of one), and faces alternate between two flux tiles, so a face needs one
+// barrier instead of two.  CSPLIT (P3, two waves): the waves split the output
+// by column tiles, each building only its own B operands and running both
+// row tiles.  W = 4: each wave one row tile and two column tiles (P3) or one
+// column tile (P2), a quarter of the MFMAs and fewer registers per wave.
+template <int Q, bool PIPE, bool MH, int W, bool EAGER = false, bool CSPLIT = false, bool LTSM = false>
+__global__ __launch_bounds__(64 * W)
+__attribute__((amdgpu_waves_per_eu(W == 4 ? (EAGER ? 2 : 4) : W == 1 || EAGER || CSPLIT ? 2 : 3, 8)))
+void k_stage_mfma(StageArgs args, int64_t per) {
+    using T = double;
+    using MD = MfmaDim<Q>;
+    using acc_t = typename Mfma<T>::acc_t;
+    constexpr int NP = MD::NP, NFP = MD::NFP, MT = MD::MT, KSV = MD::KSV, KSF = MD::KSF;
+    constexpr int RS = NP + 1;
+    constexpr int KF = 4 * KSF;
+    constexpr int NTH = 64 * W;                      // threads of the workgroup
+    constexpr int RF = (EPW * NFP + NTH - 1) / NTH;  // flux items per thread and face
+    // two waves split the output tiles: by rows when there are two row tiles
+    // (P3, unless CSPLIT), by the four 16-column tiles otherwise; four waves
+    // split by rows (P3) and by columns
+    static_assert(W == 1 || W == 2 || W == 4, "one, two or four waves per block");
+    constexpr bool ROWS = (W == 2 && MT == 2 && !CSPLIT) || (W == 4 && MT == 2);
+    constexpr bool COLS = (W == 2 && (MT == 1 || CSPLIT)) || W == 4;
+    constexpr int NB = EAGER ? 2 : 1;  // flux tiles
+    using Sh = MfmaShared<Q, NB>;
+    constexpr int MW = ROWS ? 1 : MT;  // output row tiles of one wave
+    constexpr int CWAVES = COLS ? (ROWS ? W / 2 : W) : 1;  // waves across the column tiles
+    constexpr int NW = 4 / CWAVES;                          // output column tiles of one wave
+    static_assert(W == 1 || ((ROWS || COLS) && RF == 1), "several waves per block need one flux item per thread");
+    __shared__ Sh sh;
+
+    StageArgs a;
+    if (!member_args<T>(args, a)) return;  // uniform per workgroup
+    int64_t blk = xcd_block(per);
+    if (a.blist) {  // only the listed element blocks
+        if (blk >= a.nblist) return;
+        blk = a.blist[blk];
+    }
+    const int64_t e0 = blk * EPW;
+    if (e0 >= a.K) return;  // uniform per workgroup
+    const T* __restrict__ Y = (const T*)a.Y;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int mt0 = ROWS ? (wave & 1) : 0;                           // first output row tile of this wave
+    const int nt0 = COLS ? NW * (ROWS ? wave >> 1 : wave) : 0;  // first output column tile of this wave
+    const int ne = (int)((a.K - e0) < EPW ? (a.K - e0) : EPW);
+    const int64_t base = e0 * 6 * NP;
+    constexpr int PV = 16 / (int)sizeof(T);  // values per 16-byte group
+    const int nvv = ne * 6 * NP / PV;        // 16-byte groups of the chunk (6 NP ne is a multiple of 4)
+
+    // matrix fragments (coalesced: fragment-major, lane-minor); lift
+    // fragments one face at a time, requested one face ahead
+    const T* fr = gFrag64 + frag_off(Q);
+    T afV[MW][KSV], afL[MW][KSF], afN[MW][KSF];
+    auto lift_frags = [&](int f, T (&d)[MW][KSF]) {
+#pragma unroll
+        for (int mt = 0; mt < MW; ++mt)
+#pragma unroll
+            for (int ks = 0; ks < KSF; ++ks) d[mt][ks] = fr[(MT * KSV + (f * MT + mt + mt0) * KSF + ks) * 64 + lane];
+    };
+
+    // ---- staging: chunk fields, geometry, connectivity, face-node tables;
+    // the volume and face-0 lift fragments are requested right behind the
+    // chunk's loads, so their latency hides behind the staging wait
+    const uint32_t keep = a.imask ? (a.imask[blk] ^ (a.imask_inv ? 0xffffffffu : 0u)) : 0xffffffffu;
+    {
+        ChunkIn<T, Q, NTH> in;
+        in.fetch(Y, (const T*)a.geo, a.conn, e0, ne, tid);
+#pragma unroll
+        for (int mt = 0; mt < MW; ++mt)
+#pragma unroll
+            for (int ks = 0; ks < KSV; ++ks) afV[mt][ks] = fr[((mt + mt0) * KSV + ks) * 64 + lane];
+        lift_frags(0, afL);
+        for (int v = tid; v < NB * KF * Sh::FS; v += NTH) sh.sF[v] = T(0);
+        in.put(sh.sY, sh.sG, sh.sC, sh.sT, ne, tid, keep);
+    }
+    __syncthreads();
+
+    // face 0's neighbour traces (EAGER: every face's) in flight during the volume product
+    FluxItems<Q, RF> itm;
+    itm.init(ne, tid);
+    TraceGather<T, Q, RF> cur, nxt;
+    TraceGather<T, Q, RF> all[EAGER ? 4 : 1];
+    if constexpr (EAGER) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) all[f].issue(Y, sh.sC, sh.sT, itm, f, e0, ne, a.imask, a.imask_inv);
+    } else {
+        cur.issue(Y, sh.sC, sh.sT, itm, 0, e0, ne, a.imask, a.imask_inv);
+    }
+
+    const int q4 = lane >> 4;   // K row within a 4-row block / output row group
+    const int l16 = lane & 15;  // output column within a 16-column tile
+    acc_t acc[MW][NW];
+#pragma unroll
+    for (int mt = 0; mt < MW; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NW; ++nt) acc[mt][nt] = acc_t{T(0), T(0), T(0), T(0)};
+
+    // ---- volume product: B[(a, j)][n] = sgn (g_a[m1] V_m2(j) - g_a[m2] V_m1(j));
+    // padded columns read element 0 (their results are never stored)
+#pragma unroll
+    for (int nt = 0; nt < NW; ++nt) {
+        const int n = (nt + nt0) * 16 + l16;
+        const int e = n < 6 * ne ? n / 6 : 0;
+        const int s = n - 6 * (n / 6);
+        const int m = s < 3 ? s : s - 3;
+        const int m1 = m == 2 ? 0 : m + 1, m2 = m == 0 ? 2 : m - 1;  // (m+1)%3, (m+2)%3
+        const int vb = e * 6 + (s < 3 ? 3 : 0);
+        const T sgn = s < 3 ? T(-1) : T(1);
+        const T* gE = &sh.sG[e * kGeo];
+        T g1[3], g2[3];
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            g1[ax] = sgn * gE[3 * ax + m1];
+            g2[ax] = sgn * gE[3 * ax + m2];
+        }
+        const T* v1 = &sh.sY[(vb + m1) * RS];
+        const T* v2 = &sh.sY[(vb + m2) * RS];
+        constexpr int NJ = MD::NJ;
+        T r1[NJ], r2[NJ];
+#pragma unroll
+        for (int t = 0; t < NJ; ++t) {
+            const int j = q4 + 4 * t;
+            const bool in = NP % 4 == 0 || j < NP;  // j >= Np: zero fragment, zero operand
+            r1[t] = in ? v1[in ? j : 0] : T(0);
+            r2[t] = in ? v2[in ? j : 0] : T(0);
+        }
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax)
+#pragma unroll
+            for (int t = 0; t < NJ; ++t) {
+                const T b = fma(g1[ax], r2[t], -g2[ax] * r1[t]);
+#pragma unroll
+                for (int mt = 0; mt < MW; ++mt)
+                    acc[mt][nt] = Mfma<T>::mma(afV[mt][ax * NJ + t], b, acc[mt][nt]);
+            }
+    }
+
+    // ---- upwind flux and lift, one face at a time
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+        if (!EAGER && PIPE && f < 3) nxt.issue(Y, sh.sC, sh.sT, itm, f + 1, e0, ne, a.imask, a.imask_inv);
+        if (f < 3) lift_frags(f + 1, afN);
+        T* tile = sh.sF + (EAGER ? (f & 1) * KF * Sh::FS : 0);
+        const TraceGather<T, Q, RF>& gat = EAGER ? all[f] : cur;
+#pragma unroll
+        for (int r = 0; r < RF; ++r) {
+            if (!itm.on[r]) continue;
+            const int k = itm.k[r];
+            const int fe = itm.fe[r];
+            const int own = sh.sT[f * NFP + k];
+            T Em[3], Hm[3], Ep[3], Hp[3];
+#pragma unroll
+            for (int cc = 0; cc < 3; ++cc) {
+                Em[cc] = sh.sY[(fe * 6 + cc) * RS + own];
+                Hm[cc] = sh.sY[(fe * 6 + 3 + cc) * RS + own];
+            }
+            const int code = gat.code[r];
+            if (code >= 0) {
+                gat.values(sh.sY, r, Ep, Hp);
+            } else if (code == -1) {  // PEC ghost: E+ = -E-, H+ = H-
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) {
+                    Ep[cc] = -Em[cc];
+                    Hp[cc] = Hm[cc];
+                }
+            } else {  // impedance ghost (homogeneous part): zero exterior state
+#pragma unroll
+                for (int cc = 0; cc < 3; ++cc) {
+                    Ep[cc] = T(0);
+                    Hp[cc] = T(0);
+                }
+            }
+            T fx[6];
+            upwind3(&sh.sG[fe * kGeo + 9 + 7 * f], Em, Hm, Ep, Hp, fx);
+            T* o = &tile[k * Sh::FS + fe * 6];
+#pragma unroll
+            for (int cc = 0; cc < 6; ++cc) o[cc] = fx[cc];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int ks = 0; ks < KSF; ++ks) {
+            T b[NW];
+#pragma unroll
+            for (int nt = 0; nt < NW; ++nt) b[nt] = tile[(ks * 4 + q4) * Sh::FS + (nt + nt0) * 16 + l16];
+#pragma unroll
+            for (int nt = 0; nt < NW; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MW; ++mt)
+                    acc[mt][nt] = Mfma<T>::mma(afL[mt][ks], b[nt], acc[mt][nt]);
+        }
+        // one tile: it is rewritten by the next face; two tiles: the next face
+        // writes the other one, and the face after it only once every thread
+        // has passed the next face's barrier (so has finished this lift)
+        if (!EAGER) __syncthreads();
+        if (f < 3) {
+            if (!EAGER) {
+                if (!PIPE) nxt.issue(Y, sh.sC, sh.sT, itm, f + 1, e0, ne, a.imask, a.imask_inv);
+                cur = nxt;
+            }
+#pragma unroll
+            for (int mt = 0; mt < MW; ++mt)
+#pragma unroll
+                for (int ks = 0; ks < KSF; ++ks) afL[mt][ks] = afN[mt][ks];
+        }
+    }
+
+    // ---- scaled right-hand side (1/eps or 1/mu, conductivity) into the
+    // staging tile, in place: every value is read and written by one lane
+#pragma unroll
+    for (int nt = 0; nt < NW; ++nt) {
+        const int n = (nt + nt0) * 16 + l16;
+        if (n >= 6 * ne) continue;
+        const int e = n / 6;
+        const int s = n - 6 * e;
+        const T inv = s < 3 ? sh.sG[e * kGeo + 37] : sh.sG[e * kGeo + 38];
+        const T sig = s < 3 ? sh.sG[e * kGeo + 39] : T(0);
+#pragma unroll
+        for (int mt = 0; mt < MW; ++mt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = (mt + mt0) * 16 + Mfma<T>::row(q4, r);
+                if (i < NP) {
+                    T* p = &sh.sY[n * RS + i];
+                    *p = fma(inv, acc[mt][nt][r], -sig * *p);
+                }
+            }
+    }
+    __syncthreads();
+
+    // ---- stage update
+    MfmaUpdateIn<T, Q, NTH, LTSM> upd;
+    upd.fetch(a, base, nvv, tid);
+    stage_update<T, Q, NTH, MH, LTSM>(args, a, upd, blk, base, nvv, tid, [&](int v, T (&kv)[PV]) {
+#pragma unroll
+        for (int u = 0; u < PV; ++u) kv[u] = sh.sY[v + u + (v + u) / NP];
+    });
+}
+
+// ---------------------------------------------------------------------------
+// FP32 stage kernel with one column per lane.
+//
+// A block of 10 elements has 60 columns (element, component); lane n of every
+// wave owns column n, and wave w its nodes 4 w .. 4 w + 3 (P3: five waves, P2:
+// three).  The products run on v_mfma_f32_4x4x1_16b_f32 with the
+// matrix rows broadcast (mfma_cols.h): the B operand of a K step is the lane's
+// own value, so
+//   * the reference derivatives D_a y need the lane's own row only (16-byte LDS
+//     reads), no operands are built, no matrix row is padded (20 rows = five
+//     groups of four; the 16-row tiles of v_mfma_f32_16x16x4 spend 3/8 of
+//     their rows on padding), and the matrices of a wave take 4 + 3 registers;
+//   * curl terms are exchanged between the six lanes of an element, the lift
+//     of all four faces reads the lane's 4 Nfp fluxes (16-byte LDS reads), and
+//     the right-hand side ends up with the lane that owns it.
+// Every global load that does not depend on another one (stage input, geometry,
+// connectivity, matrices, update operands) is requested at the start (P3: the
+// update operands behind the volume product, which leaves room for seven waves
+// per SIMD: 30.7 us per 48000-tet launch against 32.5; P2: 110 us against 115 per
+// 384000-tet launch the early way); the neighbour traces follow behind one
+// barrier, with consecutive lanes on the nodes of a face, whose values share
+// cache lines.  Three barriers in all.
+//
+// us per launch, before (the best form on 16x16x4 tiles with the wave's columns
+// split over its lanes) and now: P2 3072 tets 6.2 / 5.1, 24576 12.0 / 10.3,
+// 82944 28.2 / 24.2, 384000 117.7 / 110.4, 64 members of 10368 186.7 / 184; P3
+// 3072 8.9 / 6.2, 10368 13.6 / 10.0, 48000 36.5 / 30.7, 82944 56.8 / 49.7.  What
+// bounds it: memory for the large P2 launches (1.15 GB of traffic per GB of
+// the implementation's bytes, 4.8-5 TB/s, a 1 GiB copy's rate being 5.1);
+// at P3 a block's chain of dependent steps and the vector units together (418
+// vector instructions a wave, a quarter of them on the matrix cores).
+// LDS rows: stage input [column][RS], flux [column][FS], both conflict-free
+// for 16-byte accesses of consecutive columns (RS / 4 and FS / 4 odd).
+template <int Q> struct ColDim {
+    static constexpr int NP = Dim<Q>::NP, NFP = Dim<Q>::NFP;
+    static constexpr int W = (NP + 3) / 4, NTH = 64 * W;   // waves, threads
+    static constexpr int RS = 4 * W;
+    static constexpr int FS = 4 * NFP + (NFP % 2 ? 0 : 4);
+    static constexpr int NV = (3 * NP + 15) / 16, NL = (4 * NFP + 15) / 16;  // operand registers: D, LIFT
+    static constexpr int NTAB = W * (NV + NL) * 64;
+    static constexpr int RF = (EPW * 4 * NFP + NTH - 1) / NTH;  // flux nodes per thread
+};
+__host__ __device__ constexpr int col_off(int q) {
+    return q <= 2 ? 0 : ColDim<2>::NTAB;
+}
+constexpr int kColTotal = ColDim<2>::NTAB + ColDim<3>::NTAB;
+// Broadcast operands [wave][D, LIFT registers][lane]: lane l of register v holds
+// row 4 wave + l % 4 of K step 16 v + l / 4; D's K steps are (node j, axis a) =
+// (step / 3, step % 3), LIFT's (face, face node).
+__device__ float gCol[kColTotal];
+
+template <int Q> struct ColMats {
+    using CD = ColDim<Q>;
+    float mV[CD::NV], mL[CD::NL];
+    __device__ __forceinline__ void load(int wave, int lane) {
+        const float* t = gCol + col_off(Q) + wave * (CD::NV + CD::NL) * 64 + lane;
+#pragma unroll
+        for (int v = 0; v < CD::NV; ++v) mV[v] = t[64 * v];
+#pragma unroll
+        for (int v = 0; v < CD::NL; ++v) mL[v] = t[64 * (CD::NV + v)];
+    }
+};
+
+// A column's lane: its element, component, and the lanes and metric terms the
+// curl exchange needs (k_stage's, see there).
+struct ColLane {
+    int el, c, row, lane_p, lane_m, kp, km;
+    bool act;
+    __device__ __forceinline__ void init(int lane, int ne) {
+        el = lane / 6;
+        c = lane - 6 * el;
+        act = el < ne;
+        el = act ? el : 0;
+        row = el * 6 + c;
+        const int c3 = c < 3 ? c : c - 3;
+        kp = c3 == 0 ? 2 : c3 - 1;
+        km = c3 == 2 ? 0 : c3 + 1;
+        const int sb = el * 6 + (c < 3 ? 3 : 0);
+        lane_p = sb + (c3 == 0 ? 2 : c3 - 1);
+        lane_m = sb + (c3 == 2 ? 0 : c3 + 1);
+    }
+};
+
+// curl of the lane's column at the wave's nodes (E rows: -curl H, H rows: +curl
+// E), from the staged rows; geo = the element's geometry.
+template <int Q>
+__device__ __forceinline__ f32x4 col_volume(const float* srow, const float* geo, const ColLane& L,
+                                            const ColMats<Q>& mat) {
+    using CD = ColDim<Q>;
+    float y[CD::RS];
+#pragma unroll
+    for (int v = 0; v < CD::RS / 4; ++v) {
+        const f32x4 t = reinterpret_cast<const f32x4*>(srow)[v];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) y[4 * v + u] = t[u];
+    }
+    f32x4 d[3] = {};
+    mfma_rows<CD::NP, 3>(mat.mV, y, d);
+    const float sgn = L.c < 3 ? -1.f : 1.f;
+    f32x4 pv = {0.f, 0.f, 0.f, 0.f}, mv = {0.f, 0.f, 0.f, 0.f}, acc;
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        const float gp = geo[3 * ax + L.kp], gm = geo[3 * ax + L.km];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            pv[u] = fmaf(gp, d[ax][u], pv[u]);
+            mv[u] = fmaf(-gm, d[ax][u], mv[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] = sgn * (__shfl(pv[u], L.lane_p) + __shfl(mv[u], L.lane_m));
+    return acc;
+}
+
+// acc + LIFT (the column's fluxes), faces 0, 1 on top of acc and faces 2, 3 in
+// a sum of their own (two chains of dependent products instead of one).
+template <int Q>
+__device__ __forceinline__ f32x4 col_lift(const float* frow, const ColMats<Q>& mat, f32x4 acc) {
+    using CD = ColDim<Q>;
+    constexpr int NF4 = 4 * CD::NFP;
+    float x[NF4];
+#pragma unroll
+    for (int v = 0; v < NF4 / 4; ++v) {
+        const f32x4 t = reinterpret_cast<const f32x4*>(frow)[v];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[4 * v + u] = t[u];
+    }
+    f32x4 b = {0.f, 0.f, 0.f, 0.f};
+    mfma_pair<NF4>(mat.mL, x, acc, b);
+    return acc + b;
+}
+
+// Four consecutive values v .. v + 3 of the block's contiguous rows in LDS rows
+// padded to RS (P2: 10 values in 12; pairs never straddle a row).
+template <int Q> __device__ __forceinline__ void col_put(float* S, int v, f32x4 x) {
+    if constexpr (ColDim<Q>::RS == ColDim<Q>::NP) {
+        *reinterpret_cast<f32x4*>(S + v) = x;
+    } else {
+        constexpr int NP = ColDim<Q>::NP, PAD = ColDim<Q>::RS - NP;
+        *reinterpret_cast<float2*>(S + v + v / NP * PAD) = make_float2(x[0], x[1]);
+        *reinterpret_cast<float2*>(S + v + 2 + (v + 2) / NP * PAD) = make_float2(x[2], x[3]);
+    }
+}
+template <int Q> __device__ __forceinline__ f32x4 col_get(const float* S, int v) {
+    if constexpr (ColDim<Q>::RS == ColDim<Q>::NP) {
+        return *reinterpret_cast<const f32x4*>(S + v);
+    } else {
+        constexpr int NP = ColDim<Q>::NP, PAD = ColDim<Q>::RS - NP;
+        const float2 p = *reinterpret_cast<const float2*>(S + v + v / NP * PAD);
+        const float2 q = *reinterpret_cast<const float2*>(S + v + 2 + (v + 2) / NP * PAD);
+        return f32x4{p.x, p.y, q.x, q.y};
+    }
+}
+
+template <int Q> struct ColShared {
+    using CD = ColDim<Q>;
+    float sY[EPW * 6 * CD::RS];
+    float sF[EPW * 6 * CD::FS];
+    float sG[EPW * kGeo];
+    uint8_t sT[4 * ft_words(Q)];
+};
+
+template <int Q, bool MH, bool LTSM>
+__global__ __launch_bounds__(ColDim<Q>::NTH) __attribute__((amdgpu_waves_per_eu(Q == 3 ? 7 : 5, 8)))
+void k_stage_col(StageArgs args, int64_t per) {
+    using CD = ColDim<Q>;
+    constexpr int NP = CD::NP, NFP = CD::NFP, RS = CD::RS, FS = CD::FS, NTH = CD::NTH, RF = CD::RF;
+    __shared__ __align__(16) ColShared<Q> sh;
+
+    StageArgs a;
+    if (!member_args<float>(args, a)) return;  // uniform per workgroup
+    int64_t blk = xcd_block(per);
+    if (a.blist) {  // only the listed element blocks
+        if (blk >= a.nblist) return;
+        blk = a.blist[blk];
+    }
+    const int64_t e0 = blk * EPW;
+    if (e0 >= a.K) return;  // uniform per workgroup
+    const float* __restrict__ Y = (const float*)a.Y;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ne = (int)((a.K - e0) < EPW ? (a.K - e0) : EPW);
+    const int64_t base = e0 * 6 * NP;
+    const int nvv = ne * 6 * NP / 4;  // 16-byte groups of the block's rows
+    const uint32_t keep = a.imask ? (a.imask[blk] ^ (a.imask_inv ? 0xffffffffu : 0u)) : 0xffffffffu;
+
+    // ---- every load that depends on no other
+    constexpr int NIT = (EPW * 6 * NP / 4 + NTH - 1) / NTH, NG = (EPW * kGeo / 4 + NTH - 1) / NTH;
+    constexpr int NT = (ft_words(Q) + NTH - 1) / NTH;
+    int code[RF];
+    f32x4 yin[NIT], gin[NG];
+    uint32_t tw[NT];
+    ColMats<Q> mat;
+    MfmaUpdateIn<float, Q, NTH, LTSM> upd;
+#pragma unroll
+    for (int r = 0; r < RF; ++r) {
+        const int it = tid + NTH * r;
+        code[r] = it < ne * 4 * NFP ? a.conn[e0 * 4 + it / NFP] : -3;
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+        if (tid + NTH * t < ft_words(Q)) tw[t] = cFaceTab[ft_off(Q) + tid + NTH * t];
+#pragma unroll
+    for (int t = 0; t < NIT; ++t)
+        if (tid + NTH * t < nvv) yin[t] = reinterpret_cast<const f32x4*>(Y + base)[tid + NTH * t];
+#pragma unroll
+    for (int t = 0; t < NG; ++t)
+        if (tid + NTH * t < ne * kGeo / 4)
+            gin[t] = reinterpret_cast<const f32x4*>((const float*)a.geo + e0 * kGeo)[tid + NTH * t];
+    mat.load(wave, lane);
+    if constexpr (Q < 3) upd.fetch(a, base, nvv, tid);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+        if (tid + NTH * t < ft_words(Q)) reinterpret_cast<uint32_t*>(sh.sT)[tid + NTH * t] = tw[t];
+#pragma unroll
+    for (int t = 0; t < NIT; ++t) {
+        const int v = 4 * (tid + NTH * t);
+        if (tid + NTH * t < nvv) {
+            if (!((keep >> (v / (6 * NP))) & 1u)) yin[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            col_put<Q>(sh.sY, v, yin[t]);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < NG; ++t)
+        if (tid + NTH * t < ne * kGeo / 4) reinterpret_cast<f32x4*>(sh.sG)[tid + NTH * t] = gin[t];
+    __syncthreads();
+
+    // ---- neighbour traces of the thread's face nodes, in flight during the
+    // volume product (a neighbour in the block is read from LDS)
+    float nv[RF][6];
+    int own[RF], nbo[RF];
+#pragma unroll
+    for (int r = 0; r < RF; ++r) {
+        const int it = tid + NTH * r, t = it / NFP, k = it - t * NFP;
+        own[r] = (t >> 2) * 6 * RS + sh.sT[code[r] != -3 ? (t & 3) * NFP + k : 0];
+        nbo[r] = -1;
+        if (code[r] >= 0) {
+            const int nn = sh.sT[4 * NFP + (((code[r] >> 3) & 3) * 6 + (code[r] & 7)) * NFP + k];
+            const int64_t nb = code[r] >> 5;
+            if (nb >= e0 && nb < e0 + ne) {
+                nbo[r] = (int)(nb - e0) * 6 * RS + nn;
+            } else if (a.imask && !(((a.imask[nb / EPW] >> (int)(nb % EPW)) & 1u) ^ (uint32_t)a.imask_inv)) {
+#pragma unroll
+                for (int cc = 0; cc < 6; ++cc) nv[r][cc] = 0.f;
+            } else {
+                const float* q = Y + nb * 6 * NP + nn;
+#pragma unroll
+                for (int cc = 0; cc < 6; ++cc) nv[r][cc] = q[cc * NP];
+            }
+        }
+    }
+
+    ColLane L;
+    L.init(lane, ne);
+    const float* gl = &sh.sG[L.el * kGeo];
+    f32x4 acc = col_volume<Q>(&sh.sY[L.row * RS], gl, L, mat);
+    if constexpr (Q == 3) upd.fetch(a, base, nvv, tid);  // in flight during flux and lift
+
+    // ---- upwind flux of the thread's face nodes
+#pragma unroll
+    for (int r = 0; r < RF; ++r) {
+        if (code[r] == -3) continue;
+        const int it = tid + NTH * r, t = it / NFP, k = it - t * NFP;
+        const float* om = &sh.sY[own[r]];
+        float Em[3], Hm[3], Ep[3], Hp[3], fx[6];
+#pragma unroll
+        for (int cc = 0; cc < 3; ++cc) {
+            Em[cc] = om[cc * RS];
+            Hm[cc] = om[(3 + cc) * RS];
+        }
+        if (nbo[r] >= 0) {
+            const float* np = &sh.sY[nbo[r]];
+#pragma unroll
+            for (int cc = 0; cc < 3; ++cc) {
+                Ep[cc] = np[cc * RS];
+                Hp[cc] = np[(3 + cc) * RS];
+            }
+        } else {
+#pragma unroll
+            for (int cc = 0; cc < 3; ++cc) {
+                // PEC ghost: E+ = -E-, H+ = H-; impedance ghost (homogeneous
+                // part): zero exterior state
+                Ep[cc] = code[r] >= 0 ? nv[r][cc] : code[r] == -1 ? -Em[cc] : 0.f;
+                Hp[cc] = code[r] >= 0 ? nv[r][3 + cc] : code[r] == -1 ? Hm[cc] : 0.f;
+            }
+        }
+        upwind3(&sh.sG[(t >> 2) * kGeo + 9 + 7 * (t & 3)], Em, Hm, Ep, Hp, fx);
+        float* o = &sh.sF[(t >> 2) * 6 * FS + (t & 3) * NFP + k];
+#pragma unroll
+        for (int cc = 0; cc < 6; ++cc) o[cc * FS] = fx[cc];
+    }
+    __syncthreads();
+
+    // ---- lift; scaled right-hand side in place of the stage input (only this
+    // thread still reads these values)
+    acc = col_lift<Q>(&sh.sF[L.row * FS], mat, acc);
+    if (L.act) {
+        const float inv = L.c < 3 ? gl[37] : gl[38];
+        const float sig = L.c < 3 ? gl[39] : 0.f;
+        f32x4* p = reinterpret_cast<f32x4*>(&sh.sY[L.row * RS + 4 * wave]);
+        const f32x4 y = *p;
+        f32x4 kv;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) kv[u] = fmaf(inv, acc[u], -sig * y[u]);
+        *p = kv;
+    }
+    __syncthreads();
+    stage_update<float, Q, NTH, MH, LTSM>(args, a, upd, blk, base, nvv, tid, [&](int v, float (&kv)[4]) {
+        const f32x4 t = col_get<Q>(sh.sY, v);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) kv[u] = t[u];
+    });
+}
+
+// ---------------------------------------------------------------------------
+// A whole period in one launch (PeriodArgs in launch.h), for meshes whose
+// element blocks all fit on the device at once: a workgroup keeps a block of 10
+// elements resident -- state, stage combination and low parts in registers,
+// stage input and geometry in LDS, matrix fragments in registers -- and the
+// stages run in a loop.  The traces of faces between blocks go through
+// mailboxes of (value, epoch) pairs (tagged.h; the 2-D kernels do the same):
+// after its update a block writes its traces into its neighbours' mailboxes
+// and polls its own until they carry the stage's epoch.  Two buffers alternate
+// between epochs; a block overwrites a mailbox two stages later, after it has
+// read that neighbour's next epoch, which the neighbour wrote after reading
+// this one.
+//
+// The faces of a period kernel's block: which traces leave it, which arrive,
+// and the flux nodes of its threads.  LDS array S: the staged block [row][RS],
+// behind it (offset XO) the received traces [face][component][face node],
+// behind these (FO) the flux.
+template <typename T, int Q, int NTH, int RS> struct PeriodFaces {
+    static constexpr int NFP = Dim<Q>::NFP;
+    static constexpr int NFACE = EPW * 4;
+    static constexpr int XO = EPW * 6 * RS;
+    static constexpr int CF = 6 * NFP;         // values of a mailbox
+    static constexpr int RF = (NFACE * NFP + NTH - 1) / NTH;  // flux nodes per thread
+    static constexpr int FO = XO + NFACE * CF;
+    // mailbox values a thread keeps track of (20 of a block's 40 faces leaving
+    // it; more, on meshes numbered worse, are looked up each time)
+    static constexpr int RQ = (20 * CF + NTH - 1) / NTH;
+    using X = Tagged<T>;
+    struct Shared {
+        int box[NFACE];        // mailbox j: the neighbour's mailbox ...
+        uint8_t face[NFACE];   // ... and its local face 4 e + f
+        uint8_t node[4 * NFP]; // own face nodes [f][k]
+        int stop;
+    };
+    uint32_t trace[RF], place[RF];
+    uint32_t mlds[RQ], mdst[RQ];
+    int n;  // values of the block's mailboxes
+
+    static __device__ __forceinline__ int table(int i) {
+        return (int)((cFaceTab[ft_off(Q) + i / 4] >> (8 * (i % 4))) & 255u);
+    }
+    __device__ __forceinline__ void mail(const Shared& sh, int i, int& src, uint32_t& dst, int& rcv) const {
+        const int j = i / CF, r = i - j * CF;
+        const int cc = r / NFP, k = r - cc * NFP;
+        const int t = sh.face[j];
+        src = ((t >> 2) * 6 + cc) * RS + sh.node[(t & 3) * NFP + k];
+        dst = (uint32_t)(sh.box[j] * CF + r) * X::W;
+        rcv = XO + t * CF + r;
+    }
+    // first part: the shared tables (a barrier follows)
+    __device__ __forceinline__ void tables(Shared& sh, const PeriodArgs& a, int64_t blk, int ne, int tid) {
+        const int64_t e0 = blk * EPW;
+        const int x0 = a.xstart[blk];
+        n = (a.xstart[blk + 1] - x0) * CF;
+        if (tid == 0) sh.stop = 0;
+        if (tid < 4 * NFP) sh.node[tid] = (uint8_t)table(tid);
+        if (tid < ne * 4) {
+            const int id = a.xslot[e0 * 4 + tid], cd = a.conn[e0 * 4 + tid];
+            if (id >= 0) {
+                sh.face[id - x0] = (uint8_t)tid;
+                sh.box[id - x0] = a.xslot[(int64_t)(cd >> 5) * 4 + ((cd >> 3) & 3)];
+            }
+        }
+    }
+    // second part: this thread's flux nodes and mailbox values.  trace: LDS
+    // offsets of the own and the neighbour's first component; place: the face's
+    // geometry (10 bits), the flux's place behind FO (14 bits: fo(f, k, e)) and
+    // what the neighbour is (8 bits): the offset between its components, 0 on a
+    // wall with the PEC ghost, 1 with the impedance ghost
+    template <typename F>
+    __device__ __forceinline__ void init(const Shared& sh, const PeriodArgs& a, int64_t e0, int ne, int tid, F fo) {
+        static_assert(NFP > 1 && RS > 1 && RS < 256 && XO + NFACE * CF < 65536 && EPW * kGeo < 1024, "packed offsets");
+#pragma unroll
+        for (int r = 0; r < RF; ++r) {
+            const int it = tid + NTH * r;
+            const int t = it < NFACE * NFP ? it / NFP : 0, k = it < NFACE * NFP ? it % NFP : 0;
+            const int e = t >> 2, f = t & 3;
+            const int code = t < ne * 4 ? a.conn[e0 * 4 + t] : -2;
+            const int own = e * 6 * RS + table(f * NFP + k);
+            int nbo = own, what = code == -1 ? 0 : 1;
+            if (code >= 0) {
+                const int64_t nb = code >> 5;
+                const int nf = (code >> 3) & 3;
+                const int nn = table(4 * NFP + (nf * 6 + (code & 7)) * NFP + k);
+                if (nb >= e0 && nb < e0 + ne) {
+                    nbo = (int)(nb - e0) * 6 * RS + nn;
+                    what = RS;
+                } else {  // the neighbour's mailbox order: its own face nodes
+                    int m = 0;
+                    for (int q = 0; q < NFP; ++q)
+                        if (table(nf * NFP + q) == nn) m = q;
+                    nbo = XO + t * CF + m;
+                    what = NFP;
+                }
+            }
+            trace[r] = (uint32_t)own | ((uint32_t)nbo << 16);
+            place[r] = (uint32_t)(e * kGeo + 9 + 7 * f) | ((uint32_t)fo(f, k, e) << 10) | ((uint32_t)what << 24);
+        }
+#pragma unroll
+        for (int r = 0; r < RQ; ++r) {
+            mlds[r] = mdst[r] = 0;
+            if (tid + NTH * r < n) {
+                int src, rcv;
+                mail(sh, tid + NTH * r, src, mdst[r], rcv);
+                mlds[r] = (uint32_t)src | ((uint32_t)rcv << 16);
+            }
+        }
+    }
+    // packed words stay packed: unpacked ahead of the loop they would take
+    // three times the registers
+    __device__ __forceinline__ void hold() {
+#pragma unroll
+        for (int r = 0; r < RF; ++r) asm volatile("" : "+v"(trace[r]), "+v"(place[r]));
+#pragma unroll
+        for (int r = 0; r < RQ; ++r) asm volatile("" : "+v"(mlds[r]), "+v"(mdst[r]));
+    }
+    // the block's traces into the neighbours' mailboxes (out: this epoch's buffer)
+    __device__ __forceinline__ void publish(const Shared& sh, const T* S, unsigned long long* out, uint32_t epoch,
+                                            int tid) const {
+#pragma unroll
+        for (int r = 0; r < RQ; ++r)
+            if (tid + NTH * r < n) X::put(out + mdst[r], S[mlds[r] & 0xffffu], epoch);
+        for (int i = tid + NTH * RQ; i < n; i += NTH) {
+            int src, rcv;
+            uint32_t dst;
+            mail(sh, i, src, dst, rcv);
+            X::put(out + dst, S[src], epoch);
+        }
+    }
+    // waits for the block's own mailboxes (in: this epoch's buffer)
+    __device__ __forceinline__ void receive(Shared& sh, T* S, Inbox<T, RQ, NTH>& box, const unsigned long long* in,
+                                            uint32_t epoch, const PeriodArgs& a, int tid) const {
+        const bool ok = box.settle(in, n, tid, epoch, a, [&](int i, int r, T v) {
+            int src, rcv = (int)(mlds[r < RQ ? r : 0] >> 16);
+            uint32_t dst;
+            if (r >= RQ) mail(sh, i, src, dst, rcv);
+            S[rcv] = v;
+        });
+        if (!ok) sh.stop = 1;
+    }
+    // flux of every face node of the block (a barrier follows); geo = the
+    // block's geometry
+    __device__ __forceinline__ void flux(T* S, const T* geo, int cstride, int tid) const {
+#pragma unroll
+        for (int r = 0; r < RF; ++r) {
+            if (tid + NTH * r >= NFACE * NFP) break;
+            const T* om = &S[trace[r] & 0xffffu];
+            const T* np = &S[trace[r] >> 16];
+            const int what = place[r] >> 24;
+            const int st = what > 1 ? what : RS;
+            T Em[3], Hm[3], Ep[3], Hp[3], fx[6];
+#pragma unroll
+            for (int cc = 0; cc < 3; ++cc) {
+                Em[cc] = om[cc * RS];
+                Hm[cc] = om[(3 + cc) * RS];
+                Ep[cc] = np[cc * st];
+                Hp[cc] = np[(3 + cc) * st];
+                if (what == 0) Ep[cc] = -Em[cc];          // PEC ghost: E+ = -E-, H+ = H-
+                if (what == 1) Ep[cc] = Hp[cc] = T(0);    // impedance ghost (homogeneous part): zero exterior state
+            }
+            upwind3(&geo[place[r] & 1023u], Em, Hm, Ep, Hp, fx);
+            T* o = &S[FO + ((place[r] >> 10) & 16383u)];
+#pragma unroll
+            for (int cc = 0; cc < 6; ++cc) o[cc * cstride] = fx[cc];
+        }
+    }
+};
+
+// Member, block and sizes of a period kernel's workgroup; false when it has
+// nothing to do.
+__device__ __forceinline__ bool period_block(const PeriodArgs& a, int64_t per, int& mem, int64_t& blk) {
+    mem = a.order ? a.order[a.first + blockIdx.y] : 0;
+    blk = xcd_block(per);
+    return blk * EPW < a.K;
+}
+
+// FP64 P2 and P3, with the tiles and the order of sums of k_stage_mfma's
+// four-wave form: results agree with the stage launches bit for bit.
+template <int Q, int OCC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC, 8)))
+void k_period_mfma(PeriodArgs a, int64_t per) {
+    using T = double;
+    using MD = MfmaDim<Q>;
+    using PF = PeriodFaces<T, Q, 256, MfmaDim<Q>::NP + 1>;
+    using acc_t = typename Mfma<T>::acc_t;
+    constexpr int NP = MD::NP, MT = MD::MT, KSV = MD::KSV, KSF = MD::KSF, KF = 4 * KSF;
+    constexpr int NTH = 256, RS = NP + 1, FO = PF::FO;
+    constexpr int FS = 65;                          // flux tile row stride, rows [f][face node], NFP .. KF - 1 of
+                                                    // a face multiplied by zero fragments
+    constexpr int NSH = FO + 4 * KF * FS;
+    constexpr int NW = MT == 2 ? 2 : 1;             // output column tiles of a wave (P3: one of two row tiles)
+    constexpr int PV = 16 / (int)sizeof(T);         // values of an update group
+    constexpr int NIT = (EPW * 6 * NP / PV + NTH - 1) / NTH;
+    typedef T V __attribute__((ext_vector_type(PV)));
+    __shared__ __align__(16) T S[NSH];
+    __shared__ T sG[EPW * kGeo];
+    __shared__ typename PF::Shared sh;
+
+    int mem;
+    int64_t blk;
+    if (!period_block(a, per, mem, blk)) return;  // uniform per workgroup
+    const int64_t e0 = blk * EPW;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int mt0 = MT == 2 ? (wave & 1) : 0, nt0 = MT == 2 ? 2 * (wave >> 1) : wave;
+    int q4 = lane >> 4, l16 = lane & 15, upd = tid;
+    const int ne = (int)((a.K - e0) < EPW ? (a.K - e0) : EPW);
+    const int nvv = ne * 6 * NP / PV;
+    const int64_t base = (int64_t)mem * a.bstride + e0 * 6 * NP;
+    const int M = a.msteps ? a.msteps[mem] : a.M;
+    const int NS = a.scheme == 2 ? 2 : 4;
+
+    // matrix fragments of the wave's row tile
+    T afV[KSV], afL[4][KSF];
+    {
+        const T* fr = gFrag64 + frag_off(Q);
+#pragma unroll
+        for (int ks = 0; ks < KSV; ++ks) afV[ks] = fr[(mt0 * KSV + ks) * 64 + lane];
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+#pragma unroll
+            for (int ks = 0; ks < KSF; ++ks) afL[f][ks] = fr[(MT * KSV + (f * MT + mt0) * KSF + ks) * 64 + lane];
+    }
+    // state: 16-byte groups v = tid + NTH t of the block's rows
+    V up[NIT], ap[NIT];
+    const T* geo = (const T*)a.geo + (int64_t)mem * a.gstride + e0 * kGeo;
+    for (int i = tid; i < ne * kGeo; i += NTH) sG[i] = geo[i];
+    for (int i = tid; i < NSH; i += NTH) S[i] = T(0);
+    PF pf;
+    pf.tables(sh, a, blk, ne, tid);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NIT; ++t) {
+        const int vv = tid + NTH * t;
+        up[t] = V(T(0));
+        ap[t] = V(T(0));
+        if (vv < nvv) {
+            up[t] = *reinterpret_cast<const V*>((const T*)a.U + base + PV * vv);
+            const int v = PV * vv;
+#pragma unroll
+            for (int u = 0; u < PV; ++u) S[v + u + (v + u) / NP] = up[t][u];
+        }
+    }
+    pf.init(sh, a, e0, ne, tid, [](int f, int k, int e) { return (f * KF + k) * FS + e * 6; });
+
+    uint32_t epoch = a.epoch;
+    const int64_t half = (int64_t)a.members * a.next * (PF::CF * PF::X::W);  // words of one buffer
+    unsigned long long* const xch = a.xch + (int64_t)mem * a.next * (PF::CF * PF::X::W);
+    const unsigned long long* const inbox = xch + (int64_t)a.xstart[blk] * (PF::CF * PF::X::W);
+    const uint32_t sm = a.src_rows > 0 ? (a.smask ? a.smask[(int64_t)mem * ((a.K + EPW - 1) / EPW) + blk] : 0xffffffffu) : 0u;
+    // RK4 with the filter ends with one more right-hand side at the last level
+    const bool tail = a.filter && NS == 4;
+    __syncthreads();
+    pf.publish(sh, S, xch + (epoch & 1) * half, epoch, tid);
+    for (int m = 0; m < M + (tail ? 1 : 0); ++m) {
+        const int ns = m < M ? NS : 1;
+        for (int s = 0; s < ns; ++s) {
+            pf.hold();
+            // indices are formed anew in every stage: ahead of the loop they and
+            // the geometry behind them would take the registers
+            asm volatile("" : "+v"(q4), "+v"(l16), "+v"(upd));
+            const double* tab = a.mtab + (((int64_t)(m < M ? m : a.M) * NS + s) * a.members + mem) * kMemberParams;
+            const T cy = (T)tab[0], ca = (T)tab[1], cu = (T)tab[2], scos = (T)tab[3], ssin = (T)tab[4];
+            // request the neighbours' traces; they travel during the volume product
+            const unsigned long long* const in = inbox + (epoch & 1) * half;
+            Inbox<T, PF::RQ, NTH> box;
+            box.request(in, 0, pf.n, tid);
+
+            // ---- volume product (k_stage_mfma)
+            acc_t acc[NW];
+#pragma unroll
+            for (int nt = 0; nt < NW; ++nt) {
+                acc[nt] = acc_t{T(0), T(0), T(0), T(0)};
+                const int n = (nt + nt0) * 16 + l16;
+                const int e = n < 6 * ne ? n / 6 : 0;
+                const int sc = n - 6 * (n / 6);
+                const int mm = sc < 3 ? sc : sc - 3;
+                const int m1 = mm == 2 ? 0 : mm + 1, m2 = mm == 0 ? 2 : mm - 1;
+                const int vb = e * 6 + (sc < 3 ? 3 : 0);
+                const T sgn = sc < 3 ? T(-1) : T(1);
+                const T* gE = &sG[e * kGeo];
+                T g1[3], g2[3];
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax) {
+                    g1[ax] = sgn * gE[3 * ax + m1];
+                    g2[ax] = sgn * gE[3 * ax + m2];
+                }
+                const T* v1 = &S[(vb + m1) * RS];
+                const T* v2 = &S[(vb + m2) * RS];
+                constexpr int NJ = MD::NJ;
+                T r1[NJ], r2[NJ];
+#pragma unroll
+                for (int t = 0; t < NJ; ++t) {
+                    const int j = q4 + 4 * t;
+                    const bool on = NP % 4 == 0 || j < NP;
+                    r1[t] = on ? v1[on ? j : 0] : T(0);
+                    r2[t] = on ? v2[on ? j : 0] : T(0);
+                }
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax)
+#pragma unroll
+                    for (int t = 0; t < NJ; ++t)
+                        acc[nt] = Mfma<T>::mma(afV[ax * NJ + t], fma(g1[ax], r2[t], -g2[ax] * r1[t]), acc[nt]);
+            }
+
+            pf.receive(sh, S, box, in, epoch, a, tid);
+            __syncthreads();
+            if (sh.stop) return;
+            pf.flux(S, sG, 1, tid);
+            __syncthreads();
+
+            // ---- lift, face by face
+#pragma unroll
+            for (int f = 0; f < 4; ++f)
+#pragma unroll
+                for (int ks = 0; ks < KSF; ++ks)
+#pragma unroll
+                    for (int nt = 0; nt < NW; ++nt)
+                        acc[nt] = Mfma<T>::mma(afL[f][ks], S[FO + (f * KF + ks * 4 + q4) * FS + (nt + nt0) * 16 + l16],
+                                               acc[nt]);
+            // ---- scaled right-hand side into the staged rows, in place
+#pragma unroll
+            for (int nt = 0; nt < NW; ++nt) {
+                const int n = (nt + nt0) * 16 + l16;
+                if (n >= 6 * ne) continue;
+                const int e = n / 6;
+                const int sc = n - 6 * e;
+                const T inv = sc < 3 ? sG[e * kGeo + 37] : sG[e * kGeo + 38];
+                const T sig = sc < 3 ? sG[e * kGeo + 39] : T(0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int i = mt0 * 16 + Mfma<T>::row(q4, r);
+                    if (i < NP) {
+                        T* p = &S[n * RS + i];
+                        *p = fma(inv, acc[nt][r], -sig * *p);
+                    }
+                }
+            }
+            __syncthreads();
+
+            // ---- update of the thread's groups, next stage input into LDS
+            const bool last = s == NS - 1;
+#pragma unroll
+            for (int t = 0; t < NIT; ++t) {
+                const int vv = upd + NTH * t;
+                if (vv >= nvv) continue;
+                const int v = PV * vv;
+                const int64_t gi = base + v;
+                T kv[PV];
+#pragma unroll
+                for (int u = 0; u < PV; ++u) kv[u] = S[v + u + (v + u) / NP];
+                if (sm) {
+                    auto takes = [&](int row) { return row - 6 * (row / 6) < a.src_rows && ((sm >> (row / 6)) & 1u); };
+                    if (takes(v / NP) || takes((v + PV - 1) / NP)) {
+                        const int64_t si = (int64_t)mem * a.sstride + e0 * 6 * NP + v;
+                        const V srv = *reinterpret_cast<const V*>((const T*)a.Sre + si);
+                        const V siv = *reinterpret_cast<const V*>((const T*)a.Sim + si);
+#pragma unroll
+                        for (int u = 0; u < PV; ++u)
+                            if (takes((v + u) / NP)) kv[u] = fma(scos, srv[u], fma(-ssin, siv[u], kv[u]));
+                    }
+                }
+                if (a.filter && s == 0) {  // the stage input is the state
+                    const double fa_re = tab[5], fa_im = tab[6], fb_re = tab[7], fb_im = tab[8];
+#pragma unroll
+                    for (int u = 0; u < PV; ++u) {
+                        const double ud = (double)up[t][u], kd = (double)kv[u];
+                        a.Fre[gi + u] = fma(fa_re, ud, fma(fb_re, kd, a.Fre[gi + u]));
+                        a.Fim[gi + u] = fma(fa_im, ud, fma(fb_im, kd, a.Fim[gi + u]));
+                    }
+                }
+                if (m >= M) continue;  // the last level's right-hand side: filter only
+                V y;
+                if (!last) {
+#pragma unroll
+                    for (int u = 0; u < PV; ++u) {
+                        if (NS == 4)
+                            ap[t][u] = s > 0 ? fma(ca, kv[u], ap[t][u]) : fma(ca, kv[u], up[t][u]);
+                        y[u] = fma(cy, kv[u], up[t][u]);
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < PV; ++u) up[t][u] = fma(cu, kv[u], NS == 4 ? ap[t][u] : up[t][u]);
+                    y = up[t];
+                }
+#pragma unroll
+                for (int u = 0; u < PV; ++u) S[v + u + (v + u) / NP] = y[u];
+            }
+            if (m + 1 < M || (m < M && (!last || tail))) {
+                ++epoch;
+                __syncthreads();
+                pf.publish(sh, S, xch + (epoch & 1) * half, epoch, tid);
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < NIT; ++t) {
+        const int vv = tid + NTH * t;
+        if (vv >= nvv) continue;
+        *reinterpret_cast<V*>((T*)a.U + base + PV * vv) = up[t];
+    }
+}
+
+// FP32: one column per lane, the arithmetic of k_stage_col.  A thread owns
+// nodes 4 wave .. 4 wave + 3 of its lane's column throughout -- state, stage
+// combination, right-hand side -- so nothing is exchanged between the lift and
+// the next stage input: three barriers a stage.  What bounds it: one exchange
+// (0.4-0.6 us one way) and a block's chain per stage -- 3.5 us at P2 and 3072
+// tets, 4.4 us at P3 -- and with several blocks on a compute unit their vector
+// instructions (P2, 15300 tets: 6.4 us).  OCC: waves per SIMD, what the registers
+// allow without spills (95 of 96 at P3).
+template <int Q, int OCC>
+__global__ __launch_bounds__(ColDim<Q>::NTH) __attribute__((amdgpu_waves_per_eu(OCC, 8)))
+void k_period_col(PeriodArgs a, int64_t per) {
+    using CD = ColDim<Q>;
+    constexpr int NP = CD::NP, NFP = CD::NFP, RS = CD::RS, FS = CD::FS, NTH = CD::NTH;
+    using PF = PeriodFaces<float, Q, NTH, RS>;
+    constexpr int FO = PF::FO, NSH = FO + EPW * 6 * FS;
+    __shared__ __align__(16) float S[NSH];
+    __shared__ float sG[EPW * kGeo];
+    __shared__ typename PF::Shared sh;
+
+    int mem;
+    int64_t blk;
+    if (!period_block(a, per, mem, blk)) return;  // uniform per workgroup
+    const int64_t e0 = blk * EPW;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ne = (int)((a.K - e0) < EPW ? (a.K - e0) : EPW);
+    const int M = a.msteps ? a.msteps[mem] : a.M;
+    const int NS = a.scheme == 2 ? 2 : 4;
+    ColLane L;
+    L.init(lane, ne);
+    ColMats<Q> mat;
+    mat.load(wave, lane);
+    // uniform bases, 32-bit lane offsets
+    const int64_t base = (int64_t)mem * a.bstride + e0 * 6 * NP, sbase = (int64_t)mem * a.sstride + e0 * 6 * NP;
+    uint32_t at = (uint32_t)(L.row * NP + 4 * wave);
+    float* const U = (float*)a.U + base;
+    uint16_t* const Ulo = (uint16_t*)a.Ulo + base;
+    const int nn = !L.act ? 0 : NP - 4 * wave < 4 ? NP - 4 * wave : 4;  // nodes of this thread
+    const float* geo = (const float*)a.geo + (int64_t)mem * a.gstride + e0 * kGeo;
+    for (int i = tid; i < ne * kGeo; i += NTH) sG[i] = geo[i];
+    for (int i = tid; i < NSH; i += NTH) S[i] = 0.f;
+    PF pf;
+    pf.tables(sh, a, blk, ne, tid);
+    __syncthreads();
+    f32x4 up = {0.f, 0.f, 0.f, 0.f}, ap = up;
+    uint32_t lop[2] = {0u, 0u};  // bfloat16 low parts
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (u < nn) {
+            up[u] = U[at + u];
+            lop[u / 2] |= (uint32_t)Ulo[at + u] << (16 * (u % 2));
+        }
+    f32x4* const own = reinterpret_cast<f32x4*>(&S[L.row * RS + 4 * wave]);
+    if (L.act) *own = up;
+    pf.init(sh, a, e0, ne, tid, [](int f, int k, int e) { return e * 6 * FS + f * NFP + k; });
+    const bool src = L.act && L.c < a.src_rows &&
+                     (!a.smask || ((a.smask[(int64_t)mem * ((a.K + EPW - 1) / EPW) + blk] >> L.el) & 1u));
+
+    uint32_t epoch = a.epoch;
+    const int64_t half = (int64_t)a.members * a.next * PF::CF;  // words of one buffer
+    unsigned long long* const xch = a.xch + (int64_t)mem * a.next * PF::CF;
+    const unsigned long long* const inbox = xch + (int64_t)a.xstart[blk] * PF::CF;
+    // RK4 with the filter ends with one more right-hand side at the last level
+    const bool tail = a.filter && NS == 4;
+    __syncthreads();
+    pf.publish(sh, S, xch + (epoch & 1) * half, epoch, tid);
+    for (int m = 0; m < M + (tail ? 1 : 0); ++m) {
+        const int ns = m < M ? NS : 1;
+        for (int s = 0; s < ns; ++s) {
+            pf.hold();
+            asm volatile("" : "+v"(at));
+            // an offset of zero that the compiler cannot see: geometry is read
+            // from LDS in every stage (ahead of the loop it would take registers)
+            int z = 0;
+            asm volatile("" : "+v"(z));
+            const double* tab = a.mtab + (((int64_t)(m < M ? m : a.M) * NS + s) * a.members + mem) * kMemberParams;
+            const auto coef = [&](int k) {  // uniform: kept in scalar registers
+                return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint((float)tab[k])));
+            };
+            const float cy = coef(0), ca = coef(1), cu = coef(2), scos = coef(3), ssin = coef(4);
+            // request the neighbours' traces; they travel during the volume product
+            const unsigned long long* const in = inbox + (epoch & 1) * half;
+            Inbox<float, PF::RQ, NTH> box;
+            box.request(in, 0, pf.n, tid);
+            const float* gl = &sG[L.el * kGeo + z];
+            f32x4 acc = col_volume<Q>(&S[L.row * RS], gl, L, mat);
+
+            pf.receive(sh, S, box, in, epoch, a, tid);
+            __syncthreads();
+            if (sh.stop) return;
+            pf.flux(S, sG + z, FS, tid);
+            __syncthreads();
+            acc = col_lift<Q>(&S[FO + L.row * FS], mat, acc);
+
+            const float inv = L.c < 3 ? gl[37] : gl[38];
+            const float sig = L.c < 3 ? gl[39] : 0.f;
+            const f32x4 yo = *own;
+            f32x4 kv;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) kv[u] = fmaf(inv, acc[u], -sig * yo[u]);
+            if (src) {
+                const float* const Sre = (const float*)a.Sre + sbase;
+                const float* const Sim = (const float*)a.Sim + sbase;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (u < nn)
+                        kv[u] = fmaf(scos, Sre[at + u],
+                                     fmaf(-ssin, Sim[at + u], kv[u]));
+            }
+            if (a.filter && s == 0) {
+                const double fa_re = tab[5], fa_im = tab[6], fb_re = tab[7], fb_im = tab[8];
+                double* const Fre = a.Fre + base;
+                double* const Fim = a.Fim + base;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (u < nn) {
+                        const double ud = (double)yo[u], kd = (double)kv[u];
+                        Fre[at + u] = fma(fa_re, ud, fma(fb_re, kd, Fre[at + u]));
+                        Fim[at + u] = fma(fa_im, ud, fma(fb_im, kd, Fim[at + u]));
+                    }
+            }
+            if (m >= M) break;  // the last level's right-hand side: filter only
+            const bool last = s == NS - 1;
+            f32x4 yn;
+            if (!last) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (NS == 4) ap[u] = s > 0 ? fmaf(ca, kv[u], ap[u]) : ca * kv[u];
+                    yn[u] = fmaf(cy, kv[u], up[u]);
+                }
+            } else {
+                float e[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const float lo = from_bf16(u % 2 ? lop[u / 2] >> 16 : lop[u / 2] & 0xffffu);
+                    float sum;
+                    two_sum(up[u], NS == 4 ? fmaf(cu, kv[u], ap[u]) + lo : fmaf(cu, kv[u], lo), sum, e[u]);
+                    up[u] = sum;
+                }
+                lop[0] = (uint32_t)to_bf16(e[0]) | ((uint32_t)to_bf16(e[1]) << 16);
+                lop[1] = (uint32_t)to_bf16(e[2]) | ((uint32_t)to_bf16(e[3]) << 16);
+                yn = up;
+            }
+            if (m + 1 < M || !last || tail) {
+                ++epoch;
+                if (L.act) *own = yn;  // every other reader of the old value is behind the flux's barrier
+                __syncthreads();
+                pf.publish(sh, S, xch + (epoch & 1) * half, epoch, tid);
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (u < nn) {
+            U[at + u] = up[u];
+            Ulo[at + u] = (uint16_t)(u % 2 ? lop[u / 2] >> 16 : lop[u / 2] & 0xffffu);
+        }
+}
+
+// P1 with the arithmetic of k_stage: lane = (element, component), each wave
+// one of the four nodes of every row.
+template <typename T>
+__global__ __launch_bounds__(256) void k_period_p1(PeriodArgs a, int64_t per) {
+    using PF = PeriodFaces<T, 1, 256, 5>;
+    constexpr bool COMP = std::is_same<T, float>::value;
+    constexpr int NP = 4, NFP = 3, NF4 = 4 * NFP, NTH = 256, RS = NP + 1, FO = PF::FO;
+    constexpr int MO = mat_off(1), LO = MO + 3 * NP * NP;
+    constexpr int NSH = FO + EPW * 6 * NF4;
+    __shared__ T S[NSH];
+    __shared__ T sG[EPW * kGeo];
+    __shared__ typename PF::Shared sh;
+
+    int mem;
+    int64_t blk;
+    if (!period_block(a, per, mem, blk)) return;  // uniform per workgroup
+    const int64_t e0 = blk * EPW;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int i = __builtin_amdgcn_readfirstlane(tid >> 6);  // the wave's node
+    const int ne = (int)((a.K - e0) < EPW ? (a.K - e0) : EPW);
+    const int M = a.msteps ? a.msteps[mem] : a.M;
+    const int NS = a.scheme == 2 ? 2 : 4;
+    const int el = lane / 6, c = lane - 6 * el;
+    const bool act = el < ne;
+    const int elc = act ? el : 0;
+    const int row = elc * 6 + c;
+    const int64_t at = (int64_t)mem * a.bstride + (e0 * 6 + row) * NP + i;
+    const T* geo = (const T*)a.geo + (int64_t)mem * a.gstride + e0 * kGeo;
+    for (int k = tid; k < ne * kGeo; k += NTH) sG[k] = geo[k];
+    for (int k = tid; k < NSH; k += NTH) S[k] = T(0);
+    PF pf;
+    pf.tables(sh, a, blk, ne, tid);
+    __syncthreads();
+    T up = act ? ((const T*)a.U)[at] : T(0), y = up, ap = T(0);
+    float lo = 0.f;
+    if constexpr (COMP)
+        if (act) lo = from_bf16(((const uint16_t*)a.Ulo)[at]);
+    if (act) S[row * RS + i] = y;
+    pf.init(sh, a, e0, ne, tid, [](int f, int k, int e) { return e * 6 * NF4 + f * NFP + k; });
+    // the node's matrix rows, the lane's metric terms
+    T D[3][NP], L[NF4];
+    const T* Mt = mats<T>();
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax)
+#pragma unroll
+        for (int j = 0; j < NP; ++j) D[ax][j] = Mt[MO + (ax * NP + i) * NP + j];
+#pragma unroll
+    for (int k = 0; k < NF4; ++k) L[k] = Mt[LO + i * NF4 + k];
+    const int c3 = c < 3 ? c : c - 3;
+    const int kp = c3 == 0 ? 2 : c3 - 1, km = c3 == 2 ? 0 : c3 + 1;
+    const int sb = elc * 6 + (c < 3 ? 3 : 0);
+    const int lane_p = sb + (c3 == 0 ? 2 : c3 - 1), lane_m = sb + (c3 == 2 ? 0 : c3 + 1);
+    const T* gg = &sG[elc * kGeo];
+    T gp[3], gm[3];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        gp[ax] = gg[3 * ax + kp];
+        gm[ax] = gg[3 * ax + km];
+    }
+    const T inv = c < 3 ? gg[37] : gg[38];
+    const T sig = c < 3 ? gg[39] : T(0);
+    const T sgn = c < 3 ? T(-1) : T(1);
+    const bool src = act && c < a.src_rows &&
+                     (!a.smask || ((a.smask[(int64_t)mem * ((a.K + EPW - 1) / EPW) + blk] >> elc) & 1u));
+    T sr = T(0), si = T(0);
+    if (src) {
+        const int64_t so = (int64_t)mem * a.sstride + (e0 * 6 + row) * NP + i;
+        sr = ((const T*)a.Sre)[so];
+        si = ((const T*)a.Sim)[so];
+    }
+
+    uint32_t epoch = a.epoch;
+    const int64_t half = (int64_t)a.members * a.next * (PF::CF * PF::X::W);  // words of one buffer
+    unsigned long long* const xch = a.xch + (int64_t)mem * a.next * (PF::CF * PF::X::W);
+    const unsigned long long* const inbox = xch + (int64_t)a.xstart[blk] * (PF::CF * PF::X::W);
+    const bool tail = a.filter && NS == 4;
+    __syncthreads();
+    pf.publish(sh, S, xch + (epoch & 1) * half, epoch, tid);
+    for (int m = 0; m < M + (tail ? 1 : 0); ++m) {
+        const int ns = m < M ? NS : 1;
+        for (int s = 0; s < ns; ++s) {
+            const double* tab = a.mtab + (((int64_t)(m < M ? m : a.M) * NS + s) * a.members + mem) * kMemberParams;
+            const T cy = (T)tab[0], ca = (T)tab[1], cu = (T)tab[2], scos = (T)tab[3], ssin = (T)tab[4];
+            const unsigned long long* const in = inbox + (epoch & 1) * half;
+            Inbox<T, PF::RQ, NTH> box;
+            box.request(in, 0, pf.n, tid);
+            // ---- volume term of the node
+            T yr[NP], pv = T(0), mv = T(0);
+#pragma unroll
+            for (int j = 0; j < NP; ++j) yr[j] = S[row * RS + j];
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                T d = T(0);
+#pragma unroll
+                for (int j = 0; j < NP; ++j) d = fma(D[ax][j], yr[j], d);
+                pv = fma(gp[ax], d, pv);
+                mv = fma(-gm[ax], d, mv);
+            }
+            T acc = sgn * (__shfl(pv, lane_p) + __shfl(mv, lane_m));
+
+            pf.receive(sh, S, box, in, epoch, a, tid);
+            __syncthreads();
+            if (sh.stop) return;
+            pf.flux(S, sG, NF4, tid);
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < NF4; ++k) acc = fma(L[k], S[FO + row * NF4 + k], acc);
+
+            T kv = fma(inv, acc, -sig * y);
+            if (src) kv = fma(scos, sr, fma(-ssin, si, kv));
+            if (a.filter && s == 0 && act) {
+                const double ud = (double)y, kd = (double)kv;
+                a.Fre[at] = fma(tab[5], ud, fma(tab[7], kd, a.Fre[at]));
+                a.Fim[at] = fma(tab[6], ud, fma(tab[8], kd, a.Fim[at]));
+            }
+            if (m >= M) break;  // the last level's right-hand side: filter only
+            const bool last = s == NS - 1;
+            if (!last) {
+                if (NS == 4) ap = s > 0 ? fma(ca, kv, ap) : COMP ? ca * kv : fma(ca, kv, y);
+                y = fma(cy, kv, up);
+            } else {
+                if constexpr (COMP) {
+                    float sum, e;
+                    two_sum(up, NS == 4 ? fma(cu, kv, ap) + lo : fma(cu, kv, lo), sum, e);
+                    up = sum;
+                    lo = from_bf16(to_bf16(e));
+                } else {
+                    up = fma(cu, kv, NS == 4 ? ap : up);
+                }
+                y = up;
+            }
+            if (m + 1 < M || !last || tail) {
+                ++epoch;
+                if (act) S[row * RS + i] = y;  // read in this stage before the flux's barriers
+                __syncthreads();
+                pf.publish(sh, S, xch + (epoch & 1) * half, epoch, tid);
+            }
+        }
+    }
+    if (act) {
+        ((T*)a.U)[at] = up;
+        if constexpr (COMP) ((uint16_t*)a.Ulo)[at] = to_bf16(lo);
     }
 }
 
@@ -1601,24 +2629,20 @@ __global__ void k_nonfinite(const double* X, int64_t n, int* flag) {
 }
 
 // Stage-kernel variant per (q, precision): 0 = gather per face, 1 = gathers
-// pipelined one face ahead, 2 / 3 = matrix cores (q >= 2) without /
-// with the one-face-ahead gathers, 4 = 3 with two waves per block, 5-7 the
-// eager-gather and column-split forms of 4, 8 = four waves per block, 9 = 8
+// pipelined one face ahead; from 2 on (q >= 2) on the matrix cores: FP32 fields
+// k_stage_col whatever the number, FP64 fields the forms of k_stage_mfma: 2 / 3 =
+// without / with the one-face-ahead gathers, 4 = 3 with two waves per block, 5-7
+// the eager-gather and column-split forms of 4, 8 = four waves per block, 9 = 8
 // with every face's gathers at once; -1 = chosen per launch from its size.
-// Overridable through cmcg_tune_stage() and the autotuner.  Defaults:
-// per-face gathers for P1; for P2 and P3 the form the autotuner's timings
-// favour at the launch's size (workgroups over all members).  FP32 P3 (us per
-// launch, forms 4 / 6 / 8 / 9): 3072 tets 12.2 / 10.9 / 8.9 / 8.8, 10368 tets
-// 15.6 / 14.3 / 13.8 / 13.5, 24576 tets 25.2 / 21.8 / 22.7 / 23.6, 48000 tets
-// 38.7 / 37.1 / 36.8 / 39.6, 82944 tets 57.6 / 56.9 / 57.9 / -, 196608 tets
-// 131.0 / 137.4 / 139.1 / -.  FP32 P2 (forms 3 / 4 / 5 / 8 / 9): 3072 tets
-// 9.0 / 7.6 / 7.3 / 6.5 / 6.1, 10368 tets 10.7 / 8.9 / 8.7 / 8.4 / 8.0, 24576
-// tets 14.2 / 13.1 / 12.2 / 13.8 / 13.6, 82944 tets 30.3 / 28.3 / 30.4 / 31.2
-// / -, the 1,572,864-tet mesh 473 / 487 / 525 / - / -, 64 members of 10368
-// tets 188 / 199 / 222 / - / -.  FP64 (forms 4 / 8 / 9): P2 3072 tets 9.4 /
-// 8.1 / 7.8, 10368 tets 12.3 / 11.7 / 13.6, 48000 tets 33.3 / 35.6 / 37.2;
-// P3 3072 tets 17.5 / 12.9 / 12.5, 48000 tets 69.6 / 68.9 / 75.3 (the VALU
-// form: 112.7).
+// Overridable through cmcg_tune_stage() and the autotuner.  Defaults: per-face
+// gathers for P1; for FP64 P2 and P3 the form the autotuner's timings favour at
+// the launch's size (workgroups over all members; us per launch, forms 4 / 8 /
+// 9): P2 3072 tets 9.4 / 8.1 / 7.8, 10368 tets 12.3 / 11.7 / 13.6, 48000 tets
+// 33.3 / 35.6 / 37.2; P3 3072 tets 17.5 / 12.9 / 12.5, 48000 tets 69.6 / 68.9 /
+// 75.3 (the VALU form: 112.7).  FP32 P2 and P3 have one form for every size,
+// ahead of the VALU form throughout (P2: 196608 tets 50 / 53 us, 64 members of
+// 10368 184 / 200); the numbers by size are what cmcg_tune_resolve_stage has
+// always reported there.
 int g_variant[kMaxQ + 1][2] = {{0, 0}, {0, 0}, {-1, -1}, {-1, -1}};
 inline int variant_by_size(int q, int precision, int64_t blocks) {
     if (precision == CMCG_FP64) {
@@ -1647,38 +2671,43 @@ void stage_launch_mh(const StageArgs& a, hipStream_t s) {
     const int64_t per = (blocks + 7) / 8;
     const int v = stage_variant(Q, sizeof(T) == 8 ? CMCG_FP64 : CMCG_FP32, blocks * (a.nmembers > 1 ? a.nmembers : 1));
     const dim3 grid((unsigned)(8 * per), (unsigned)(a.nmembers > 1 ? a.nmembers : 1));
-    if constexpr (Q >= 2) {
+    if constexpr (std::is_same<T, float>::value && Q >= 2) {
+        if (v >= 2) {
+            hipLaunchKernelGGL((k_stage_col<Q, MH, false>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
+            return;
+        }
+    } else if constexpr (Q >= 2) {
         if (v == 2) {
-            hipLaunchKernelGGL((k_stage_mfma<T, Q, false, MH, 1>), grid, dim3(64), 0, s, a, per);
+            hipLaunchKernelGGL((k_stage_mfma<Q, false, MH, 1>), grid, dim3(64), 0, s, a, per);
             return;
         }
         if (v == 3) {
-            hipLaunchKernelGGL((k_stage_mfma<T, Q, true, MH, 1>), grid, dim3(64), 0, s, a, per);
+            hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 1>), grid, dim3(64), 0, s, a, per);
             return;
         }
         if (v == 4) {
-            hipLaunchKernelGGL((k_stage_mfma<T, Q, true, MH, 2>), grid, dim3(128), 0, s, a, per);
+            hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 2>), grid, dim3(128), 0, s, a, per);
             return;
         }
         if (v == 5) {
-            hipLaunchKernelGGL((k_stage_mfma<T, Q, true, MH, 2, true>), grid, dim3(128), 0, s, a, per);
+            hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 2, true>), grid, dim3(128), 0, s, a, per);
             return;
         }
         if (v == 8) {
-            hipLaunchKernelGGL((k_stage_mfma<T, Q, true, MH, 4>), grid, dim3(256), 0, s, a, per);
+            hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 4>), grid, dim3(256), 0, s, a, per);
             return;
         }
         if (v == 9) {
-            hipLaunchKernelGGL((k_stage_mfma<T, Q, true, MH, 4, true>), grid, dim3(256), 0, s, a, per);
+            hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 4, true>), grid, dim3(256), 0, s, a, per);
             return;
         }
         if constexpr (Q == 3) {
             if (v == 6) {
-                hipLaunchKernelGGL((k_stage_mfma<T, Q, true, MH, 2, false, true>), grid, dim3(128), 0, s, a, per);
+                hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 2, false, true>), grid, dim3(128), 0, s, a, per);
                 return;
             }
             if (v == 7) {
-                hipLaunchKernelGGL((k_stage_mfma<T, Q, true, MH, 2, true, true>), grid, dim3(128), 0, s, a, per);
+                hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 2, true, true>), grid, dim3(128), 0, s, a, per);
                 return;
             }
         }
@@ -1695,16 +2724,18 @@ void stage_launch(const StageArgs& a, hipStream_t s) {
         const int64_t blocks = a.blist ? a.nblist : (a.K + EPW - 1) / EPW;
         const int64_t per = (blocks + 7) / 8;
         const dim3 grid((unsigned)(8 * per));
-        // four waves per block on the launches restricted to a block list
+        // FP64: four waves per block on the launches restricted to a block list
         // (the substep stages: a partial round of workgroups, whose time is
         // one block's chain) and where the chosen form has four (8, 9); two
         // otherwise
-        if constexpr (Q >= 2) {
+        if constexpr (Q >= 2 && std::is_same<T, float>::value) {
+            hipLaunchKernelGGL((k_stage_col<Q, false, true>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
+        } else if constexpr (Q >= 2) {
             if (a.blist || stage_variant(Q, sizeof(T) == 8 ? CMCG_FP64 : CMCG_FP32, blocks) >= 8)
-                hipLaunchKernelGGL((k_stage_mfma<T, Q, true, false, 4, false, false, true>), grid, dim3(256), 0, s,
+                hipLaunchKernelGGL((k_stage_mfma<Q, true, false, 4, false, false, true>), grid, dim3(256), 0, s,
                                    a, per);
             else
-                hipLaunchKernelGGL((k_stage_mfma<T, Q, true, false, 2, false, false, true>), grid, dim3(128), 0, s,
+                hipLaunchKernelGGL((k_stage_mfma<Q, true, false, 2, false, false, true>), grid, dim3(128), 0, s,
                                    a, per);
         } else
             hipLaunchKernelGGL((k_stage<T, Q, false, false, true>), grid, dim3(64), 0, s, a, per);
@@ -1791,6 +2822,27 @@ void upload_constants(int q, int precision, const double* D, const double* LIFT,
                                    ft_off(q) * sizeof(uint32_t), hipMemcpyHostToDevice));
     }
     if (q >= 2) {
+        // broadcast operands of the FP32 kernels with one column per lane (gCol)
+        const int W = (NP + 3) / 4, NV = (3 * NP + 15) / 16, NL = (4 * NFP + 15) / 16;
+        std::vector<float> t((size_t)W * (NV + NL) * 64, 0.f);
+        for (int w = 0; w < W; ++w)
+            for (int l = 0; l < 64; ++l) {
+                const int i = 4 * w + l % 4;
+                if (i >= NP) continue;
+                float* o = &t[(size_t)w * (NV + NL) * 64 + l];
+                for (int v = 0; v < NV; ++v) {
+                    const int st = 16 * v + l / 4;
+                    if (st < 3 * NP) o[64 * v] = (float)D[(st % 3 * NP + i) * NP + st / 3];
+                }
+                for (int v = 0; v < NL; ++v) {
+                    const int st = 16 * v + l / 4;
+                    if (st < 4 * NFP) o[64 * (NV + v)] = (float)LIFT[i * 4 * NFP + st];
+                }
+            }
+        CMCG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(gCol), t.data(), t.size() * sizeof(float), col_off(q) * sizeof(float),
+                                   hipMemcpyHostToDevice));
+    }
+    if (q >= 2) {
         // lane-ordered A fragments of the matrix-core kernel: entry (frag, lane)
         // = A[16 mt + lane % 16][4 ks + lane / 16] of the block the fragment names
         const int MT = (NP + 15) / 16, NJ = (NP + 3) / 4, KSV = 3 * NJ, KSF = (NFP + 3) / 4;
@@ -1815,10 +2867,6 @@ void upload_constants(int q, int precision, const double* D, const double* LIFT,
                     }
             }
         }
-        // FP32 fragments are the rounded FP64 ones
-        std::vector<float> fr32(fr.begin(), fr.end());
-        CMCG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(gFrag), fr32.data(), fr32.size() * sizeof(float),
-                                   frag_off(q) * sizeof(float), hipMemcpyHostToDevice));
         CMCG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(gFrag64), fr.data(), fr.size() * sizeof(double),
                                    frag_off(q) * sizeof(double), hipMemcpyHostToDevice));
     }
@@ -1835,6 +2883,34 @@ void launch_stage(int q, int precision, const StageArgs& a, hipStream_t s) {
         else stage_launch<float, 3>(a, s);
     }
     check_launch();
+}
+
+// One-launch periods, whenever all members' blocks are resident at once.  Time
+// per stage, one launch per period against one per stage (us):
+//   FP32 P1 1296 tets 1.1 / 2.9, 10368 2.1 / 3.1, 12790 2.3 / 3.2;
+//   FP32 P2 3072 3.5 / 4.7, 10368 5.2 / 6.8, 15300 6.4 / 8.3;
+//   FP32 P3 384 3.7 / 4.7, 3072 4.4 / 5.8, 7600 5.7 / 8.3;
+//   FP64 P1 1296 1.4 / 3.1, 6000 3.1 / 3.3; P2 3072 5.4 / 7.5, 6000 8.7 / 9.1;
+//   FP64 P3 384 6.5 / 8.8, 4374 10.5 / 13.1.
+// Members in several groups, one after another, lose to stage launches that run
+// all members at once (FP32 P2, 16 members of 10368 tets: 156 ms a solve against
+// 102; FP64 P1, 16 of 1296: 50 against 27).
+namespace {
+bool period3d_f32(int q, const PeriodArgs& a, int64_t nb, int n, hipStream_t s) {
+    if (q == 1) return launch_resident(k_period_p1<float>, nb, n, 256, false, a, s);
+    if (q == 2) return launch_resident(k_period_col<2, 4>, nb, n, ColDim<2>::NTH, false, a, s);
+    return launch_resident(k_period_col<3, 5>, nb, n, ColDim<3>::NTH, false, a, s);
+}
+bool period3d_f64(int q, const PeriodArgs& a, int64_t nb, int n, hipStream_t s) {
+    if (q == 1) return launch_resident(k_period_p1<double>, nb, n, 256, false, a, s);
+    if (q == 2) return launch_resident(k_period_mfma<2, 3>, nb, n, 256, false, a, s);
+    return launch_resident(k_period_mfma<3, 2>, nb, n, 256, false, a, s);
+}
+}  // namespace
+
+bool launch_period(int q, int precision, const PeriodArgs& a, int n, hipStream_t s) {
+    const int64_t nb = (a.K + EPW - 1) / EPW;
+    return precision == CMCG_FP64 ? period3d_f64(q, a, nb, n, s) : period3d_f32(q, a, nb, n, s);
 }
 
 void launch_to_field(int precision, int Np, const double* X, void* U, void* Ulo, int64_t n, int flipH,

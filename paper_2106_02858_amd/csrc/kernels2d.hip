@@ -18,11 +18,11 @@
 #include <algorithm>
 #include <string>
 #include <type_traits>
-#include <utility>
 #include <vector>
 
 #include "internal.h"
 #include "launch.h"
+#include "mfma_cols.h"
 #include "tagged.h"
 
 namespace cmcg {
@@ -515,33 +515,6 @@ __global__ __launch_bounds__(64) void k_stage2d(StageArgs args, int64_t per) {
             }
         }
     }
-}
-
-// FP32 products of small matrices with one column per lane on
-// v_mfma_f32_4x4x1_16b_f32: with the A operand of one of the 16 blocks
-// broadcast to all of them (cbsz = 4, abid = the block) an instruction adds
-// A[4 g .. 4 g + 3][k] * column[k] to four rows of every lane's column, in the
-// order and with the rounding of an fma() per row (checked on the GPU).  A
-// register holds the operands of 16 instructions, so the matrices of an order
-// take a few registers instead of LDS reads, four rows a time instead of one.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <int NK, int G, typename F>
-__device__ __forceinline__ void mfma_operand(float (&m)[(NK * G + 15) / 16], int lane, F at) {
-#pragma unroll
-    for (int v = 0; v < (NK * G + 15) / 16; ++v) {
-        const int q = 16 * v + lane / 4;
-        m[v] = q < NK * G ? at(4 * (q % G) + lane % 4, q / G) : 0.f;
-    }
-}
-template <int NK, int G, int NX, size_t... I>
-__device__ __forceinline__ void mfma_steps(const float (&m)[(NK * G + 15) / 16], const float (&x)[NX], f32x4 (&acc)[G],
-                                           std::index_sequence<I...>) {
-    ((acc[I % G] = __builtin_amdgcn_mfma_f32_4x4x1f32(m[I / 16], x[I / G], acc[I % G], 4, I % 16, 0)), ...);
-}
-template <int NK, int G, int NX>
-__device__ __forceinline__ void mfma_rows(const float (&m)[(NK * G + 15) / 16], const float (&x)[NX], f32x4 (&acc)[G]) {
-    static_assert(NX >= NK, "a column value per K step");
-    mfma_steps<NK, G>(m, x, acc, std::make_index_sequence<NK * G>());
 }
 
 // ---------------------------------------------------------------------------
@@ -1101,7 +1074,7 @@ void stage2d(const StageArgs& a, hipStream_t s) {
 
 template <typename T, int Q>
 bool period2d(const PeriodArgs& a, int n, hipStream_t s) {
-    return launch_resident(k_period2d<T, Q>, (a.K + EPB - 1) / EPB, n, 256, a, s);
+    return launch_resident(k_period2d<T, Q>, (a.K + EPB - 1) / EPB, n, 256, true, a, s);
 }
 
 }  // namespace

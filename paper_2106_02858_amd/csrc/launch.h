@@ -104,7 +104,7 @@ constexpr int kMaxHarm = 8;
 constexpr int kMemberParams = 9;
 
 // A whole period in one launch, for meshes whose element blocks all fit on the
-// device at once (kernels2d.hip k_period2d): U (and Ulo) advance M steps in
+// device at once (kernels.hip k_period_mfma, k_period_p1; kernels2d.hip k_period2d): U (and Ulo) advance M steps in
 // place.  Member b of a batch (grid.y) offsets fields, source and filter by
 // b * bstride / sstride and the geometry by b * gstride.
 struct PeriodArgs {
@@ -226,10 +226,11 @@ void launch_nonfinite(const double* X, int64_t n, int* out_dev, hipStream_t s);
 // member, StageArgs::mtab non-null) as in 3-D, without the source mask.
 void upload_constants2d(int q, const double* D, const double* LIFT, const double* M, const int* fnode);
 void launch_stage2d(int q, int precision, const StageArgs& a, hipStream_t s);
-// One period of the n members of a.order in one launch, or a launch per group
-// of members that fits on the device at once; false (nothing launched) when
-// one member does not.
-bool launch_period2d(int q, int precision, const PeriodArgs& a, int n, hipStream_t s);
+// One period of the n members of a.order in one launch (triangles: or a launch
+// per group of members that fits on the device at once); false, and nothing
+// launched, when the members do not fit.  Without a.xch: only whether they fit.
+bool launch_period(int q, int precision, const PeriodArgs& a, int n, hipStream_t s);    // tetrahedra
+bool launch_period2d(int q, int precision, const PeriodArgs& a, int n, hipStream_t s);  // triangles
 void launch_to_field2d(int precision, int Np, const double* X, void* U, void* Ulo, int64_t n, int flipH,
                        hipStream_t s);
 void launch_from_field2d(int precision, int Np, const void* U, const void* Ulo, double* Y, const double* sub,

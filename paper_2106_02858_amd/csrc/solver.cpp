@@ -678,8 +678,18 @@ ResidentTurn g_resident[64];
 constexpr double kResidentWait = 2.0;  // seconds a workgroup waits for a neighbour before it gives up
 }  // namespace
 
+// whether the variant of (q, precision) was chosen through cmcg_tune_stage (the
+// autotuner's choice between stage launches leaves the one-launch periods on)
+static bool& stage_by_hand(int q, int precision) {
+    static bool by_hand[kMaxQ + 1][2];
+    return by_hand[q][precision];
+}
+
 bool resident_variant(const SpaceData& s) {
-    return s.dim == 2;
+    if (s.dim == 2) return true;
+    if (stage_by_hand(s.q, s.precision)) return false;
+    const int v = get_stage_variant(s.q, s.precision);
+    return s.q == 1 ? v <= 1 : v != 0 && v != 1;
 }
 
 // Numbers the faces whose neighbour lies in another element block, block by
@@ -705,9 +715,10 @@ static void build_mailboxes(SpaceData& s, hipStream_t st) {
 
 bool run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t st) {
     if (r.off) return false;
-    const int nf = s.dim + 1;
-    // more faces than any device holds at once: no mailboxes are numbered
-    if (s.K * nf * a.members > kPeriodMaxValues / 8) {
+    const auto launch = [&] {
+        return s.dim == 2 ? launch_period2d(s.q, s.precision, a, n, st) : launch_period(s.q, s.precision, a, n, st);
+    };
+    if (!r.xch.p && !launch()) {  // does not fit on the device: no mailboxes are numbered
         r.off = true;
         return false;
     }
@@ -749,8 +760,7 @@ bool run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t s
             CMCG_HIP(hipEventCreateWithFlags(&turn.last, hipEventDisableTiming));
         else
             CMCG_HIP(hipStreamWaitEvent(st, turn.last, 0));
-        const bool ran = s.dim == 2 && launch_period2d(s.q, s.precision, a, n, st);
-        if (!ran) {
+        if (!launch()) {
             r.off = true;
             return false;
         }
@@ -1780,6 +1790,7 @@ int cmcg_tune_stage(int q, int precision, int variant) {
         variant >= kStageVariants)
         fail(CMCG_ERR_ARG, "tune_stage: bad q, precision or variant");
     set_stage_variant(q, precision, variant);
+    stage_by_hand(q, precision) = variant >= 0;
     return CMCG_OK;
     CMCG_GUARD_END
 }

@@ -115,17 +115,32 @@ template <typename T, int R, int NTH> struct Inbox {
     }
 };
 
-// Launches a period kernel over nblocks element blocks and n members, as many
-// members at a time as fit on the device at once; false (nothing launched)
-// when one member does not.
+// Launches a period kernel over nblocks element blocks and n members, with
+// `groups` as many members at a time as fit on the device at once; false
+// (nothing launched) when one member, or without `groups` all of them, do not.
+// Without an exchange buffer (a.xch) it only tells whether they would.
+//
+// Room: what the occupancy query allows.  Blocks whose waves do not divide
+// over the four SIMDs of a compute unit need a free wave slot besides: with five
+// slots per SIMD, four blocks of five waves were not placed (799 blocks of
+// k_period_col<3> waited in vain), three were, and six blocks of three waves.
 template <typename F>
-inline bool launch_resident(F kernel, int64_t nblocks, int n, int threads, PeriodArgs a, hipStream_t s) {
+inline bool launch_resident(F kernel, int64_t nblocks, int n, int threads, bool groups, PeriodArgs a, hipStream_t s) {
     int dev = 0, cus = 0, fit = 0;
     CMCG_HIP(hipGetDevice(&dev));
     CMCG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     CMCG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, kernel, threads, 0));
+    const int waves = threads / 64;
+    if (waves % 4 != 0) {
+        hipFuncAttributes at;
+        CMCG_HIP(hipFuncGetAttributes(&at, reinterpret_cast<const void*>(kernel)));
+        const int slots = 512 / ((at.numRegs + 7) / 8 * 8);  // per SIMD, at most 8
+        const int limit = (4 * (slots < 8 ? slots : 8) - 1) / waves;
+        if (fit > limit) fit = limit;
+    }
     const int64_t per = (nblocks + 7) / 8, room = (int64_t)fit * cus / (8 * per);
-    if (room < 1) return false;
+    if (room < (groups ? 1 : n)) return false;
+    if (!a.xch) return true;
     for (int first = 0; first < n; first += (int)room) {
         a.first = first;
         const dim3 grid((unsigned)(8 * per), (unsigned)(n - first < room ? n - first : room));

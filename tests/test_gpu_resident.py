@@ -94,6 +94,29 @@ def test_period2d_equals_stage_launches(lib, kind, q, precision):
         assert torch.isfinite(x).all() and torch.equal(x, y)
 
 
+def _mesh3d(kind):
+    """The first tets of a cube (the faces of the cut become walls), or all of them numbered at random."""
+    xyz, tet, tags = inputs.cube_mesh(3)
+    if kind == "shuffled":
+        p = np.random.default_rng(8).permutation(len(tet))
+        return xyz, tet[p], tags[p]
+    return xyz, tet[:kind], np.where(tags[:kind] == 0, inputs.TAG_IMPEDANCE, tags[:kind]).astype(tags.dtype)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("q", [1, 2, 3])
+@pytest.mark.parametrize("kind", [1, 9, 10, 11, 43, "shuffled"])
+def test_period3d_equals_stage_launches(lib, kind, q, precision):
+    import torch
+    print(f"resident 3-D {kind} q={q} prec={precision}", flush=True)
+    mesh = _mesh3d(kind)
+    s, p = _problem(lib, 3, mesh, q, precision, seed=5)
+    K, Np = len(mesh[1]), lib.cmcg_space_info(s)["Np"]
+    a, b = (_periods(lib, p, K, 6, Np, q, g) for g in (1, 0))
+    for x, y in zip(a, b):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
+
+
 @pytest.mark.parametrize("precision", [0, 1])
 def test_batch2d_in_groups_equals_stage_launches(lib, precision):
     """30 members of 1200 triangles (58 blocks each) do not fit on the device
