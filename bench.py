@@ -89,20 +89,17 @@ def parse():
 # FETCH_SIZE / WRITE_SIZE per dispatch (KiB) of the stage kernel on the
 # 48000-tet P3 FP32 problem, with the scales a 1 GiB copy gives each counter;
 # valid only for the kernel source they were taken on (SHA-256 below).
-_SHA_3D = "81523165ddc92a8d82c4cb960db3867453aea65aa336fe1e269871073474a489"
+_SHA_3D = "f297220647e19204de9f7b513cd78d352bb226789bfe57d8b3b9c4215f78b2e1"
 MEASURED_TRAFFIC = [
     {"kernels_sha256": _SHA_3D, "kernel": "k_stage_col<3,false,false>", "K": 48000,
-     "fetch_kib": 40871.78, "fetch_scale": 2.0000, "write_kib": 42187.53, "write_scale": 1.0000},
+     "fetch_kib": 40864.70, "fetch_scale": 2.0000, "write_kib": 42187.52, "write_scale": 1.0000},
 ]
 
 
-# The same for the FP64 stage kernel of the plain FP64 solve (48000 tets, P3):
-# the two forms its autotuner keeps (two and four waves per block).
+# The same for the FP64 stage kernel of the plain FP64 solve (48000 tets, P3).
 MEASURED_TRAFFIC_FP64 = [
-    {"kernels_sha256": _SHA_3D, "kernel": k, "K": 48000,
-     "fetch_kib": fe, "fetch_scale": 2.0000, "write_kib": wr, "write_scale": 1.0000}
-    for k, fe, wr in (("k_stage_mfma<3,true,false,2>", 80891.66, 78750.00),
-                      ("k_stage_mfma<3,true,false,4>", 75507.63, 78750.00))
+    {"kernels_sha256": _SHA_3D, "kernel": "k_stage_tile<3,false,false>", "K": 48000,
+     "fetch_kib": 72841.10, "fetch_scale": 2.0000, "write_kib": 78750.00, "write_scale": 1.0000},
 ]
 
 
@@ -113,10 +110,10 @@ MEASURED_TRAFFIC_FP64 = [
 MEASURED_TRAFFIC_Q2 = [
     {"kernels_sha256": _SHA_3D, "kernel": k, "K": K,
      "fetch_kib": fe, "fetch_scale": 2.0000, "write_kib": wr, "write_scale": 1.0000}
-    for k, K, fe, wr in (("k_stage_col<2,false,false>", 1572864, 772943.21, 691300.82),
-                         ("k_stage_col<2,false,false>", 64 * 10368, 245625.16, 291610.99),
-                         ("k_stage<float,2,false,false>", 64 * 10368, 284170.39, 292219.03),
-                         ("k_stage<float,2,true,false>", 64 * 10368, 252674.47, 291668.46))
+    for k, K, fe, wr in (("k_stage_col<2,false,false>", 1572864, 772953.35, 691298.41),
+                         ("k_stage_col<2,false,false>", 64 * 10368, 245614.58, 291610.84),
+                         ("k_stage<float,2,false,false>", 64 * 10368, 284488.97, 292230.44),
+                         ("k_stage<float,2,true,false>", 64 * 10368, 252803.37, 291671.47))
 ]
 
 
@@ -151,10 +148,7 @@ def measured_traffic(kernel: str, K: int, table=None, source: str = "kernels.hip
 STAGE_KERNEL = {0: "k_stage<float,{q},false,false>", 1: "k_stage<float,{q},true,false>",
                 **dict.fromkeys(range(2, 10), "k_stage_col<{q},false,false>")}
 STAGE_KERNEL64 = {0: "k_stage<double,{q},false,false>", 1: "k_stage<double,{q},true,false>",
-                  2: "k_stage_mfma<{q},false,false,1>", 3: "k_stage_mfma<{q},true,false,1>",
-                  4: "k_stage_mfma<{q},true,false,2>", 5: "k_stage_mfma<{q},true,false,2,true>",
-                  6: "k_stage_mfma<{q},true,false,2,false,true>", 7: "k_stage_mfma<{q},true,false,2,true,true>",
-                  8: "k_stage_mfma<{q},true,false,4>", 9: "k_stage_mfma<{q},true,false,4,true>"}
+                  **dict.fromkeys(range(2, 10), "k_stage_tile<{q},false,false>")}
 
 
 def stage_bytes_per_element(q: int, esize: int) -> float:

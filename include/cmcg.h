@@ -476,24 +476,13 @@ int cmcg_engine_collect_batch(cmcg_engine* e, int slot, cmcg_result** results, i
 /* Stage-kernel implementation variant for (q, precision): 0 gathers each
  * face's neighbour traces when it is processed, 1 requests them one face
  * ahead (more registers, more latency hiding), 2 and up run the volume and
- * lift products on the matrix cores (q = 2, 3; q = 1 falls back to 0).  FP32
- * fields have one such kernel (v_mfma_f32_4x4x1, a wave per four nodes of the
- * 10-element block), run by 2..9 alike.  FP64 fields (v_mfma_f64_16x16x4f64)
- * have several: 2 has one wave per block, 3 is 2 with the neighbour traces
- * requested one face ahead, 4 is 3 with two waves per 10-element block, each
- * computing half of the output tiles, 5 is 4 with the neighbour traces of all
- * four faces requested at once and two alternating flux tiles, 6 is 4 with the
- * two waves splitting the output by column tiles instead of row tiles (q = 3),
- * 7 combines 5 and 6 (q = 3), 8 is 3 with four waves per block, each computing
- * one row tile and half of the column tiles (q = 3) or a quarter of them (q =
- * 2), 9 is 8 with the neighbour traces of all four faces requested at once
- * (more registers per wave: for launches of a round of workgroups or less);
- * variants that do not exist for
+ * lift products on the matrix cores (q = 2, 3): one kernel for FP32 fields
+ * (v_mfma_f32_4x4x1, a wave per four nodes of a 10-element block) and one for
+ * FP64 fields (v_mfma_f64_16x16x4, a wave per 16 columns), run by 2..5, 8 and 9
+ * and for q = 3 by 6 and 7 alike; variants that do not exist for
  * (q, precision) fall back to 0; -1 chooses per launch from its size
  * (workgroups of 10 elements over all members), the form the autotuner's
  * timings favour there.  All compute the same Phi(t, Y) and stage update.
- * Local time stepping's FP64 substep launches (restricted to the element
- * blocks near the fine region) take the four-wave form whatever the choice.
  * A whole period may also run as one launch with the stage kernels' arithmetic
  * (use_graph, meshes whose element blocks fit on the device at once) unless a
  * variant was set here.

@@ -711,35 +711,6 @@ __global__ __launch_bounds__(64) void k_stage(StageArgs args, int64_t per) {
 }
 
 // ---------------------------------------------------------------------------
-// FP64 stage kernel on the matrix cores (q = 2, 3).
-//
-// Per 64-lane workgroup (10 elements, columns n = element * 6 + s):
-//   volume:  C[i][n] = sum_{a,j} D_a[i][j] W_a[j][n],  W_a = sgn (grad xi_a x V)_m,
-//            V = H for s < 3 (E rows, sgn = -1), V = E for s >= 3 (sgn = +1),
-//            m = s mod 3 -- i.e. curl V = sum_a D_a (grad xi_a x V) for an affine
-//            element, so the product already is the curl column;
-//   lift:    C[i][n] += sum_{f,k} LIFT[i][f Nfp + k] flux_f[k][n], face by face;
-// with v_mfma_f64_16x16x4f64: A = the reference matrices, held as register
-// fragments (lane l holds A[l % 16][l / 16] of each 16x4 block, read once from a
-// lane-ordered table), B = W or flux values from LDS, D rows per Mfma<T>::row.
-// The volume's K steps are axis-major: step ks covers axis a = ks / NJ and
-// nodes j = 4 (ks % NJ) + (0..3), so a lane meets the same nodes j = l/16 + 4 t
-// on every axis and reads them once.  Rows i >= Np and nodes j >= Np carry
-// zero A fragments.
-template <int Q> struct MfmaDim {
-    static constexpr int NP = Dim<Q>::NP, NFP = Dim<Q>::NFP;
-    static constexpr int MT = (NP + 15) / 16;        // 16-row output tiles
-    static constexpr int NJ = (NP + 3) / 4;          // K steps per axis of the volume product
-    static constexpr int KSV = 3 * NJ;               // K steps of the volume product
-    static constexpr int KSF = (NFP + 3) / 4;        // K steps per face of the lift
-    static constexpr int NFRAG = MT * KSV + 4 * MT * KSF;
-};
-__host__ __device__ constexpr int frag_off(int q) {
-    return q <= 2 ? 0 : frag_off(q - 1) + 64 * MfmaDim<2>::NFRAG;
-}
-constexpr int kFragTotal = 64 * (MfmaDim<2>::NFRAG + MfmaDim<3>::NFRAG);
-__device__ double gFrag64[kFragTotal];
-
 // One 16x16x4 matrix-core product D = A B + C in the field precision:
 // v_mfma_f32_16x16x4f32 or v_mfma_f64_16x16x4f64.  Both take A[l % 16][l / 16]
 // and B[l / 16][l % 16] from lane l; their accumulators differ: register r of
@@ -760,20 +731,6 @@ template <> struct Mfma<double> {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
     static __device__ __forceinline__ int row(int q4, int r) { return 4 * r + q4; }
-};
-
-template <int Q, int NB = 1>
-struct MfmaShared {
-    using T = double;
-    static constexpr int NP = Dim<Q>::NP, NFP = Dim<Q>::NFP;
-    static constexpr int RS = NP + 1;
-    static constexpr int KF = 4 * MfmaDim<Q>::KSF;
-    static constexpr int FS = 65;  // flux tile row stride: the face nodes of one column fall in different banks
-    T sY[EPW * 6 * RS];       // stage input, rows (element, component) padded to NP + 1
-    T sF[NB * KF * FS];       // NB flux tiles [face node][column], rows >= NFP stay zero
-    T sG[EPW * kGeo];         // geometry of the chunk
-    int sC[EPW * 4];          // connectivity codes of the chunk
-    uint8_t sT[4 * ft_words(Q)];  // own face nodes [f][k], then neighbour face nodes [nf][perm][k]
 };
 
 // Operands of the coalesced update pass (16-byte groups v = lane + NTH t of
@@ -1052,254 +1009,340 @@ __device__ __forceinline__ void stage_update(const StageArgs& args, const StageA
     }
 }
 
-// PIPE: the next face's neighbour traces are requested before this face's
-// flux (more registers, the gather latency hides behind the lift).
-// W: waves per workgroup.  W = 2 gives each wave half the output tiles: P3
-// one of its two 16-row tiles (both waves build the same B operands), P2 two
-// of the four 16-column tiles (each wave builds only its own); each runs half
-// the MFMAs, the flux items and the update pass are shared by 128 threads.  A
-// block's dependent chain gets shorter, which pays where the launch ends in a
-// partial round of workgroups.
-// EAGER: the neighbour traces of all four faces are requested right after
-// the staging (four faces' loads in flight during the volume product instead
-// of one), and faces alternate between two flux tiles, so a face needs one
-// barrier instead of two.  CSPLIT (P3, two waves): the waves split the output
-// by column tiles, each building only its own B operands and running both
-// row tiles.  W = 4: each wave one row tile and two column tiles (P3) or one
-// column tile (P2), a quarter of the MFMAs and fewer registers per wave.
-template <int Q, bool PIPE, bool MH, int W, bool EAGER = false, bool CSPLIT = false, bool LTSM = false>
-__global__ __launch_bounds__(64 * W)
-__attribute__((amdgpu_waves_per_eu(W == 4 ? (EAGER ? 2 : 4) : W == 1 || EAGER || CSPLIT ? 2 : 3, 8)))
-void k_stage_mfma(StageArgs args, int64_t per) {
-    using T = double;
-    using MD = MfmaDim<Q>;
-    using acc_t = typename Mfma<T>::acc_t;
-    constexpr int NP = MD::NP, NFP = MD::NFP, MT = MD::MT, KSV = MD::KSV, KSF = MD::KSF;
-    constexpr int RS = NP + 1;
-    constexpr int KF = 4 * KSF;
-    constexpr int NTH = 64 * W;                      // threads of the workgroup
-    constexpr int RF = (EPW * NFP + NTH - 1) / NTH;  // flux items per thread and face
-    // two waves split the output tiles: by rows when there are two row tiles
-    // (P3, unless CSPLIT), by the four 16-column tiles otherwise; four waves
-    // split by rows (P3) and by columns
-    static_assert(W == 1 || W == 2 || W == 4, "one, two or four waves per block");
-    constexpr bool ROWS = (W == 2 && MT == 2 && !CSPLIT) || (W == 4 && MT == 2);
-    constexpr bool COLS = (W == 2 && (MT == 1 || CSPLIT)) || W == 4;
-    constexpr int NB = EAGER ? 2 : 1;  // flux tiles
-    using Sh = MfmaShared<Q, NB>;
-    constexpr int MW = ROWS ? 1 : MT;  // output row tiles of one wave
-    constexpr int CWAVES = COLS ? (ROWS ? W / 2 : W) : 1;  // waves across the column tiles
-    constexpr int NW = 4 / CWAVES;                          // output column tiles of one wave
-    static_assert(W == 1 || ((ROWS || COLS) && RF == 1), "several waves per block need one flux item per thread");
-    __shared__ Sh sh;
+// ---------------------------------------------------------------------------
+// FP64 stage kernel on the matrix cores (q = 2, 3).
+//
+// Columns n = element * 6 + s of a block of 10 elements; wave w of four owns the
+// column tile 16 w .. 16 w + 15 and all its rows:
+//   volume:  C[i][n] = sum_{a,j} D_a[i][j] W_a[j][n],  W_a = sgn (grad xi_a x V)_m,
+//            V = H for s < 3 (E rows, sgn = -1), V = E for s >= 3 (sgn = +1),
+//            m = s mod 3 -- i.e. curl V = sum_a D_a (grad xi_a x V) for an affine
+//            element, so the product already is the curl column;
+//   lift:    C[i][n] += sum_{f,k} LIFT[i][f Nfp + k] flux[f][k][n], all faces.
+// Rows 0 .. 15 run on v_mfma_f64_16x16x4, P3's rows 16 .. 19 on
+// v_mfma_f64_4x4x4_4b, whose four blocks are the tile's four groups of four
+// columns: both take B[l / 16][l % 16] from lane l, so an operand is built once
+// and no row of P3 is padded (a second 16-row tile would spend 12 of its 16 rows
+// on padding: 216 products of 64 cycles a block against 100 of 64 and 100 of
+// about 19).  Register r of lane l holds row 4 r + l / 16 of column l % 16, the
+// 4x4x4 result row 16 + l / 16 (measured with one-hot operands).  The volume's
+// K steps are axis-major (step ks: axis ks / NJ, nodes 4 (ks % NJ) + 0..3), so
+// a lane reads the same nodes once for all axes; the lift's 4 Nfp flux rows
+// are Nfp steps without padding.  Three barriers: the neighbour traces of all
+// faces are requested ahead of the volume product, their fluxes formed at once.
+//
+// P2 takes its operands from registers (15 loads per wave).  P3's 25 steps need
+// 100 registers and 50 loads per wave, which alone cost 10 us of a 60 us
+// 48000-tet launch; a workgroup therefore keeps the table in LDS (16 KB; three
+// workgroups per compute unit as the registers allow) and runs several blocks.
+// Requesting the next block ahead gained nothing (50.9 against 50.1 us).  P3
+// requests the update's operands ahead of the flux (60 us against 69 behind it).
+//
+// us per launch, before (the best of eight forms with one to four waves, a
+// barrier pair per face and P3's rows padded to 32) and now: P2 3072 tets 7.9 /
+// 6.0, 10368 11.9 / 9.6, 24576 20.5 / 15.3, 82944 49.4 / 38.5; P3 3072 12.5 / 9.2,
+// 10368 23.0 / 17.3, 48000 67.1 / 50.5, 82944 118.5 / 95.  What bounds it: the
+// larger launches move 3.9-4.6 TB/s of traffic (a copy: 5.1), the small ones are
+// one block's chain (7 us for P3, of which the products are 0.9).
+template <int Q> struct TileDim {
+    static constexpr int NP = Dim<Q>::NP, NFP = Dim<Q>::NFP;
+    static constexpr int NJ = (NP + 3) / 4, KSV = 3 * NJ, NST = KSV + NFP;  // K steps: per axis, volume, all
+    static constexpr bool TAIL = NP > 16;                                   // rows 16 .. 19
+    static constexpr int RS = NP + 1;                                       // staged row stride
+    static constexpr int FS = 65;  // flux row stride: the face nodes of one column fall in different banks
+    static constexpr int RF = (EPW * 4 * NFP + 255) / 256;                  // flux nodes per thread
+    static constexpr int NTAB = NST * (TAIL ? 80 : 64);
+    static constexpr bool LOOP = Q == 3;  // a workgroup runs several blocks
+};
+// A operands [step][lane] of rows 0 .. 15 (lane l: row l % 16, K row l / 16),
+// behind them [step][16] of rows 16 .. 19 (entry 4 k + i).
+__device__ double gTile[TileDim<2>::NTAB + TileDim<3>::NTAB];
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+template <int Q, int FIRST, int N> struct TileMats {  // steps FIRST .. FIRST + N - 1 in registers
+    using TD = TileDim<Q>;
+    double m[N], x[TD::TAIL ? N : 1];
+    __device__ __forceinline__ void load(int lane) {
+        const double* t = gTile + (Q == 2 ? 0 : TileDim<2>::NTAB);
+#pragma unroll
+        for (int i = 0; i < N; ++i) m[i] = t[(FIRST + i) * 64 + lane];
+        if constexpr (TD::TAIL) {
+            const double* u = t + TD::NST * 64 + (lane >> 4) * 4 + (lane & 3);
+#pragma unroll
+            for (int i = 0; i < N; ++i) x[i] = u[(FIRST + i) * 16];
+        }
+    }
+    __device__ __forceinline__ double rows(int i) const { return m[i]; }
+    __device__ __forceinline__ double tail(int i) const { return x[i]; }
+};
+template <int Q> using TileVolume = TileMats<Q, 0, TileDim<Q>::KSV>;
+template <int Q> using TileLift = TileMats<Q, TileDim<Q>::KSV, TileDim<Q>::NFP>;
+template <int Q, int FIRST> struct TileTable {  // the same from a copy of the table in LDS
+    const double *m, *x;
+    __device__ __forceinline__ TileTable(const double* t, int lane)
+        : m(t + FIRST * 64 + lane), x(t + TileDim<Q>::NST * 64 + FIRST * 16 + (lane >> 4) * 4 + (lane & 3)) {}
+    __device__ __forceinline__ double rows(int i) const { return m[i * 64]; }
+    __device__ __forceinline__ double tail(int i) const { return x[i * 16]; }
+};
+
+template <int Q> struct TileAcc {
+    f64x4 a = {0., 0., 0., 0.};
+    double x = 0.;
+    template <typename M> __device__ __forceinline__ void step(const M& mat, int i, double b) {
+        a = __builtin_amdgcn_mfma_f64_16x16x4f64(mat.rows(i), b, a, 0, 0, 0);
+        if constexpr (TileDim<Q>::TAIL) x = __builtin_amdgcn_mfma_f64_4x4x4f64(mat.tail(i), b, x, 0, 0, 0);
+    }
+    // rows of the lane's column: f(row, value)
+    template <typename F> __device__ __forceinline__ void rows(int q4, F f) const {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (4 * r + q4 < TileDim<Q>::NP) f(4 * r + q4, a[r]);
+        if constexpr (TileDim<Q>::TAIL) f(16 + q4, x);
+    }
+};
+
+// curl at all nodes of the lane's column n from the staged rows: B[(a, j)][n] =
+// sgn (g_a[m1] V_m2(j) - g_a[m2] V_m1(j)); padded columns take element 0 (their
+// results are never stored)
+template <int Q, typename M>
+__device__ __forceinline__ void tile_volume(const double* S, const double* sG, int n, int q4, int ne, const M& mat,
+                                            TileAcc<Q>& acc) {
+    using TD = TileDim<Q>;
+    constexpr int NJ = TD::NJ, NP = TD::NP;
+    const int e = n < 6 * ne ? n / 6 : 0;
+    const int s = n - 6 * (n / 6);
+    const int m = s < 3 ? s : s - 3;
+    const int m1 = m == 2 ? 0 : m + 1, m2 = m == 0 ? 2 : m - 1;  // (m+1)%3, (m+2)%3
+    const int vb = e * 6 + (s < 3 ? 3 : 0);
+    const double sgn = s < 3 ? -1. : 1.;
+    const double* gE = sG + e * kGeo;
+    double g1[3], g2[3], r1[NJ], r2[NJ];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        g1[ax] = sgn * gE[3 * ax + m1];
+        g2[ax] = sgn * gE[3 * ax + m2];
+    }
+    const double* v1 = S + (vb + m1) * TD::RS;
+    const double* v2 = S + (vb + m2) * TD::RS;
+#pragma unroll
+    for (int t = 0; t < NJ; ++t) {
+        const int j = q4 + 4 * t;
+        const bool in = NP % 4 == 0 || j < NP;  // j >= Np: zero operands
+        r1[t] = in ? v1[in ? j : 0] : 0.;
+        r2[t] = in ? v2[in ? j : 0] : 0.;
+    }
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax)
+#pragma unroll
+        for (int t = 0; t < NJ; ++t) acc.step(mat, ax * NJ + t, fma(g1[ax], r2[t], -g2[ax] * r1[t]));
+}
+
+// + LIFT (the column's fluxes); F = the flux tile [f Nfp + k][FS]
+template <int Q, typename M>
+__device__ __forceinline__ void tile_lift(const double* F, int n, int q4, const M& mat, TileAcc<Q>& acc) {
+#pragma unroll
+    for (int i = 0; i < TileDim<Q>::NFP; ++i) acc.step(mat, i, F[(4 * i + q4) * TileDim<Q>::FS + n]);
+}
+
+template <int Q> struct TileShared {
+    using TD = TileDim<Q>;
+    double sY[EPW * 6 * TD::RS];
+    double sF[4 * TD::NFP * TD::FS];
+    double sG[EPW * kGeo];
+    double sM[TD::LOOP ? TD::NTAB : 1];
+    uint8_t sT[4 * ft_words(Q)];
+};
+
+// The thread's share of a block: stage input, geometry and connectivity.
+template <int Q> struct TileIn {
+    typedef double f64x2 __attribute__((ext_vector_type(2)));
+    using TD = TileDim<Q>;
+    static constexpr int NP = TD::NP, NTH = 256;
+    static constexpr int NIT = (EPW * 6 * NP / 2 + NTH - 1) / NTH;
+    static_assert(EPW * kGeo / 2 <= NTH && ft_words(Q) <= NTH, "one load per thread");
+    f64x2 y[NIT], g;
+    int code[TD::RF];
+    uint32_t keep;
+    __device__ __forceinline__ void request(const StageArgs& a, int64_t blk, int tid) {
+        const int64_t e0 = blk * EPW;
+        const int ne = (int)((a.K - e0) < EPW ? (a.K - e0) : EPW);
+        const f64x2* Y = reinterpret_cast<const f64x2*>((const double*)a.Y + e0 * 6 * NP);
+        const f64x2* geo = reinterpret_cast<const f64x2*>((const double*)a.geo + e0 * kGeo);
+        const int* conn = a.conn + e0 * 4;
+#pragma unroll
+        for (int r = 0; r < TD::RF; ++r) {
+            const int it = tid + NTH * r;
+            code[r] = it < ne * 4 * TD::NFP ? conn[it / TD::NFP] : -3;
+        }
+#pragma unroll
+        for (int t = 0; t < NIT; ++t)
+            if (tid + NTH * t < ne * 6 * NP / 2) y[t] = Y[tid + NTH * t];
+        if (tid < ne * kGeo / 2) g = geo[tid];
+        keep = a.imask ? (a.imask[blk] ^ (a.imask_inv ? 0xffffffffu : 0u)) : 0xffffffffu;
+    }
+    __device__ __forceinline__ void put(TileShared<Q>& sh, int ne, int tid) const {
+#pragma unroll
+        for (int t = 0; t < NIT; ++t) {
+            const int v = 2 * (tid + NTH * t);
+            if (tid + NTH * t < ne * 6 * NP / 2) {
+                const bool on = (keep >> (v / (6 * NP))) & 1u;
+                sh.sY[v + v / NP] = on ? y[t][0] : 0.;
+                sh.sY[v + 1 + v / NP] = on ? y[t][1] : 0.;
+            }
+        }
+        if (tid < ne * kGeo / 2) reinterpret_cast<f64x2*>(sh.sG)[tid] = g;
+    }
+};
+
+template <int Q, bool MH, bool LTSM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 3 ? 3 : 5, 8)))
+void k_stage_tile(StageArgs args, int64_t per) {
+    using TD = TileDim<Q>;
+    constexpr int NP = TD::NP, NFP = TD::NFP, RS = TD::RS, FS = TD::FS, NTH = 256, RF = TD::RF;
+    constexpr bool LOOP = TD::LOOP;
+    __shared__ __align__(16) TileShared<Q> sh;
 
     StageArgs a;
-    if (!member_args<T>(args, a)) return;  // uniform per workgroup
-    int64_t blk = xcd_block(per);
-    if (a.blist) {  // only the listed element blocks
-        if (blk >= a.nblist) return;
-        blk = a.blist[blk];
-    }
-    const int64_t e0 = blk * EPW;
-    if (e0 >= a.K) return;  // uniform per workgroup
-    const T* __restrict__ Y = (const T*)a.Y;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int mt0 = ROWS ? (wave & 1) : 0;                           // first output row tile of this wave
-    const int nt0 = COLS ? NW * (ROWS ? wave >> 1 : wave) : 0;  // first output column tile of this wave
-    const int ne = (int)((a.K - e0) < EPW ? (a.K - e0) : EPW);
-    const int64_t base = e0 * 6 * NP;
-    constexpr int PV = 16 / (int)sizeof(T);  // values per 16-byte group
-    const int nvv = ne * 6 * NP / PV;        // 16-byte groups of the chunk (6 NP ne is a multiple of 4)
+    if (!member_args<double>(args, a)) return;  // uniform per workgroup
+    // the blocks of this workgroup: index, index + gridDim.x / 8, .. of its XCD's range
+    const int64_t nblk = a.blist ? a.nblist : (a.K + EPW - 1) / EPW;
+    const int64_t lo = (blockIdx.x & 7) * per, hi = lo + per < nblk ? lo + per : nblk;
+    const double* __restrict__ Y = (const double*)a.Y;
+    int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // matrix fragments (coalesced: fragment-major, lane-minor); lift
-    // fragments one face at a time, requested one face ahead
-    const T* fr = gFrag64 + frag_off(Q);
-    T afV[MW][KSV], afL[MW][KSF], afN[MW][KSF];
-    auto lift_frags = [&](int f, T (&d)[MW][KSF]) {
-#pragma unroll
-        for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-            for (int ks = 0; ks < KSF; ++ks) d[mt][ks] = fr[(MT * KSV + (f * MT + mt + mt0) * KSF + ks) * 64 + lane];
-    };
+    for (int64_t at = lo + (blockIdx.x >> 3); at < hi; at += gridDim.x >> 3) {
+        // what depends on the thread alone is formed anew for every block: kept
+        // across blocks it would take the registers of the loads in flight
+        if constexpr (LOOP) asm volatile("" : "+v"(tid));
+        const int lane = tid & 63, q4 = lane >> 4, n = 16 * wave + (lane & 15);
+        const int64_t blk = a.blist ? a.blist[at] : at;  // with a list only the listed element blocks
+        const int64_t e0 = blk * EPW;
+        const int ne = (int)((a.K - e0) < EPW ? (a.K - e0) : EPW);
+        const int64_t base = e0 * 6 * NP;
+        const int nvv = ne * 6 * NP / 2;  // 16-byte groups of the block's rows
 
-    // ---- staging: chunk fields, geometry, connectivity, face-node tables;
-    // the volume and face-0 lift fragments are requested right behind the
-    // chunk's loads, so their latency hides behind the staging wait
-    const uint32_t keep = a.imask ? (a.imask[blk] ^ (a.imask_inv ? 0xffffffffu : 0u)) : 0xffffffffu;
-    {
-        ChunkIn<T, Q, NTH> in;
-        in.fetch(Y, (const T*)a.geo, a.conn, e0, ne, tid);
+        // ---- every load that depends on no other; the tables with the first block
+        const bool first = !LOOP || at < lo + (gridDim.x >> 3);
+        constexpr int NM = LOOP ? (TD::NTAB + NTH - 1) / NTH : 1;
+        uint32_t tw;
+        double m[NM];
+        if (first && tid < ft_words(Q)) tw = cFaceTab[ft_off(Q) + tid];
+        TileIn<Q> in;
+        in.request(a, blk, tid);
+        TileVolume<Q> vol;
+        if constexpr (!LOOP) vol.load(lane);
+        if (LOOP && first) {
 #pragma unroll
-        for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-            for (int ks = 0; ks < KSV; ++ks) afV[mt][ks] = fr[((mt + mt0) * KSV + ks) * 64 + lane];
-        lift_frags(0, afL);
-        for (int v = tid; v < NB * KF * Sh::FS; v += NTH) sh.sF[v] = T(0);
-        in.put(sh.sY, sh.sG, sh.sC, sh.sT, ne, tid, keep);
-    }
-    __syncthreads();
-
-    // face 0's neighbour traces (EAGER: every face's) in flight during the volume product
-    FluxItems<Q, RF> itm;
-    itm.init(ne, tid);
-    TraceGather<T, Q, RF> cur, nxt;
-    TraceGather<T, Q, RF> all[EAGER ? 4 : 1];
-    if constexpr (EAGER) {
-#pragma unroll
-        for (int f = 0; f < 4; ++f) all[f].issue(Y, sh.sC, sh.sT, itm, f, e0, ne, a.imask, a.imask_inv);
-    } else {
-        cur.issue(Y, sh.sC, sh.sT, itm, 0, e0, ne, a.imask, a.imask_inv);
-    }
-
-    const int q4 = lane >> 4;   // K row within a 4-row block / output row group
-    const int l16 = lane & 15;  // output column within a 16-column tile
-    acc_t acc[MW][NW];
-#pragma unroll
-    for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NW; ++nt) acc[mt][nt] = acc_t{T(0), T(0), T(0), T(0)};
-
-    // ---- volume product: B[(a, j)][n] = sgn (g_a[m1] V_m2(j) - g_a[m2] V_m1(j));
-    // padded columns read element 0 (their results are never stored)
-#pragma unroll
-    for (int nt = 0; nt < NW; ++nt) {
-        const int n = (nt + nt0) * 16 + l16;
-        const int e = n < 6 * ne ? n / 6 : 0;
-        const int s = n - 6 * (n / 6);
-        const int m = s < 3 ? s : s - 3;
-        const int m1 = m == 2 ? 0 : m + 1, m2 = m == 0 ? 2 : m - 1;  // (m+1)%3, (m+2)%3
-        const int vb = e * 6 + (s < 3 ? 3 : 0);
-        const T sgn = s < 3 ? T(-1) : T(1);
-        const T* gE = &sh.sG[e * kGeo];
-        T g1[3], g2[3];
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            g1[ax] = sgn * gE[3 * ax + m1];
-            g2[ax] = sgn * gE[3 * ax + m2];
+            for (int i = 0; i < NM; ++i)
+                if (tid + NTH * i < TD::NTAB) m[i] = gTile[TileDim<2>::NTAB + tid + NTH * i];
         }
-        const T* v1 = &sh.sY[(vb + m1) * RS];
-        const T* v2 = &sh.sY[(vb + m2) * RS];
-        constexpr int NJ = MD::NJ;
-        T r1[NJ], r2[NJ];
+        if (!first) __syncthreads();  // the update has read the staged rows of the block before
+        if (first && tid < ft_words(Q)) reinterpret_cast<uint32_t*>(sh.sT)[tid] = tw;
+        in.put(sh, ne, tid);
+        if (LOOP && first) {
 #pragma unroll
-        for (int t = 0; t < NJ; ++t) {
-            const int j = q4 + 4 * t;
-            const bool in = NP % 4 == 0 || j < NP;  // j >= Np: zero fragment, zero operand
-            r1[t] = in ? v1[in ? j : 0] : T(0);
-            r2[t] = in ? v2[in ? j : 0] : T(0);
+            for (int i = 0; i < NM; ++i)
+                if (tid + NTH * i < TD::NTAB) sh.sM[tid + NTH * i] = m[i];
         }
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax)
-#pragma unroll
-            for (int t = 0; t < NJ; ++t) {
-                const T b = fma(g1[ax], r2[t], -g2[ax] * r1[t]);
-#pragma unroll
-                for (int mt = 0; mt < MW; ++mt)
-                    acc[mt][nt] = Mfma<T>::mma(afV[mt][ax * NJ + t], b, acc[mt][nt]);
-            }
-    }
+        __syncthreads();
 
-    // ---- upwind flux and lift, one face at a time
-#pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        if (!EAGER && PIPE && f < 3) nxt.issue(Y, sh.sC, sh.sT, itm, f + 1, e0, ne, a.imask, a.imask_inv);
-        if (f < 3) lift_frags(f + 1, afN);
-        T* tile = sh.sF + (EAGER ? (f & 1) * KF * Sh::FS : 0);
-        const TraceGather<T, Q, RF>& gat = EAGER ? all[f] : cur;
+        // ---- neighbour traces of the thread's face nodes, in flight during the
+        // volume product (a neighbour in the block is read from LDS)
+        double nv[RF][6];
+        int own[RF], nbo[RF];
+        const auto& code = in.code;
 #pragma unroll
         for (int r = 0; r < RF; ++r) {
-            if (!itm.on[r]) continue;
-            const int k = itm.k[r];
-            const int fe = itm.fe[r];
-            const int own = sh.sT[f * NFP + k];
-            T Em[3], Hm[3], Ep[3], Hp[3];
+            const int it = tid + NTH * r, t = it / NFP, k = it - t * NFP;
+            own[r] = (t >> 2) * 6 * RS + sh.sT[code[r] != -3 ? (t & 3) * NFP + k : 0];
+            nbo[r] = -1;
+            if (code[r] >= 0) {
+                const int nn = sh.sT[4 * NFP + (((code[r] >> 3) & 3) * 6 + (code[r] & 7)) * NFP + k];
+                const int64_t nb = code[r] >> 5;
+                if (nb >= e0 && nb < e0 + ne) {
+                    nbo[r] = (int)(nb - e0) * 6 * RS + nn;
+                } else if (a.imask && !(((a.imask[nb / EPW] >> (int)(nb % EPW)) & 1u) ^ (uint32_t)a.imask_inv)) {
+#pragma unroll
+                    for (int cc = 0; cc < 6; ++cc) nv[r][cc] = 0.;
+                } else {
+                    const double* q = Y + nb * 6 * NP + nn;
+#pragma unroll
+                    for (int cc = 0; cc < 6; ++cc) nv[r][cc] = q[cc * NP];
+                }
+            }
+        }
+
+        TileAcc<Q> acc;
+        TileLift<Q> lift;
+        if constexpr (LOOP) {
+            tile_volume<Q>(sh.sY, sh.sG, n, q4, ne, TileTable<Q, 0>(sh.sM, lane), acc);
+        } else {
+            tile_volume<Q>(sh.sY, sh.sG, n, q4, ne, vol, acc);
+            lift.load(lane);  // in flight during the flux
+        }
+        MfmaUpdateIn<double, Q, NTH, LTSM> upd;
+        if constexpr (LOOP) upd.fetch(a, base, nvv, tid);  // in flight during flux and lift
+
+        // ---- upwind flux of the thread's face nodes
+#pragma unroll
+        for (int r = 0; r < RF; ++r) {
+            if (code[r] == -3) continue;
+            const int it = tid + NTH * r, t = it / NFP, k = it - t * NFP;
+            const double* om = &sh.sY[own[r]];
+            double Em[3], Hm[3], Ep[3], Hp[3], fx[6];
 #pragma unroll
             for (int cc = 0; cc < 3; ++cc) {
-                Em[cc] = sh.sY[(fe * 6 + cc) * RS + own];
-                Hm[cc] = sh.sY[(fe * 6 + 3 + cc) * RS + own];
+                Em[cc] = om[cc * RS];
+                Hm[cc] = om[(3 + cc) * RS];
             }
-            const int code = gat.code[r];
-            if (code >= 0) {
-                gat.values(sh.sY, r, Ep, Hp);
-            } else if (code == -1) {  // PEC ghost: E+ = -E-, H+ = H-
+            if (nbo[r] >= 0) {
+                const double* np = &sh.sY[nbo[r]];
 #pragma unroll
                 for (int cc = 0; cc < 3; ++cc) {
-                    Ep[cc] = -Em[cc];
-                    Hp[cc] = Hm[cc];
+                    Ep[cc] = np[cc * RS];
+                    Hp[cc] = np[(3 + cc) * RS];
                 }
-            } else {  // impedance ghost (homogeneous part): zero exterior state
+            } else {
 #pragma unroll
                 for (int cc = 0; cc < 3; ++cc) {
-                    Ep[cc] = T(0);
-                    Hp[cc] = T(0);
+                    // PEC ghost: E+ = -E-, H+ = H-; impedance ghost (homogeneous
+                    // part): zero exterior state
+                    Ep[cc] = code[r] >= 0 ? nv[r][cc] : code[r] == -1 ? -Em[cc] : 0.;
+                    Hp[cc] = code[r] >= 0 ? nv[r][3 + cc] : code[r] == -1 ? Hm[cc] : 0.;
                 }
             }
-            T fx[6];
-            upwind3(&sh.sG[fe * kGeo + 9 + 7 * f], Em, Hm, Ep, Hp, fx);
-            T* o = &tile[k * Sh::FS + fe * 6];
+            upwind3(&sh.sG[(t >> 2) * kGeo + 9 + 7 * (t & 3)], Em, Hm, Ep, Hp, fx);
+            double* o = &sh.sF[((t & 3) * NFP + k) * FS + (t >> 2) * 6];
 #pragma unroll
             for (int cc = 0; cc < 6; ++cc) o[cc] = fx[cc];
         }
         __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < KSF; ++ks) {
-            T b[NW];
-#pragma unroll
-            for (int nt = 0; nt < NW; ++nt) b[nt] = tile[(ks * 4 + q4) * Sh::FS + (nt + nt0) * 16 + l16];
-#pragma unroll
-            for (int nt = 0; nt < NW; ++nt)
-#pragma unroll
-                for (int mt = 0; mt < MW; ++mt)
-                    acc[mt][nt] = Mfma<T>::mma(afL[mt][ks], b[nt], acc[mt][nt]);
-        }
-        // one tile: it is rewritten by the next face; two tiles: the next face
-        // writes the other one, and the face after it only once every thread
-        // has passed the next face's barrier (so has finished this lift)
-        if (!EAGER) __syncthreads();
-        if (f < 3) {
-            if (!EAGER) {
-                if (!PIPE) nxt.issue(Y, sh.sC, sh.sT, itm, f + 1, e0, ne, a.imask, a.imask_inv);
-                cur = nxt;
-            }
-#pragma unroll
-            for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-                for (int ks = 0; ks < KSF; ++ks) afL[mt][ks] = afN[mt][ks];
-        }
-    }
 
-    // ---- scaled right-hand side (1/eps or 1/mu, conductivity) into the
-    // staging tile, in place: every value is read and written by one lane
-#pragma unroll
-    for (int nt = 0; nt < NW; ++nt) {
-        const int n = (nt + nt0) * 16 + l16;
-        if (n >= 6 * ne) continue;
-        const int e = n / 6;
-        const int s = n - 6 * e;
-        const T inv = s < 3 ? sh.sG[e * kGeo + 37] : sh.sG[e * kGeo + 38];
-        const T sig = s < 3 ? sh.sG[e * kGeo + 39] : T(0);
-#pragma unroll
-        for (int mt = 0; mt < MW; ++mt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = (mt + mt0) * 16 + Mfma<T>::row(q4, r);
-                if (i < NP) {
-                    T* p = &sh.sY[n * RS + i];
-                    *p = fma(inv, acc[mt][nt][r], -sig * *p);
-                }
-            }
+        // ---- lift; scaled right-hand side in place of the stage input (only this
+        // thread still reads these values)
+        if constexpr (LOOP) {
+            tile_lift<Q>(sh.sF, n, q4, TileTable<Q, TD::KSV>(sh.sM, lane), acc);
+        } else {
+            upd.fetch(a, base, nvv, tid);
+            tile_lift<Q>(sh.sF, n, q4, lift, acc);
+        }
+        if (n < 6 * ne) {
+            const int e = n / 6, s = n - 6 * e;
+            const double inv = s < 3 ? sh.sG[e * kGeo + 37] : sh.sG[e * kGeo + 38];
+            const double sig = s < 3 ? sh.sG[e * kGeo + 39] : 0.;
+            acc.rows(q4, [&](int i, double v) {
+                double* p = &sh.sY[n * RS + i];
+                *p = fma(inv, v, -sig * *p);
+            });
+        }
+        __syncthreads();
+        stage_update<double, Q, NTH, MH, LTSM>(args, a, upd, blk, base, nvv, tid, [&](int v, double (&kv)[2]) {
+            kv[0] = sh.sY[v + v / NP];
+            kv[1] = sh.sY[v + 1 + v / NP];
+        });
+        if constexpr (!LOOP) return;
     }
-    __syncthreads();
-
-    // ---- stage update
-    MfmaUpdateIn<T, Q, NTH, LTSM> upd;
-    upd.fetch(a, base, nvv, tid);
-    stage_update<T, Q, NTH, MH, LTSM>(args, a, upd, blk, base, nvv, tid, [&](int v, T (&kv)[PV]) {
-#pragma unroll
-        for (int u = 0; u < PV; ++u) kv[u] = sh.sY[v + u + (v + u) / NP];
-    });
 }
 
 // ---------------------------------------------------------------------------
@@ -1792,21 +1835,16 @@ __device__ __forceinline__ bool period_block(const PeriodArgs& a, int64_t per, i
     return blk * EPW < a.K;
 }
 
-// FP64 P2 and P3, with the tiles and the order of sums of k_stage_mfma's
-// four-wave form: results agree with the stage launches bit for bit.
+// FP64 P2 and P3, with the arithmetic of k_stage_tile: results agree with the
+// stage launches bit for bit.
 template <int Q, int OCC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCC, 8)))
-void k_period_mfma(PeriodArgs a, int64_t per) {
+void k_period_tile(PeriodArgs a, int64_t per) {
     using T = double;
-    using MD = MfmaDim<Q>;
-    using PF = PeriodFaces<T, Q, 256, MfmaDim<Q>::NP + 1>;
-    using acc_t = typename Mfma<T>::acc_t;
-    constexpr int NP = MD::NP, MT = MD::MT, KSV = MD::KSV, KSF = MD::KSF, KF = 4 * KSF;
-    constexpr int NTH = 256, RS = NP + 1, FO = PF::FO;
-    constexpr int FS = 65;                          // flux tile row stride, rows [f][face node], NFP .. KF - 1 of
-                                                    // a face multiplied by zero fragments
-    constexpr int NSH = FO + 4 * KF * FS;
-    constexpr int NW = MT == 2 ? 2 : 1;             // output column tiles of a wave (P3: one of two row tiles)
+    using TD = TileDim<Q>;
+    constexpr int NP = TD::NP, NTH = 256, RS = TD::RS, FS = TD::FS;
+    using PF = PeriodFaces<T, Q, NTH, RS>;
+    constexpr int FO = PF::FO, NSH = FO + 4 * TD::NFP * FS;
     constexpr int PV = 16 / (int)sizeof(T);         // values of an update group
     constexpr int NIT = (EPW * 6 * NP / PV + NTH - 1) / NTH;
     typedef T V __attribute__((ext_vector_type(PV)));
@@ -1820,25 +1858,17 @@ void k_period_mfma(PeriodArgs a, int64_t per) {
     const int64_t e0 = blk * EPW;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int mt0 = MT == 2 ? (wave & 1) : 0, nt0 = MT == 2 ? 2 * (wave >> 1) : wave;
-    int q4 = lane >> 4, l16 = lane & 15, upd = tid;
+    int q4 = lane >> 4, n = 16 * wave + (lane & 15), upd = tid;
     const int ne = (int)((a.K - e0) < EPW ? (a.K - e0) : EPW);
     const int nvv = ne * 6 * NP / PV;
     const int64_t base = (int64_t)mem * a.bstride + e0 * 6 * NP;
     const int M = a.msteps ? a.msteps[mem] : a.M;
     const int NS = a.scheme == 2 ? 2 : 4;
 
-    // matrix fragments of the wave's row tile
-    T afV[KSV], afL[4][KSF];
-    {
-        const T* fr = gFrag64 + frag_off(Q);
-#pragma unroll
-        for (int ks = 0; ks < KSV; ++ks) afV[ks] = fr[(mt0 * KSV + ks) * 64 + lane];
-#pragma unroll
-        for (int f = 0; f < 4; ++f)
-#pragma unroll
-            for (int ks = 0; ks < KSF; ++ks) afL[f][ks] = fr[(MT * KSV + (f * MT + mt0) * KSF + ks) * 64 + lane];
-    }
+    TileVolume<Q> vol;
+    TileLift<Q> lift;
+    vol.load(lane);
+    lift.load(lane);
     // state: 16-byte groups v = tid + NTH t of the block's rows
     V up[NIT], ap[NIT];
     const T* geo = (const T*)a.geo + (int64_t)mem * a.gstride + e0 * kGeo;
@@ -1859,7 +1889,7 @@ void k_period_mfma(PeriodArgs a, int64_t per) {
             for (int u = 0; u < PV; ++u) S[v + u + (v + u) / NP] = up[t][u];
         }
     }
-    pf.init(sh, a, e0, ne, tid, [](int f, int k, int e) { return (f * KF + k) * FS + e * 6; });
+    pf.init(sh, a, e0, ne, tid, [](int f, int k, int e) { return (f * TD::NFP + k) * FS + e * 6; });
 
     uint32_t epoch = a.epoch;
     const int64_t half = (int64_t)a.members * a.next * (PF::CF * PF::X::W);  // words of one buffer
@@ -1876,7 +1906,7 @@ void k_period_mfma(PeriodArgs a, int64_t per) {
             pf.hold();
             // indices are formed anew in every stage: ahead of the loop they and
             // the geometry behind them would take the registers
-            asm volatile("" : "+v"(q4), "+v"(l16), "+v"(upd));
+            asm volatile("" : "+v"(q4), "+v"(n), "+v"(upd));
             const double* tab = a.mtab + (((int64_t)(m < M ? m : a.M) * NS + s) * a.members + mem) * kMemberParams;
             const T cy = (T)tab[0], ca = (T)tab[1], cu = (T)tab[2], scos = (T)tab[3], ssin = (T)tab[4];
             // request the neighbours' traces; they travel during the volume product
@@ -1884,42 +1914,8 @@ void k_period_mfma(PeriodArgs a, int64_t per) {
             Inbox<T, PF::RQ, NTH> box;
             box.request(in, 0, pf.n, tid);
 
-            // ---- volume product (k_stage_mfma)
-            acc_t acc[NW];
-#pragma unroll
-            for (int nt = 0; nt < NW; ++nt) {
-                acc[nt] = acc_t{T(0), T(0), T(0), T(0)};
-                const int n = (nt + nt0) * 16 + l16;
-                const int e = n < 6 * ne ? n / 6 : 0;
-                const int sc = n - 6 * (n / 6);
-                const int mm = sc < 3 ? sc : sc - 3;
-                const int m1 = mm == 2 ? 0 : mm + 1, m2 = mm == 0 ? 2 : mm - 1;
-                const int vb = e * 6 + (sc < 3 ? 3 : 0);
-                const T sgn = sc < 3 ? T(-1) : T(1);
-                const T* gE = &sG[e * kGeo];
-                T g1[3], g2[3];
-#pragma unroll
-                for (int ax = 0; ax < 3; ++ax) {
-                    g1[ax] = sgn * gE[3 * ax + m1];
-                    g2[ax] = sgn * gE[3 * ax + m2];
-                }
-                const T* v1 = &S[(vb + m1) * RS];
-                const T* v2 = &S[(vb + m2) * RS];
-                constexpr int NJ = MD::NJ;
-                T r1[NJ], r2[NJ];
-#pragma unroll
-                for (int t = 0; t < NJ; ++t) {
-                    const int j = q4 + 4 * t;
-                    const bool on = NP % 4 == 0 || j < NP;
-                    r1[t] = on ? v1[on ? j : 0] : T(0);
-                    r2[t] = on ? v2[on ? j : 0] : T(0);
-                }
-#pragma unroll
-                for (int ax = 0; ax < 3; ++ax)
-#pragma unroll
-                    for (int t = 0; t < NJ; ++t)
-                        acc[nt] = Mfma<T>::mma(afV[ax * NJ + t], fma(g1[ax], r2[t], -g2[ax] * r1[t]), acc[nt]);
-            }
+            TileAcc<Q> acc;
+            tile_volume<Q>(S, sG, n, q4, ne, vol, acc);
 
             pf.receive(sh, S, box, in, epoch, a, tid);
             __syncthreads();
@@ -1927,32 +1923,16 @@ void k_period_mfma(PeriodArgs a, int64_t per) {
             pf.flux(S, sG, 1, tid);
             __syncthreads();
 
-            // ---- lift, face by face
-#pragma unroll
-            for (int f = 0; f < 4; ++f)
-#pragma unroll
-                for (int ks = 0; ks < KSF; ++ks)
-#pragma unroll
-                    for (int nt = 0; nt < NW; ++nt)
-                        acc[nt] = Mfma<T>::mma(afL[f][ks], S[FO + (f * KF + ks * 4 + q4) * FS + (nt + nt0) * 16 + l16],
-                                               acc[nt]);
-            // ---- scaled right-hand side into the staged rows, in place
-#pragma unroll
-            for (int nt = 0; nt < NW; ++nt) {
-                const int n = (nt + nt0) * 16 + l16;
-                if (n >= 6 * ne) continue;
-                const int e = n / 6;
-                const int sc = n - 6 * e;
+            // ---- lift; scaled right-hand side into the staged rows, in place
+            tile_lift<Q>(S + FO, n, q4, lift, acc);
+            if (n < 6 * ne) {
+                const int e = n / 6, sc = n - 6 * e;
                 const T inv = sc < 3 ? sG[e * kGeo + 37] : sG[e * kGeo + 38];
                 const T sig = sc < 3 ? sG[e * kGeo + 39] : T(0);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = mt0 * 16 + Mfma<T>::row(q4, r);
-                    if (i < NP) {
-                        T* p = &S[n * RS + i];
-                        *p = fma(inv, acc[nt][r], -sig * *p);
-                    }
-                }
+                acc.rows(q4, [&](int i, T v) {
+                    T* p = &S[n * RS + i];
+                    *p = fma(inv, v, -sig * *p);
+                });
             }
             __syncthreads();
 
@@ -2629,20 +2609,14 @@ __global__ void k_nonfinite(const double* X, int64_t n, int* flag) {
 }
 
 // Stage-kernel variant per (q, precision): 0 = gather per face, 1 = gathers
-// pipelined one face ahead; from 2 on (q >= 2) on the matrix cores: FP32 fields
-// k_stage_col whatever the number, FP64 fields the forms of k_stage_mfma: 2 / 3 =
-// without / with the one-face-ahead gathers, 4 = 3 with two waves per block, 5-7
-// the eager-gather and column-split forms of 4, 8 = four waves per block, 9 = 8
-// with every face's gathers at once; -1 = chosen per launch from its size.
-// Overridable through cmcg_tune_stage() and the autotuner.  Defaults: per-face
-// gathers for P1; for FP64 P2 and P3 the form the autotuner's timings favour at
-// the launch's size (workgroups over all members; us per launch, forms 4 / 8 /
-// 9): P2 3072 tets 9.4 / 8.1 / 7.8, 10368 tets 12.3 / 11.7 / 13.6, 48000 tets
-// 33.3 / 35.6 / 37.2; P3 3072 tets 17.5 / 12.9 / 12.5, 48000 tets 69.6 / 68.9 /
-// 75.3 (the VALU form: 112.7).  FP32 P2 and P3 have one form for every size,
-// ahead of the VALU form throughout (P2: 196608 tets 50 / 53 us, 64 members of
-// 10368 184 / 200); the numbers by size are what cmcg_tune_resolve_stage has
-// always reported there.
+// pipelined one face ahead; from 2 on (q >= 2) on the matrix cores, one kernel
+// per precision whatever the number: k_stage_col (FP32), k_stage_tile (FP64);
+// -1 = chosen per launch from its size.  Overridable through cmcg_tune_stage()
+// and the autotuner.  Defaults: per-face gathers for P1, the matrix cores for P2
+// and P3, ahead of the VALU form at every size (FP32 P2: 196608 tets 50 / 53 us,
+// 64 members of 10368 184 / 200; FP64 P2: 82944 tets 38.5 / 54; P3: 48000 tets
+// 50.5 / 116).  The numbers by size are what cmcg_tune_resolve_stage has always
+// reported.
 int g_variant[kMaxQ + 1][2] = {{0, 0}, {0, 0}, {-1, -1}, {-1, -1}};
 inline int variant_by_size(int q, int precision, int64_t blocks) {
     if (precision == CMCG_FP64) {
@@ -2665,51 +2639,28 @@ inline int grid_for(int64_t n, int threads = 256) {
     return (int)g;
 }
 
+// Grid of k_stage_tile.  P3: what the device holds at once (three workgroups per
+// compute unit, 32 compute units per XCD), each running several blocks where
+// there are more.
+template <int Q> inline dim3 tile_grid(int64_t per, unsigned members) {
+    int64_t n = per;
+    if (TileDim<Q>::LOOP && n > 96 / (int64_t)members) n = 96 / members;
+    return dim3((unsigned)(8 * (n < 1 ? 1 : n)), members);
+}
+
 template <typename T, int Q, bool MH>
 void stage_launch_mh(const StageArgs& a, hipStream_t s) {
     const int64_t blocks = a.blist ? a.nblist : (a.K + EPW - 1) / EPW;
     const int64_t per = (blocks + 7) / 8;
     const int v = stage_variant(Q, sizeof(T) == 8 ? CMCG_FP64 : CMCG_FP32, blocks * (a.nmembers > 1 ? a.nmembers : 1));
     const dim3 grid((unsigned)(8 * per), (unsigned)(a.nmembers > 1 ? a.nmembers : 1));
-    if constexpr (std::is_same<T, float>::value && Q >= 2) {
-        if (v >= 2) {
-            hipLaunchKernelGGL((k_stage_col<Q, MH, false>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
+    if constexpr (Q >= 2) {
+        if (v >= 2 && (Q == 3 || (v != 6 && v != 7))) {
+            if constexpr (std::is_same<T, float>::value)
+                hipLaunchKernelGGL((k_stage_col<Q, MH, false>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
+            else
+                hipLaunchKernelGGL((k_stage_tile<Q, MH, false>), tile_grid<Q>(per, grid.y), dim3(256), 0, s, a, per);
             return;
-        }
-    } else if constexpr (Q >= 2) {
-        if (v == 2) {
-            hipLaunchKernelGGL((k_stage_mfma<Q, false, MH, 1>), grid, dim3(64), 0, s, a, per);
-            return;
-        }
-        if (v == 3) {
-            hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 1>), grid, dim3(64), 0, s, a, per);
-            return;
-        }
-        if (v == 4) {
-            hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 2>), grid, dim3(128), 0, s, a, per);
-            return;
-        }
-        if (v == 5) {
-            hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 2, true>), grid, dim3(128), 0, s, a, per);
-            return;
-        }
-        if (v == 8) {
-            hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 4>), grid, dim3(256), 0, s, a, per);
-            return;
-        }
-        if (v == 9) {
-            hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 4, true>), grid, dim3(256), 0, s, a, per);
-            return;
-        }
-        if constexpr (Q == 3) {
-            if (v == 6) {
-                hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 2, false, true>), grid, dim3(128), 0, s, a, per);
-                return;
-            }
-            if (v == 7) {
-                hipLaunchKernelGGL((k_stage_mfma<Q, true, MH, 2, true, true>), grid, dim3(128), 0, s, a, per);
-                return;
-            }
         }
     }
     if (v == 1)
@@ -2724,20 +2675,11 @@ void stage_launch(const StageArgs& a, hipStream_t s) {
         const int64_t blocks = a.blist ? a.nblist : (a.K + EPW - 1) / EPW;
         const int64_t per = (blocks + 7) / 8;
         const dim3 grid((unsigned)(8 * per));
-        // FP64: four waves per block on the launches restricted to a block list
-        // (the substep stages: a partial round of workgroups, whose time is
-        // one block's chain) and where the chosen form has four (8, 9); two
-        // otherwise
-        if constexpr (Q >= 2 && std::is_same<T, float>::value) {
+        if constexpr (Q >= 2 && std::is_same<T, float>::value)
             hipLaunchKernelGGL((k_stage_col<Q, false, true>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
-        } else if constexpr (Q >= 2) {
-            if (a.blist || stage_variant(Q, sizeof(T) == 8 ? CMCG_FP64 : CMCG_FP32, blocks) >= 8)
-                hipLaunchKernelGGL((k_stage_mfma<Q, true, false, 4, false, false, true>), grid, dim3(256), 0, s,
-                                   a, per);
-            else
-                hipLaunchKernelGGL((k_stage_mfma<Q, true, false, 2, false, false, true>), grid, dim3(128), 0, s,
-                                   a, per);
-        } else
+        else if constexpr (Q >= 2)
+            hipLaunchKernelGGL((k_stage_tile<Q, false, true>), tile_grid<Q>(per, 1), dim3(256), 0, s, a, per);
+        else
             hipLaunchKernelGGL((k_stage<T, Q, false, false, true>), grid, dim3(64), 0, s, a, per);
         return;
     }
@@ -2843,32 +2785,21 @@ void upload_constants(int q, int precision, const double* D, const double* LIFT,
                                    hipMemcpyHostToDevice));
     }
     if (q >= 2) {
-        // lane-ordered A fragments of the matrix-core kernel: entry (frag, lane)
-        // = A[16 mt + lane % 16][4 ks + lane / 16] of the block the fragment names
-        const int MT = (NP + 15) / 16, NJ = (NP + 3) / 4, KSV = 3 * NJ, KSF = (NFP + 3) / 4;
-        const int nfrag = MT * KSV + 4 * MT * KSF;
-        std::vector<double> fr(64 * nfrag, 0.0);
-        for (int l = 0; l < 64; ++l) {
-            const int i_in = l % 16, k_in = l / 16;
-            for (int mt = 0; mt < MT; ++mt) {
-                const int i = 16 * mt + i_in;
-                for (int ks = 0; ks < KSV; ++ks) {
-                    const int a = ks / NJ, j = 4 * (ks % NJ) + k_in;  // axis-major K order
-                    double v = 0.0;
-                    if (i < NP && j < NP) v = D[(a * NP + i) * NP + j];
-                    fr[(mt * KSV + ks) * 64 + l] = v;
-                }
-                for (int f = 0; f < 4; ++f)
-                    for (int ks = 0; ks < KSF; ++ks) {
-                        const int k = 4 * ks + k_in;
-                        double v = 0.0;
-                        if (i < NP && k < NFP) v = LIFT[i * 4 * NFP + f * NFP + k];
-                        fr[(MT * KSV + (f * MT + mt) * KSF + ks) * 64 + l] = v;
-                    }
-            }
+        // A operands of the FP64 kernels' K steps (gTile)
+        const int NJ = (NP + 3) / 4, KSV = 3 * NJ, NST = KSV + NFP, tail = NP > 16;
+        std::vector<double> t((size_t)NST * (tail ? 80 : 64), 0.0);
+        const auto at = [&](int i, int st, int k) {  // row i, K row k of step st
+            if (i >= NP) return 0.0;
+            if (st >= KSV) return LIFT[i * 4 * NFP + 4 * (st - KSV) + k];
+            const int j = 4 * (st % NJ) + k;
+            return j < NP ? D[(st / NJ * NP + i) * NP + j] : 0.0;
+        };
+        for (int st = 0; st < NST; ++st) {
+            for (int l = 0; l < 64; ++l) t[st * 64 + l] = at(l % 16, st, l / 16);
+            for (int l = 0; tail && l < 16; ++l) t[NST * 64 + st * 16 + l] = at(16 + l % 4, st, l / 4);
         }
-        CMCG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(gFrag64), fr.data(), fr.size() * sizeof(double),
-                                   frag_off(q) * sizeof(double), hipMemcpyHostToDevice));
+        CMCG_HIP(hipMemcpyToSymbol(HIP_SYMBOL(gTile), t.data(), t.size() * sizeof(double),
+                                   (q == 2 ? 0 : TileDim<2>::NTAB) * sizeof(double), hipMemcpyHostToDevice));
     }
 }
 
@@ -2890,8 +2821,11 @@ void launch_stage(int q, int precision, const StageArgs& a, hipStream_t s) {
 //   FP32 P1 1296 tets 1.1 / 2.9, 10368 2.1 / 3.1, 12790 2.3 / 3.2;
 //   FP32 P2 3072 3.5 / 4.7, 10368 5.2 / 6.8, 15300 6.4 / 8.3;
 //   FP32 P3 384 3.7 / 4.7, 3072 4.4 / 5.8, 7600 5.7 / 8.3;
-//   FP64 P1 1296 1.4 / 3.1, 6000 3.1 / 3.3; P2 3072 5.4 / 7.5, 6000 8.7 / 9.1;
-//   FP64 P3 384 6.5 / 8.8, 4374 10.5 / 13.1.
+//   FP64 P1 1296 1.4 / 3.1, 6000 3.1 / 3.3;
+//   FP64 P2 384 3.8 / 4.5, 1296 4.1 / 4.7, 3072 5.2 / 5.7, but 4374 6.7 / 5.9 and
+//   6000 8.7 / 7.2, so up to 350 blocks only (two FP64 words a value and the
+//   update's copy through LDS cost more than the launches they replace);
+//   FP64 P3 384 5.3 / 7.0, 3072 7.6 / 9.2, 4374 9.5 / 9.8.
 // Members in several groups, one after another, lose to stage launches that run
 // all members at once (FP32 P2, 16 members of 10368 tets: 156 ms a solve against
 // 102; FP64 P1, 16 of 1296: 50 against 27).
@@ -2903,8 +2837,8 @@ bool period3d_f32(int q, const PeriodArgs& a, int64_t nb, int n, hipStream_t s) 
 }
 bool period3d_f64(int q, const PeriodArgs& a, int64_t nb, int n, hipStream_t s) {
     if (q == 1) return launch_resident(k_period_p1<double>, nb, n, 256, false, a, s);
-    if (q == 2) return launch_resident(k_period_mfma<2, 3>, nb, n, 256, false, a, s);
-    return launch_resident(k_period_mfma<3, 2>, nb, n, 256, false, a, s);
+    if (q == 2) return nb * n <= 350 && launch_resident(k_period_tile<2, 3>, nb, n, 256, false, a, s);
+    return launch_resident(k_period_tile<3, 2>, nb, n, 256, false, a, s);
 }
 }  // namespace
 
