@@ -733,11 +733,31 @@ template <> struct Mfma<double> {
     static __device__ __forceinline__ int row(int q4, int r) { return 4 * r + q4; }
 };
 
+// 8- and 16-byte accesses of the update pass, with the non-temporal hint where
+// STREAM says so (stream_hints below; a template argument, since the compiler
+// merges two branches that differ in the hint alone, and drops it).
+template <typename V> struct Raw {
+    typedef unsigned int W __attribute__((ext_vector_type(sizeof(V) / 4)));
+};
+template <bool STREAM, typename V> __device__ __forceinline__ V ldg(const void* p) {
+    const auto* q = reinterpret_cast<const typename Raw<V>::W*>(p);
+    if constexpr (STREAM) return __builtin_bit_cast(V, __builtin_nontemporal_load(q));
+    return __builtin_bit_cast(V, *q);
+}
+template <bool STREAM, typename V> __device__ __forceinline__ void stg(void* p, const V& v) {
+    auto* q = reinterpret_cast<typename Raw<V>::W*>(p);
+    const auto w = __builtin_bit_cast(typename Raw<V>::W, v);
+    if constexpr (STREAM)
+        __builtin_nontemporal_store(w, q);
+    else
+        *q = w;
+}
+
 // Operands of the coalesced update pass (16-byte groups v = lane + NTH t of
 // the chunk: 4 FP32 or 2 FP64 values), all requested before the pass
 // computes: r0 = U (modes that combine with the state) or the stage input
 // (stage-1 modes, filter), r1 = Acc, r2 = the bfloat16 low parts (FP32).
-template <typename T, int Q, int NTH = 64, bool LTSM = false> struct MfmaUpdateIn {
+template <typename T, int Q, int NTH, bool LTSM, int STREAM> struct MfmaUpdateIn {
     static constexpr int PV = 16 / (int)sizeof(T);
     static constexpr bool COMP = std::is_same<T, float>::value;  // compensated state U + Ulo
     using V = typename std::conditional<COMP, float4, double2>::type;
@@ -760,10 +780,10 @@ template <typename T, int Q, int NTH = 64, bool LTSM = false> struct MfmaUpdateI
             const int vv = lane + NTH * t;
             if (vv >= nvv) continue;
             const int64_t gi = base + PV * vv;
-            if (s1 || needU) r0[t] = *reinterpret_cast<const V*>(src0 + gi);
-            if (needA) r1[t] = *reinterpret_cast<const V*>((const T*)a.Acc + gi);
+            if (s1 || needU) r0[t] = ldg<STREAM == 2, V>(src0 + gi);
+            if (needA) r1[t] = ldg<STREAM == 2, V>((const T*)a.Acc + gi);
             if constexpr (COMP)
-                if (needL) r2[t] = *reinterpret_cast<const uint2*>((const uint16_t*)a.Ulo + gi);
+                if (needL) r2[t] = ldg<STREAM == 2, uint2>((const uint16_t*)a.Ulo + gi);
         }
     }
 };
@@ -771,13 +791,13 @@ template <typename T, int Q, int NTH = 64, bool LTSM = false> struct MfmaUpdateI
 // Stage update of a block: one coalesced pass over its contiguous rows
 // (16-byte groups v = PV (tid + NTH t)), kvals(v, kv) giving the scaled
 // right-hand side of a group and upd its operands.
-template <typename T, int Q, int NTH, bool MH, bool LTSM, typename KV>
+template <typename T, int Q, int NTH, bool MH, bool LTSM, int STREAM, typename KV>
 __device__ __forceinline__ void stage_update(const StageArgs& args, const StageArgs& a,
-                                             const MfmaUpdateIn<T, Q, NTH, LTSM>& upd, int64_t blk, int64_t base,
+                                             const MfmaUpdateIn<T, Q, NTH, LTSM, STREAM>& upd, int64_t blk, int64_t base,
                                              int nvv, int tid, KV kvals) {
     constexpr bool COMP = std::is_same<T, float>::value;  // compensated state U + Ulo
     constexpr int NP = Dim<Q>::NP, PV = 16 / (int)sizeof(T);
-    using UIn = MfmaUpdateIn<T, Q, NTH, LTSM>;
+    using UIn = MfmaUpdateIn<T, Q, NTH, LTSM, STREAM>;
     using V = typename UIn::V;
     const int mode = a.mode;
     const T scos = (T)a.scos, ssin = (T)a.ssin;
@@ -846,7 +866,7 @@ __device__ __forceinline__ void stage_update(const StageArgs& args, const StageA
             T* q = reinterpret_cast<T*>(&w);
 #pragma unroll
             for (int u = 0; u < PV; ++u) q[u] = o[u];
-            *reinterpret_cast<V*>((T*)p + gi) = w;
+            stg<STREAM == 2, V>((T*)p + gi, w);
         };
         T o1[PV], o2[PV];
         if constexpr (LTSM) {
@@ -944,7 +964,7 @@ __device__ __forceinline__ void stage_update(const StageArgs& args, const StageA
                         uint2 w;
                         w.x = (uint32_t)to_bf16(o2[0]) | ((uint32_t)to_bf16(o2[1]) << 16);
                         w.y = (uint32_t)to_bf16(o2[2]) | ((uint32_t)to_bf16(o2[3]) << 16);
-                        *reinterpret_cast<uint2*>((uint16_t*)a.Ulo + gi) = w;
+                        stg<STREAM == 2, uint2>((uint16_t*)a.Ulo + gi, w);
                     } else {
 #pragma unroll
                         for (int u = 0; u < PV; ++u) o1[u] = fma(cu, kv[u], x0[u]);
@@ -978,7 +998,7 @@ __device__ __forceinline__ void stage_update(const StageArgs& args, const StageA
                         uint2 w;
                         w.x = (uint32_t)to_bf16(o2[0]) | ((uint32_t)to_bf16(o2[1]) << 16);
                         w.y = (uint32_t)to_bf16(o2[2]) | ((uint32_t)to_bf16(o2[3]) << 16);
-                        *reinterpret_cast<uint2*>((uint16_t*)a.Ulo + gi) = w;
+                        stg<STREAM == 2, uint2>((uint16_t*)a.Ulo + gi, w);
                     } else {
 #pragma unroll
                         for (int u = 0; u < PV; ++u) o1[u] = fma(cu, kv[u], x1[u]);
@@ -991,11 +1011,24 @@ __device__ __forceinline__ void stage_update(const StageArgs& args, const StageA
             }
         }
         if (a.filter) {  // stage-1 and RHS modes: x0 is the stage input
+            double2 fr[PV / 2], fi[PV / 2];
+#pragma unroll
+            for (int u = 0; u < PV / 2; ++u) {
+                fr[u] = ldg<STREAM != 0, double2>(a.Fre + gi + 2 * u);
+                fi[u] = ldg<STREAM != 0, double2>(a.Fim + gi + 2 * u);
+            }
 #pragma unroll
             for (int u = 0; u < PV; ++u) {
                 const double ud = (double)x0[u], kd = (double)kv[u];
-                a.Fre[gi + u] = fma(a.fa_re, ud, fma(a.fb_re, kd, a.Fre[gi + u]));
-                a.Fim[gi + u] = fma(a.fa_im, ud, fma(a.fb_im, kd, a.Fim[gi + u]));
+                double& re = u % 2 ? fr[u / 2].y : fr[u / 2].x;
+                double& im = u % 2 ? fi[u / 2].y : fi[u / 2].x;
+                re = fma(a.fa_re, ud, fma(a.fb_re, kd, re));
+                im = fma(a.fa_im, ud, fma(a.fb_im, kd, im));
+            }
+#pragma unroll
+            for (int u = 0; u < PV / 2; ++u) {
+                stg<STREAM != 0, double2>(a.Fre + gi + 2 * u, fr[u]);
+                stg<STREAM != 0, double2>(a.Fim + gi + 2 * u, fi[u]);
             }
 #pragma unroll 1
             for (int h = 1; MH && h < a.nharm; ++h)
@@ -1194,7 +1227,7 @@ template <int Q> struct TileIn {
     }
 };
 
-template <int Q, bool MH, bool LTSM>
+template <int Q, bool MH, bool LTSM, int STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 3 ? 3 : 5, 8)))
 void k_stage_tile(StageArgs args, int64_t per) {
     using TD = TileDim<Q>;
@@ -1281,7 +1314,7 @@ void k_stage_tile(StageArgs args, int64_t per) {
             tile_volume<Q>(sh.sY, sh.sG, n, q4, ne, vol, acc);
             lift.load(lane);  // in flight during the flux
         }
-        MfmaUpdateIn<double, Q, NTH, LTSM> upd;
+        MfmaUpdateIn<double, Q, NTH, LTSM, STREAM> upd;
         if constexpr (LOOP) upd.fetch(a, base, nvv, tid);  // in flight during flux and lift
 
         // ---- upwind flux of the thread's face nodes
@@ -1337,7 +1370,7 @@ void k_stage_tile(StageArgs args, int64_t per) {
             });
         }
         __syncthreads();
-        stage_update<double, Q, NTH, MH, LTSM>(args, a, upd, blk, base, nvv, tid, [&](int v, double (&kv)[2]) {
+        stage_update<double, Q, NTH, MH, LTSM, STREAM>(args, a, upd, blk, base, nvv, tid, [&](int v, double (&kv)[2]) {
             kv[0] = sh.sY[v + v / NP];
             kv[1] = sh.sY[v + 1 + v / NP];
         });
@@ -1507,7 +1540,7 @@ template <int Q> struct ColShared {
     uint8_t sT[4 * ft_words(Q)];
 };
 
-template <int Q, bool MH, bool LTSM>
+template <int Q, bool MH, bool LTSM, int STREAM>
 __global__ __launch_bounds__(ColDim<Q>::NTH) __attribute__((amdgpu_waves_per_eu(Q == 3 ? 7 : 5, 8)))
 void k_stage_col(StageArgs args, int64_t per) {
     using CD = ColDim<Q>;
@@ -1538,7 +1571,7 @@ void k_stage_col(StageArgs args, int64_t per) {
     f32x4 yin[NIT], gin[NG];
     uint32_t tw[NT];
     ColMats<Q> mat;
-    MfmaUpdateIn<float, Q, NTH, LTSM> upd;
+    MfmaUpdateIn<float, Q, NTH, LTSM, STREAM> upd;
 #pragma unroll
     for (int r = 0; r < RF; ++r) {
         const int it = tid + NTH * r;
@@ -1652,7 +1685,7 @@ void k_stage_col(StageArgs args, int64_t per) {
         *p = kv;
     }
     __syncthreads();
-    stage_update<float, Q, NTH, MH, LTSM>(args, a, upd, blk, base, nvv, tid, [&](int v, float (&kv)[4]) {
+    stage_update<float, Q, NTH, MH, LTSM, STREAM>(args, a, upd, blk, base, nvv, tid, [&](int v, float (&kv)[4]) {
         const f32x4 t = col_get<Q>(sh.sY, v);
 #pragma unroll
         for (int u = 0; u < 4; ++u) kv[u] = t[u];
@@ -2648,6 +2681,32 @@ template <int Q> inline dim3 tile_grid(int64_t per, unsigned members) {
     return dim3((unsigned)(8 * (n < 1 ? 1 : n)), members);
 }
 
+// Non-temporal hints for what the update pass reads and writes once per launch,
+// where the vectors of a launch exceed the 256 MB Infinity Cache anyway: the
+// stage input's planes, whose face traces the neighbouring blocks read, then
+// stay in the caches.  With and without (us per launch): FP32 P2 384000 tets (415
+// MB) 105.9 / 111.0, P3 196608 (425 MB) 131.9 / 134.8, FP64 P2 196608 (377 MB)
+// 111 / 117, FP64 P3 82944 (319 MB) 94.1 / 95.6; below the line the hint sends to
+// memory what the cache would have held: FP32 P2 196608 (212 MB) 55.6 / 49.1, P3
+// 48000 (104 MB) 34.3 / 30.6, FP64 P3 48000 (184 MB) 55.0 / 50.0.  The filter's
+// accumulators (16 B per value, read and written once per step) count as vectors
+// of their own; a filtered launch of P2 384000 tets takes 265 us, 142 of them for
+// 737 MB of accumulators, a copy's rate (scalar accesses without the hint: 360 us).
+template <typename T, int Q> int stream_hints(const StageArgs& a) {  // 2: all, 1: the filter alone
+    constexpr double kCache = 256e6;
+    const double dofs = (double)a.K * 6 * Dim<Q>::NP * (a.nmembers > 1 ? a.nmembers : 1);
+    const double vectors = dofs * (sizeof(T) == 4 ? 18 : 32);  // U, Y, Y', Acc, FP32's low parts
+    return vectors > kCache ? 2 : a.filter && vectors + 16 * dofs > kCache ? 1 : 0;
+}
+
+template <int Q, bool MH, int STREAM>
+void stage_launch_mfma(const StageArgs& a, dim3 grid, int64_t per, int precision, hipStream_t s) {
+    if (precision == CMCG_FP32)
+        hipLaunchKernelGGL((k_stage_col<Q, MH, false, STREAM>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
+    else
+        hipLaunchKernelGGL((k_stage_tile<Q, MH, false, STREAM>), tile_grid<Q>(per, grid.y), dim3(256), 0, s, a, per);
+}
+
 template <typename T, int Q, bool MH>
 void stage_launch_mh(const StageArgs& a, hipStream_t s) {
     const int64_t blocks = a.blist ? a.nblist : (a.K + EPW - 1) / EPW;
@@ -2656,10 +2715,14 @@ void stage_launch_mh(const StageArgs& a, hipStream_t s) {
     const dim3 grid((unsigned)(8 * per), (unsigned)(a.nmembers > 1 ? a.nmembers : 1));
     if constexpr (Q >= 2) {
         if (v >= 2 && (Q == 3 || (v != 6 && v != 7))) {
-            if constexpr (std::is_same<T, float>::value)
-                hipLaunchKernelGGL((k_stage_col<Q, MH, false>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
+            const int prec = sizeof(T) == 8 ? CMCG_FP64 : CMCG_FP32;
+            const int hints = MH ? 0 : stream_hints<T, Q>(a);
+            if (hints == 0)
+                stage_launch_mfma<Q, MH, 0>(a, grid, per, prec, s);
+            else if (hints == 1)
+                stage_launch_mfma<Q, false, 1>(a, grid, per, prec, s);
             else
-                hipLaunchKernelGGL((k_stage_tile<Q, MH, false>), tile_grid<Q>(per, grid.y), dim3(256), 0, s, a, per);
+                stage_launch_mfma<Q, false, 2>(a, grid, per, prec, s);
             return;
         }
     }
@@ -2676,9 +2739,9 @@ void stage_launch(const StageArgs& a, hipStream_t s) {
         const int64_t per = (blocks + 7) / 8;
         const dim3 grid((unsigned)(8 * per));
         if constexpr (Q >= 2 && std::is_same<T, float>::value)
-            hipLaunchKernelGGL((k_stage_col<Q, false, true>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
+            hipLaunchKernelGGL((k_stage_col<Q, false, true, 0>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
         else if constexpr (Q >= 2)
-            hipLaunchKernelGGL((k_stage_tile<Q, false, true>), tile_grid<Q>(per, 1), dim3(256), 0, s, a, per);
+            hipLaunchKernelGGL((k_stage_tile<Q, false, true, 0>), tile_grid<Q>(per, 1), dim3(256), 0, s, a, per);
         else
             hipLaunchKernelGGL((k_stage<T, Q, false, false, true>), grid, dim3(64), 0, s, a, per);
         return;
