@@ -764,6 +764,7 @@ template <typename T, int Q, int NTH, bool LTSM, int STREAM> struct MfmaUpdateIn
     static constexpr int NIT = (EPW * 6 * Dim<Q>::NP / PV + NTH - 1) / NTH;
     V r0[NIT], r1[NIT];
     uint2 r2[COMP ? NIT : 1];
+    V w[LTSM ? NIT : 1][4], z[LTSM ? NIT : 1];  // local time stepping: W_j, and LTS_ADJ's zbar
     __device__ __forceinline__ void fetch(const StageArgs& a, int64_t base, int nvv, int lane) {
         const int mode = a.mode;
         // LTS_FWD reads U (and Acc when given), LTS_ADJ the stage input and Acc
@@ -782,6 +783,17 @@ template <typename T, int Q, int NTH, bool LTSM, int STREAM> struct MfmaUpdateIn
             const int64_t gi = base + PV * vv;
             if (s1 || needU) r0[t] = ldg<STREAM == 2, V>(src0 + gi);
             if (needA) r1[t] = ldg<STREAM == 2, V>((const T*)a.Acc + gi);
+            if constexpr (LTSM) {
+                // all at once: behind one another, at the end, they added up to
+                // four memory latencies to every substep launch (P2 FP64, 12096
+                // tets, four substeps: 107.1 ms a solve against 104.2)
+                if (mode != LTS_CHAIN && !(mode == LTS_ADJ && a.linit)) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (j < a.lnw) w[t][j] = *reinterpret_cast<const V*>((const T*)a.lw[j] + gi);
+                }
+                if (mode == LTS_ADJ) z[t] = *reinterpret_cast<const V*>((const T*)a.U + gi);
+            }
             if constexpr (COMP)
                 if (needL) r2[t] = ldg<STREAM == 2, uint2>((const uint16_t*)a.Ulo + gi);
         }
@@ -892,8 +904,7 @@ __device__ __forceinline__ void stage_update(const StageArgs& args, const StageA
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     if (j >= a.lnw) break;
-                    T w[PV];
-                    ldv(args.lw[j], gi, w);
+                    const T* w = reinterpret_cast<const T*>(&upd.w[t][j]);
                     const T cj = (T)args.lcw[j];
 #pragma unroll
                     for (int u = 0; u < PV; ++u) kv[u] = fma(cj, w[u], kv[u]);
@@ -922,7 +933,9 @@ __device__ __forceinline__ void stage_update(const StageArgs& args, const StageA
 #pragma unroll
                             for (int u = 0; u < PV; ++u) w[u] = T(0);
                         } else {
-                            ldv(args.lw[j], gi, w);
+                            const T* wj = reinterpret_cast<const T*>(&upd.w[t][j]);
+#pragma unroll
+                            for (int u = 0; u < PV; ++u) w[u] = wj[u];
                         }
                         const T cj = (T)args.lcw[j];
 #pragma unroll
@@ -930,8 +943,7 @@ __device__ __forceinline__ void stage_update(const StageArgs& args, const StageA
                         stv(const_cast<void*>(args.lw[j]), w);
                     }
                 }
-                T z[PV];
-                ldv(a.U, gi, z);
+                const T* z = reinterpret_cast<const T*>(&upd.z[t]);
                 const T le = (T)a.le, lf = (T)a.lf;
 #pragma unroll
                 for (int u = 0; u < PV; ++u) {
@@ -1228,7 +1240,7 @@ template <int Q> struct TileIn {
 };
 
 template <int Q, bool MH, bool LTSM, int STREAM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 3 ? 3 : 5, 8)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 3 ? (LTSM ? 2 : 3) : LTSM ? 4 : 5, 8)))
 void k_stage_tile(StageArgs args, int64_t per) {
     using TD = TileDim<Q>;
     constexpr int NP = TD::NP, NFP = TD::NFP, RS = TD::RS, FS = TD::FS, NTH = 256, RF = TD::RF;
@@ -1284,21 +1296,27 @@ void k_stage_tile(StageArgs args, int64_t per) {
         // volume product (a neighbour in the block is read from LDS)
         double nv[RF][6];
         int own[RF], nbo[RF];
+        bool off[RF];
+        const auto masked = [&](int64_t nb) {  // the neighbour's values count as zero
+            return a.imask && !(((a.imask[nb / EPW] >> (int)(nb % EPW)) & 1u) ^ (uint32_t)a.imask_inv);
+        };
         const auto& code = in.code;
 #pragma unroll
         for (int r = 0; r < RF; ++r) {
             const int it = tid + NTH * r, t = it / NFP, k = it - t * NFP;
             own[r] = (t >> 2) * 6 * RS + sh.sT[code[r] != -3 ? (t & 3) * NFP + k : 0];
             nbo[r] = -1;
+            off[r] = false;
             if (code[r] >= 0) {
                 const int nn = sh.sT[4 * NFP + (((code[r] >> 3) & 3) * 6 + (code[r] & 7)) * NFP + k];
                 const int64_t nb = code[r] >> 5;
                 if (nb >= e0 && nb < e0 + ne) {
                     nbo[r] = (int)(nb - e0) * 6 * RS + nn;
-                } else if (a.imask && !(((a.imask[nb / EPW] >> (int)(nb % EPW)) & 1u) ^ (uint32_t)a.imask_inv)) {
+                } else if (!LTSM && masked(nb)) {
 #pragma unroll
                     for (int cc = 0; cc < 6; ++cc) nv[r][cc] = 0.;
                 } else {
+                    if (LTSM) off[r] = masked(nb);  // the mask travels with the traces
                     const double* q = Y + nb * 6 * NP + nn;
 #pragma unroll
                     for (int cc = 0; cc < 6; ++cc) nv[r][cc] = q[cc * NP];
@@ -1341,8 +1359,8 @@ void k_stage_tile(StageArgs args, int64_t per) {
                 for (int cc = 0; cc < 3; ++cc) {
                     // PEC ghost: E+ = -E-, H+ = H-; impedance ghost (homogeneous
                     // part): zero exterior state
-                    Ep[cc] = code[r] >= 0 ? nv[r][cc] : code[r] == -1 ? -Em[cc] : 0.;
-                    Hp[cc] = code[r] >= 0 ? nv[r][3 + cc] : code[r] == -1 ? Hm[cc] : 0.;
+                    Ep[cc] = code[r] >= 0 ? (LTSM && off[r] ? 0. : nv[r][cc]) : code[r] == -1 ? -Em[cc] : 0.;
+                    Hp[cc] = code[r] >= 0 ? (LTSM && off[r] ? 0. : nv[r][3 + cc]) : code[r] == -1 ? Hm[cc] : 0.;
                 }
             }
             upwind3(&sh.sG[(t >> 2) * kGeo + 9 + 7 * (t & 3)], Em, Hm, Ep, Hp, fx);
@@ -1541,7 +1559,7 @@ template <int Q> struct ColShared {
 };
 
 template <int Q, bool MH, bool LTSM, int STREAM>
-__global__ __launch_bounds__(ColDim<Q>::NTH) __attribute__((amdgpu_waves_per_eu(Q == 3 ? 7 : 5, 8)))
+__global__ __launch_bounds__(ColDim<Q>::NTH) __attribute__((amdgpu_waves_per_eu(LTSM ? 5 : Q == 3 ? 7 : 5, 8)))
 void k_stage_col(StageArgs args, int64_t per) {
     using CD = ColDim<Q>;
     constexpr int NP = CD::NP, NFP = CD::NFP, RS = CD::RS, FS = CD::FS, NTH = CD::NTH, RF = CD::RF;
@@ -1609,20 +1627,26 @@ void k_stage_col(StageArgs args, int64_t per) {
     // volume product (a neighbour in the block is read from LDS)
     float nv[RF][6];
     int own[RF], nbo[RF];
+    bool off[RF];
+    const auto masked = [&](int64_t nb) {  // the neighbour's values count as zero
+        return a.imask && !(((a.imask[nb / EPW] >> (int)(nb % EPW)) & 1u) ^ (uint32_t)a.imask_inv);
+    };
 #pragma unroll
     for (int r = 0; r < RF; ++r) {
         const int it = tid + NTH * r, t = it / NFP, k = it - t * NFP;
         own[r] = (t >> 2) * 6 * RS + sh.sT[code[r] != -3 ? (t & 3) * NFP + k : 0];
         nbo[r] = -1;
+        off[r] = false;
         if (code[r] >= 0) {
             const int nn = sh.sT[4 * NFP + (((code[r] >> 3) & 3) * 6 + (code[r] & 7)) * NFP + k];
             const int64_t nb = code[r] >> 5;
             if (nb >= e0 && nb < e0 + ne) {
                 nbo[r] = (int)(nb - e0) * 6 * RS + nn;
-            } else if (a.imask && !(((a.imask[nb / EPW] >> (int)(nb % EPW)) & 1u) ^ (uint32_t)a.imask_inv)) {
+            } else if (!LTSM && masked(nb)) {
 #pragma unroll
                 for (int cc = 0; cc < 6; ++cc) nv[r][cc] = 0.f;
             } else {
+                if (LTSM) off[r] = masked(nb);  // the mask travels with the traces
                 const float* q = Y + nb * 6 * NP + nn;
 #pragma unroll
                 for (int cc = 0; cc < 6; ++cc) nv[r][cc] = q[cc * NP];
@@ -1660,8 +1684,8 @@ void k_stage_col(StageArgs args, int64_t per) {
             for (int cc = 0; cc < 3; ++cc) {
                 // PEC ghost: E+ = -E-, H+ = H-; impedance ghost (homogeneous
                 // part): zero exterior state
-                Ep[cc] = code[r] >= 0 ? nv[r][cc] : code[r] == -1 ? -Em[cc] : 0.f;
-                Hp[cc] = code[r] >= 0 ? nv[r][3 + cc] : code[r] == -1 ? Hm[cc] : 0.f;
+                Ep[cc] = code[r] >= 0 ? (LTSM && off[r] ? 0.f : nv[r][cc]) : code[r] == -1 ? -Em[cc] : 0.f;
+                Hp[cc] = code[r] >= 0 ? (LTSM && off[r] ? 0.f : nv[r][3 + cc]) : code[r] == -1 ? Hm[cc] : 0.f;
             }
         }
         upwind3(&sh.sG[(t >> 2) * kGeo + 9 + 7 * (t & 3)], Em, Hm, Ep, Hp, fx);
