@@ -1848,12 +1848,29 @@ template <typename T, int Q, int NTH, int RS> struct PeriodFaces {
     // waits for the block's own mailboxes (in: this epoch's buffer)
     __device__ __forceinline__ void receive(Shared& sh, T* S, Inbox<T, RQ, NTH>& box, const unsigned long long* in,
                                             uint32_t epoch, const PeriodArgs& a, int tid) const {
-        const bool ok = box.settle(in, n, tid, epoch, a, [&](int i, int r, T v) {
+        const auto take = [&](int i, int r, T v) {
             int src, rcv = (int)(mlds[r < RQ ? r : 0] >> 16);
             uint32_t dst;
             if (r >= RQ) mail(sh, i, src, dst, rcv);
             S[rcv] = v;
-        });
+        };
+        bool ok;
+        if constexpr (Q == 1) {
+            // values beyond the tracked ones are requested before those are waited
+            // for (randomly numbered 1296 tets FP64: 1.87 -> 1.59 us a stage; cube
+            // order, where there are none, 1.41 -> 1.35.  P2 and P3, which track
+            // more: 4.2 -> 4.9 and 5.2 -> 5.8 us)
+            constexpr int RX = (8 * CF + NTH - 1) / NTH;
+            Inbox<T, RX, NTH> more;
+            if (n > NTH * RQ) more.request(in, NTH * RQ, n, tid);
+            ok = box.settle_batch(in, 0, n, tid, epoch, a, take);
+            for (int first = NTH * RQ; ok && first < n; first += NTH * RX) {
+                if (first > NTH * RQ) more.request(in, first, n, tid);
+                ok = more.settle_batch(in, first, n, tid, epoch, a, [&](int i, int, T v) { take(i, RQ, v); });
+            }
+        } else {
+            ok = box.settle(in, n, tid, epoch, a, take);
+        }
         if (!ok) sh.stop = 1;
     }
     // flux of every face node of the block (a barrier follows); geo = the

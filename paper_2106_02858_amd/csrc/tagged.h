@@ -86,30 +86,38 @@ template <typename T, int R, int NTH> struct Inbox {
             if (i < n) X::get(in + (uint32_t)i * X::W, w[r]);
         }
     }
+    // the batch requested from `first` on; r = a value's place in it
+    template <typename F>
+    __device__ __forceinline__ bool settle_batch(const unsigned long long* in, int first, int n, int tid,
+                                                 uint32_t epoch, const PeriodArgs& a, F take) {
+        unsigned long long t0 = 0;
+        for (uint32_t spin = 0;; ++spin) {
+            bool ok = true;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int i = first + tid + NTH * r;
+                if (i < n && !X::ok(w[r], epoch)) {
+                    ok = false;
+                    X::get(in + (uint32_t)i * X::W, w[r]);
+                }
+            }
+            if (__all(ok)) break;
+            if (period_stuck(a, spin, t0)) return false;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = first + tid + NTH * r;
+            if (i < n) take(i, r, X::value(w[r]));
+        }
+        return true;
+    }
     template <typename F>
     __device__ __forceinline__ bool settle(const unsigned long long* in, int n, int tid, uint32_t epoch,
                                            const PeriodArgs& a, F take) {
         for (int first = 0; first < n; first += NTH * R) {
             if (first > 0) request(in, first, n, tid);
-            unsigned long long t0 = 0;
-            for (uint32_t spin = 0;; ++spin) {
-                bool ok = true;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int i = first + tid + NTH * r;
-                    if (i < n && !X::ok(w[r], epoch)) {
-                        ok = false;
-                        X::get(in + (uint32_t)i * X::W, w[r]);
-                    }
-                }
-                if (__all(ok)) break;
-                if (period_stuck(a, spin, t0)) return false;
-            }
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int i = first + tid + NTH * r;
-                if (i < n) take(i, first == 0 ? r : R, X::value(w[r]));
-            }
+            if (!settle_batch(in, first, n, tid, epoch, a, [&](int i, int r, T v) { take(i, first == 0 ? r : R, v); }))
+                return false;
         }
         return true;
     }
