@@ -104,6 +104,7 @@ void enqueue_batch_period(Batch& bt, bool src, bool filt, hipStream_t st) {
     auto row = [&](int m, int s) { return tab + ((size_t)m * S + s) * B * kMemberParams; };
     for (int m = 0; m < bt.Mmax; ++m) {
         a.step = m;
+        a.nrun = (int)std::count_if(bt.cfg.begin(), bt.cfg.end(), [&](const StepCfg& c) { return c.M > m; });
         if (bt.scheme == 2) {
             a.mode = RK2_S1;
             a.Y = bt.U.p;
@@ -153,6 +154,7 @@ void enqueue_batch_period(Batch& bt, bool src, bool filt, hipStream_t st) {
         } else {
             a.mode = RHS;
             a.step = -1;
+            a.nrun = B;
             a.Y = bt.U.p;
             a.U = bt.U.p;
             a.Kout = bt.Kbuf.p;

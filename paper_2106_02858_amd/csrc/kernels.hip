@@ -2735,7 +2735,9 @@ template <int Q> inline dim3 tile_grid(int64_t per, unsigned members) {
 // 737 MB of accumulators, a copy's rate (scalar accesses without the hint: 360 us).
 template <typename T, int Q> int stream_hints(const StageArgs& a) {  // 2: all, 1: the filter alone
     constexpr double kCache = 256e6;
-    const double dofs = (double)a.K * 6 * Dim<Q>::NP * (a.nmembers > 1 ? a.nmembers : 1);
+    // members whose period is over keep their vectors out of it
+    const int members = a.nrun > 0 ? a.nrun : a.nmembers > 1 ? a.nmembers : 1;
+    const double dofs = (double)a.K * 6 * Dim<Q>::NP * members;
     const double vectors = dofs * (sizeof(T) == 4 ? 18 : 32);  // U, Y, Y', Acc, FP32's low parts
     return vectors > kCache ? 2 : a.filter && vectors + 16 * dofs > kCache ? 1 : 0;
 }

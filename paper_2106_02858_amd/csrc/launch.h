@@ -67,6 +67,7 @@ struct StageArgs {
     const int* active;      // member still iterating (0: its workgroups exit)
     const int* msteps;      // steps per period of each member
     int step;               // time step of this launch; -1 skips the step check
+    int nrun = 0;           // members that take this step (0: all of them)
     int64_t bstride;        // field elements between consecutive members
     int64_t gstride;        // geometry elements between members (0: shared)
     int64_t sstride;        // source elements between members
