@@ -105,7 +105,7 @@ constexpr int kMaxHarm = 8;
 constexpr int kMemberParams = 9;
 
 // A whole period in one launch, for meshes whose element blocks all fit on the
-// device at once (kernels.hip k_period_mfma, k_period_p1; kernels2d.hip k_period2d): U (and Ulo) advance M steps in
+// device at once (kernels.hip k_period_col, k_period_tile, k_period_p1; kernels2d.hip k_period2d): U (and Ulo) advance M steps in
 // place.  Member b of a batch (grid.y) offsets fields, source and filter by
 // b * bstride / sstride and the geometry by b * gstride.
 struct PeriodArgs {
