@@ -119,9 +119,9 @@ MEASURED_TRAFFIC_Q2 = [
 
 # The same for the 2-D stage kernel on the 22500-triangle disk trap (P3, FP32).
 MEASURED_TRAFFIC_2D = {
-    "kernels_sha256": "6f0bf95eeb576004fa376c2a335602ad33a1bdfacc2bbecf0b4647296d971b04",
+    "kernels_sha256": "176b032d2b818327be767ace09615e0212481100d4fa402fa48930bba752bce1",
     "kernel": "k_stage2d<float,3,true>", "K": 22500,
-    "fetch_kib": 5075.75, "fetch_scale": 2.0000, "write_kib": 4944.12, "write_scale": 1.0000,
+    "fetch_kib": 5076.50, "fetch_scale": 2.0000, "write_kib": 4944.12, "write_scale": 1.0000,
 }
 
 

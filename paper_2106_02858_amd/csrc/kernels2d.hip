@@ -368,7 +368,11 @@ __global__ __launch_bounds__(64) void k_stage2d(StageArgs args, int64_t per) {
     // ---- upwind flux of the lane's component on each edge, lifted
     auto face = [&](int f, const T (&tr)[NFP][3]) {
         const int code = sC[elc * 3 + f];
-        const T* g = &gg[4 + 6 * f];
+        // read once per edge, ahead of the branches below (P3 FP32, 30276 triangles:
+        // 9.2 us a launch; read in each branch 9.6)
+        T g[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) g[i] = gg[4 + 6 * f + i];
         T fl[NFP];
 #pragma unroll
         for (int k = 0; k < NFP; ++k) {
