@@ -7,6 +7,7 @@
 // member-wise inner products and vector updates use the same per-member
 // arithmetic and reduction order as the single-problem path, so a member's
 // result does not depend on the batch it runs in.
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -36,7 +37,7 @@ struct Batch {
     std::map<int, hipGraphExec_t> graphs;
     bool no_capture = false;  // periods without a captured graph run eagerly
     bool resident_ok = false;  // periods may run as one launch
-    DevBuf order;              // the active members
+    DevBuf order, nlive;       // the active members, longest period first; how many take step m (m = Mmax: all)
     int nactive = 0;
     std::unique_ptr<Resident> resident;
     ~Batch() {
@@ -86,6 +87,7 @@ StageArgs batch_args(Batch& bt) {
     a.nmembers = bt.B;
     a.active = bt.active.as<int>();
     a.msteps = bt.msteps.as<int>();
+    a.order = bt.order.as<int>();
     a.bstride = bt.n();
     a.gstride = bt.shared_geo ? 0 : (int64_t)geo_values(*bt.sp) * bt.sp->K;
     a.sstride = bt.n();
@@ -104,6 +106,7 @@ void enqueue_batch_period(Batch& bt, bool src, bool filt, hipStream_t st) {
     auto row = [&](int m, int s) { return tab + ((size_t)m * S + s) * B * kMemberParams; };
     for (int m = 0; m < bt.Mmax; ++m) {
         a.step = m;
+        a.nlive = bt.nlive.as<int>() + m;
         a.nrun = (int)std::count_if(bt.cfg.begin(), bt.cfg.end(), [&](const StepCfg& c) { return c.M > m; });
         if (bt.scheme == 2) {
             a.mode = RK2_S1;
@@ -154,6 +157,7 @@ void enqueue_batch_period(Batch& bt, bool src, bool filt, hipStream_t st) {
         } else {
             a.mode = RHS;
             a.step = -1;
+            a.nlive = bt.nlive.as<int>() + bt.Mmax;
             a.nrun = B;
             a.Y = bt.U.p;
             a.U = bt.U.p;
@@ -297,10 +301,17 @@ void set_active(Batch& bt, const std::vector<int>& act, hipStream_t st) {
     std::vector<int> order;
     for (int b = 0; b < bt.B; ++b)
         if (act[b]) order.push_back(b);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return bt.cfg[x].M > bt.cfg[y].M; });
     bt.nactive = (int)order.size();
+    std::vector<int> live(bt.Mmax + 1, 0);
+    for (int b : order) ++live[bt.cfg[b].M - 1];
+    for (int m = bt.Mmax - 1; m > 0; --m) live[m - 1] += live[m];
+    live[bt.Mmax] = bt.nactive;
     bt.order.alloc(bt.B * sizeof(int));
+    bt.nlive.alloc(live.size() * sizeof(int));
     if (bt.nactive)
         CMCG_HIP(hipMemcpyAsync(bt.order.p, order.data(), order.size() * sizeof(int), hipMemcpyHostToDevice, st));
+    CMCG_HIP(hipMemcpyAsync(bt.nlive.p, live.data(), live.size() * sizeof(int), hipMemcpyHostToDevice, st));
     CMCG_HIP(hipStreamSynchronize(st));
 }
 

@@ -156,12 +156,7 @@ __device__ __forceinline__ int64_t xcd_block(int64_t per) {
 // come from the member table; returns false when the member is idle (CG
 // converged, or all of its steps in this period already taken).
 template <typename T>
-__device__ __forceinline__ bool member_args(const StageArgs& in, StageArgs& a) {
-    a = in;
-    if (!in.mtab) return true;
-    const int b = blockIdx.y;
-    if (!in.active[b]) return false;
-    if (in.step >= 0 && in.step >= in.msteps[b]) return false;
+__device__ __forceinline__ void member_offsets(const StageArgs& in, int b, StageArgs& a) {
     const double* p = in.mtab + (int64_t)b * kMemberParams;
     a.cy = p[0];
     a.ca = p[1];
@@ -186,6 +181,15 @@ __device__ __forceinline__ bool member_args(const StageArgs& in, StageArgs& a) {
     if (in.Sre) a.Sre = (const T*)in.Sre + (int64_t)b * in.sstride;
     if (in.Sim) a.Sim = (const T*)in.Sim + (int64_t)b * in.sstride;
     if (in.smask) a.smask = in.smask + (int64_t)b * ((in.K + EPW - 1) / EPW);
+}
+template <typename T>
+__device__ __forceinline__ bool member_args(const StageArgs& in, StageArgs& a) {
+    a = in;
+    if (!in.mtab) return true;
+    const int b = blockIdx.y;
+    if (!in.active[b]) return false;
+    if (in.step >= 0 && in.step >= in.msteps[b]) return false;
+    member_offsets<T>(in, b, a);
     return true;
 }
 
@@ -1098,6 +1102,8 @@ template <int Q> struct TileDim {
     static constexpr int RF = (EPW * 4 * NFP + 255) / 256;                  // flux nodes per thread
     static constexpr int NTAB = NST * (TAIL ? 80 : 64);
     static constexpr bool LOOP = Q == 3;  // a workgroup runs several blocks
+    // waves per SIMD that the registers allow, so workgroups per compute unit
+    static constexpr int occ(bool ltsm) { return Q == 3 ? (ltsm ? 2 : 3) : ltsm ? 4 : 5; }
 };
 // A operands [step][lane] of rows 0 .. 15 (lane l: row l % 16, K row l / 16),
 // behind them [step][16] of rows 16 .. 19 (entry 4 k + i).
@@ -1240,23 +1246,37 @@ template <int Q> struct TileIn {
 };
 
 template <int Q, bool MH, bool LTSM, int STREAM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 3 ? (LTSM ? 2 : 3) : LTSM ? 4 : 5, 8)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TileDim<Q>::occ(LTSM), 8)))
 void k_stage_tile(StageArgs args, int64_t per) {
     using TD = TileDim<Q>;
     constexpr int NP = TD::NP, NFP = TD::NFP, RS = TD::RS, FS = TD::FS, NTH = 256, RF = TD::RF;
     constexpr bool LOOP = TD::LOOP;
     __shared__ __align__(16) TileShared<Q> sh;
 
+    // the workgroup's blocks: index, index + step, .. of its XCD's range, of one
+    // member: a batch's workgroups are dealt out to the members that take the step
+    int index = blockIdx.x >> 3, step = gridDim.x >> 3;
     StageArgs a;
-    if (!member_args<double>(args, a)) return;  // uniform per workgroup
-    // the blocks of this workgroup: index, index + gridDim.x / 8, .. of its XCD's range
+    if constexpr (LOOP) {
+        a = args;
+        if (args.mtab) {
+            const int live = *args.nlive;
+            if (live == 0) return;
+            const int m = index % live;
+            step = (step - m + live - 1) / live;
+            index /= live;
+            member_offsets<double>(args, args.order[m], a);
+        }
+    } else if (!member_args<double>(args, a)) {
+        return;  // uniform per workgroup
+    }
     const int64_t nblk = a.blist ? a.nblist : (a.K + EPW - 1) / EPW;
     const int64_t lo = (blockIdx.x & 7) * per, hi = lo + per < nblk ? lo + per : nblk;
     const double* __restrict__ Y = (const double*)a.Y;
     int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    for (int64_t at = lo + (blockIdx.x >> 3); at < hi; at += gridDim.x >> 3) {
+    for (int64_t at = lo + index; at < hi; at += step) {
         // what depends on the thread alone is formed anew for every block: kept
         // across blocks it would take the registers of the loads in flight
         if constexpr (LOOP) asm volatile("" : "+v"(tid));
@@ -1268,7 +1288,7 @@ void k_stage_tile(StageArgs args, int64_t per) {
         const int nvv = ne * 6 * NP / 2;  // 16-byte groups of the block's rows
 
         // ---- every load that depends on no other; the tables with the first block
-        const bool first = !LOOP || at < lo + (gridDim.x >> 3);
+        const bool first = !LOOP || at < lo + step;
         constexpr int NM = LOOP ? (TD::NTAB + NTH - 1) / NTH : 1;
         uint32_t tw;
         double m[NM];
@@ -2713,13 +2733,20 @@ inline int grid_for(int64_t n, int threads = 256) {
     return (int)g;
 }
 
-// Grid of k_stage_tile.  P3: what the device holds at once (three workgroups per
-// compute unit, 32 compute units per XCD), each running several blocks where
-// there are more.
-template <int Q> inline dim3 tile_grid(int64_t per, unsigned members) {
-    int64_t n = per;
-    if (TileDim<Q>::LOOP && n > 96 / (int64_t)members) n = 96 / members;
-    return dim3((unsigned)(8 * (n < 1 ? 1 : n)), members);
+// Grid of k_stage_tile.  P3, single problems: what the device holds at once
+// (occ workgroups per compute unit, 32 compute units per XCD), each running
+// several blocks where there are more.  Batches: twice as many, dealt out on
+// the device to the members that take the step, so that members which have
+// converged or have fewer steps leave no part of the device idle; the second
+// round evens out what the division leaves over.  A fixed share per member
+// against this (ms a solve): 16 members of 10368 tets 366 / 366, one of them with
+// six times the steps 1340 / 550; 64 of 3072 397 / 338, 1428 / 404.  Three or four
+// rounds cost 1-6 % (the matrix table is read by more workgroups).
+template <int Q> inline dim3 tile_grid(int64_t per, unsigned members, int occ) {
+    if (!TileDim<Q>::LOOP) return dim3((unsigned)(8 * per), members);
+    const int64_t n = per * members, held = 32 * occ;
+    const int64_t most = members == 1 ? held : 2 * held > members ? 2 * held : members;
+    return dim3((unsigned)(8 * (n < most ? n : most)));
 }
 
 // Non-temporal hints for what the update pass reads and writes once per launch,
@@ -2747,7 +2774,7 @@ void stage_launch_mfma(const StageArgs& a, dim3 grid, int64_t per, int precision
     if (precision == CMCG_FP32)
         hipLaunchKernelGGL((k_stage_col<Q, MH, false, STREAM>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
     else
-        hipLaunchKernelGGL((k_stage_tile<Q, MH, false, STREAM>), tile_grid<Q>(per, grid.y), dim3(256), 0, s, a, per);
+        hipLaunchKernelGGL((k_stage_tile<Q, MH, false, STREAM>), tile_grid<Q>(per, grid.y, TileDim<Q>::occ(false)), dim3(256), 0, s, a, per);
 }
 
 template <typename T, int Q, bool MH>
@@ -2784,7 +2811,7 @@ void stage_launch(const StageArgs& a, hipStream_t s) {
         if constexpr (Q >= 2 && std::is_same<T, float>::value)
             hipLaunchKernelGGL((k_stage_col<Q, false, true, 0>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
         else if constexpr (Q >= 2)
-            hipLaunchKernelGGL((k_stage_tile<Q, false, true, 0>), tile_grid<Q>(per, 1), dim3(256), 0, s, a, per);
+            hipLaunchKernelGGL((k_stage_tile<Q, false, true, 0>), tile_grid<Q>(per, 1, TileDim<Q>::occ(true)), dim3(256), 0, s, a, per);
         else
             hipLaunchKernelGGL((k_stage<T, Q, false, false, true>), grid, dim3(64), 0, s, a, per);
         return;

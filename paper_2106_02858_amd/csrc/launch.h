@@ -68,6 +68,8 @@ struct StageArgs {
     const int* msteps;      // steps per period of each member
     int step;               // time step of this launch; -1 skips the step check
     int nrun = 0;           // members that take this step (0: all of them)
+    const int* order;       // the active members, those with the most steps first ...
+    const int* nlive;       // ... and how many of them take this step (device memory: it outlives a capture)
     int64_t bstride;        // field elements between consecutive members
     int64_t gstride;        // geometry elements between members (0: shared)
     int64_t sstride;        // source elements between members
