@@ -2750,23 +2750,25 @@ template <int Q> inline dim3 tile_grid(int64_t per, unsigned members, int occ) {
 }
 
 // Non-temporal hints for what the update pass reads and writes once per launch,
-// where the vectors of a launch exceed the 256 MB Infinity Cache anyway: the
-// stage input's planes, whose face traces the neighbouring blocks read, then
-// stay in the caches.  With and without (us per launch): FP32 P2 384000 tets (415
-// MB) 105.9 / 111.0, P3 196608 (425 MB) 131.9 / 134.8, FP64 P2 196608 (377 MB)
-// 111 / 117, FP64 P3 82944 (319 MB) 94.1 / 95.6; below the line the hint sends to
-// memory what the cache would have held: FP32 P2 196608 (212 MB) 55.6 / 49.1, P3
-// 48000 (104 MB) 34.3 / 30.6, FP64 P3 48000 (184 MB) 55.0 / 50.0.  The filter's
+// where the vectors of a launch exceed the 256 MB Infinity Cache by so much that
+// it holds little of them anyway: the stage input's planes, whose face traces
+// the neighbouring blocks read, then stay in the caches.  With and without (us
+// per launch): FP32 P2 279936 tets (302 MB) 83.4 / 84.5, 384000 (415 MB) 105.9 /
+// 111.0, P3 162000 (350 MB) 112.5 / 114.1, 196608 (425 MB) 131.9 / 134.8, FP64 P2
+// 196608 (377 MB) 111 / 117, FP64 P3 82944 (319 MB) 94.1 / 95.6; below the line the
+// hint sends to memory what the cache would have held: FP32 P2 196608 (212 MB)
+// 55.6 / 49.1, P3 48000 (104 MB) 34.3 / 30.6, 131712 (284 MB) 91.6 / 85.5, FP64 P3
+// 48000 (184 MB) 55.0 / 50.0.  The filter's
 // accumulators (16 B per value, read and written once per step) count as vectors
 // of their own; a filtered launch of P2 384000 tets takes 265 us, 142 of them for
 // 737 MB of accumulators, a copy's rate (scalar accesses without the hint: 360 us).
 template <typename T, int Q> int stream_hints(const StageArgs& a) {  // 2: all, 1: the filter alone
-    constexpr double kCache = 256e6;
+    constexpr double kLine = 300e6;
     // members whose period is over keep their vectors out of it
     const int members = a.nrun > 0 ? a.nrun : a.nmembers > 1 ? a.nmembers : 1;
     const double dofs = (double)a.K * 6 * Dim<Q>::NP * members;
     const double vectors = dofs * (sizeof(T) == 4 ? 18 : 32);  // U, Y, Y', Acc, FP32's low parts
-    return vectors > kCache ? 2 : a.filter && vectors + 16 * dofs > kCache ? 1 : 0;
+    return vectors > kLine ? 2 : a.filter && vectors + 16 * dofs > kLine ? 1 : 0;
 }
 
 template <int Q, bool MH, int STREAM>
