@@ -383,6 +383,10 @@ int cmcg_debug_dot(cmcg_problem* p, const double* u_dev, const double* v_dev, do
  * FP64 device arrays; synchronous on return.  Errors: CMCG_ERR_ARG (NULL,
  * unknown precision). */
 int cmcg_debug_mfma(int precision, const double* a_dev, const double* b_dev, double* d_dev, hipStream_t stream);
+/* Periods run as one launch (use_graph) on the current device since the
+ * process started: *done ran to their end (a batch's period counts once),
+ * *restarted were begun again from their start state, by stage launches. */
+int cmcg_debug_period_counts(int64_t* done, int64_t* restarted);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the inner

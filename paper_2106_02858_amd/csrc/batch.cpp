@@ -262,7 +262,10 @@ void batch_apply(Batch& bt, const cmcg_options* o, const double* X, double* Yo, 
     };
     start();
     if (!resident_batch_period(bt, src && direction > 0, filt, o->use_graph != 0, st)) {
-        if (bt.resident && bt.resident->off) start();  // a launch that gave up left no state
+        if (bt.resident && bt.resident->off) {  // a launch that gave up left no state
+            start();
+            ++period_counts(s.device).restarted;
+        }
         run_batch_period(bt, src && direction > 0, filt, o->use_graph != 0, st);
     }
     if (Yo) from_field_dim(s, bt.U.p, bt.Ulo.p, Yo, sub, N, flip, st);

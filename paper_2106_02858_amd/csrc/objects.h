@@ -2,6 +2,7 @@
 // drivers (not part of the ABI).
 #pragma once
 
+#include <atomic>
 #include <chrono>
 #include <complex>
 #include <functional>
@@ -118,6 +119,13 @@ struct Resident {
     int tab_M = 0, tab_scheme = 0;
     bool off = false;        // does not fit on this device, or a launch has given up
 };
+
+// One-launch periods of a device since the process started.
+struct PeriodCounts {
+    std::atomic<int64_t> done{0};       // ran to their end
+    std::atomic<int64_t> restarted{0};  // begun again from their start state, by stage launches
+};
+PeriodCounts& period_counts(int device);
 
 }  // namespace cmcg
 

@@ -673,10 +673,13 @@ namespace {
 struct ResidentTurn {
     std::mutex mu;
     hipEvent_t last = nullptr;
+    PeriodCounts counts;
 };
 ResidentTurn g_resident[64];
 constexpr double kResidentWait = 2.0;  // seconds a workgroup waits for a neighbour before it gives up
 }  // namespace
+
+PeriodCounts& period_counts(int device) { return g_resident[device].counts; }
 
 // whether the variant of (q, precision) was chosen through cmcg_tune_stage (the
 // autotuner's choice between stage launches leaves the one-launch periods on)
@@ -768,6 +771,7 @@ bool run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t s
     }
     CMCG_HIP(hipStreamSynchronize(st));
     r.off = *failed != 0;
+    if (!r.off) ++period_counts(s.device).done;
     return !r.off;
 }
 
@@ -880,7 +884,10 @@ void apply_period(cmcg_problem* p, const StepCfg& c, const cmcg_options* o, cons
     };
     start();
     if (!resident_period(p, c, src && direction > 0, filt, o->use_graph != 0, st)) {
-        if (c.resident && p->resident && p->resident->off) start();  // a launch that gave up left no state
+        if (c.resident && p->resident && p->resident->off) {  // a launch that gave up left no state
+            start();
+            ++period_counts(s.device).restarted;
+        }
         run_period(p, c, src && direction > 0, filt, o->use_graph != 0, st);
     }
     if (Yo) from_field_dim(s, p->U.p, p->Ulo.p, Yo, sub, s.ndof, flip, st);
@@ -1780,6 +1787,16 @@ int cmcg_debug_mfma(int precision, const double* a, const double* b, double* d, 
     if (precision != CMCG_FP64 && precision != CMCG_FP32) fail(CMCG_ERR_ARG, "debug_mfma: unknown precision");
     launch_mfma_probe(precision, a, b, d, stream);
     CMCG_HIP(hipStreamSynchronize(stream));
+    return CMCG_OK;
+    CMCG_GUARD_END
+}
+
+int cmcg_debug_period_counts(int64_t* done, int64_t* restarted) {
+    CMCG_GUARD_BEGIN
+    if (!done || !restarted) fail(CMCG_ERR_ARG, "debug_period_counts: NULL argument");
+    const PeriodCounts& c = period_counts(current_device());
+    *done = c.done;
+    *restarted = c.restarted;
     return CMCG_OK;
     CMCG_GUARD_END
 }

@@ -1,0 +1,51 @@
+"""Which periods run as one launch: the library's own count of them.  Results
+do not tell (they equal those of stage launches, bit for bit; see
+test_gpu_resident.py), so the tests here ask the counters."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from paper_2106_02858_amd import inputs
+from tests.test_gpu_resident import _member, _mesh2d, _mesh3d, _problem
+
+pytestmark = pytest.mark.gpu
+
+
+def _period(lib, p, K, comps, Np, n=1, **kw):
+    """n forward periods; how many of them (ran as one launch, were restarted)."""
+    import torch
+    U = torch.tensor(np.random.default_rng(3).standard_normal((K, comps, Np)), device="cuda")
+    V = torch.zeros_like(U)
+    a = lib.cmcg_debug_period_counts()
+    for _ in range(n):
+        lib.cmcg_debug_period(p, U, V, 1, True, opts=lib.cmcg_options_default(**kw))
+    b = lib.cmcg_debug_period_counts()
+    assert torch.isfinite(V).all()
+    return tuple(y - x for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("dim,q", [(2, 1), (2, 2), (2, 3), (3, 2), (3, 3)])
+@pytest.mark.parametrize("kind", [43, "shuffled"])
+def test_small_meshes_run_as_one_launch(lib, kind, dim, q, precision):
+    print(f"one launch dim={dim} q={q} prec={precision} {kind}", flush=True)
+    mesh = (_mesh2d if dim == 2 else _mesh3d)(kind)
+    s, p = _problem(lib, dim, mesh, q, precision, seed=4)
+    K, Np, comps = len(mesh[1]), lib.cmcg_space_info(s)["Np"], 3 if dim == 2 else 6
+    assert _period(lib, p, K, comps, Np, n=2) == (2, 0)
+    assert _period(lib, p, K, comps, Np, scheme=4 if q == 1 else 2) == (1, 0)
+    assert _period(lib, p, K, comps, Np, use_graph=0) == (0, 0)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_batch2d_periods_run_as_one_launch(lib, precision):
+    print(f"one launch 2-D batch prec={precision}", flush=True)
+    xy, tri, tags = inputs.cartesian_triangles(12, 9)
+    s = lib.cmcg_space_create(lib.cmcg_mesh2d_create(xy, tri, tags), 3, precision)
+    probs = [_member(lib, s, 2, len(tri), 3, np.random.default_rng(b), 20.0 + b) for b in range(6)]
+    a = lib.cmcg_debug_period_counts()
+    res = lib.cmcg_solve_batch(probs, lib.cmcg_options_default(fixed_iters=2))
+    b = lib.cmcg_debug_period_counts()
+    periods = lib.cmcg_result_stats(res[0])["periods"]
+    assert (b[0] - a[0], b[1] - a[1]) == (periods, 0)
