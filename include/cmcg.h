@@ -489,7 +489,7 @@ int cmcg_engine_collect_batch(cmcg_engine* e, int slot, cmcg_result** results, i
  * timings favour there.  All compute the same Phi(t, Y) and stage update.
  * A whole period may also run as one launch with the stage kernels' arithmetic
  * (use_graph, meshes whose element blocks fit on the device at once) unless a
- * variant was set here.
+ * variant other than the default was set here.
  * Defaults: -1 for q = 2, 3, 0 for q = 1.  Process-wide;
  * not thread-safe against concurrent solves.  Returns CMCG_ERR_ARG for an unknown q / precision /
  * variant.  cmcg_tune_get_stage reports the current choice (possibly -1);

@@ -688,6 +688,8 @@ static bool& stage_by_hand(int q, int precision) {
     return by_hand[q][precision];
 }
 
+static int default_stage_variant(int q) { return q == 1 ? 0 : -1; }
+
 bool resident_variant(const SpaceData& s) {
     if (s.dim == 2) return true;
     if (stage_by_hand(s.q, s.precision)) return false;
@@ -1807,7 +1809,8 @@ int cmcg_tune_stage(int q, int precision, int variant) {
         variant >= kStageVariants)
         fail(CMCG_ERR_ARG, "tune_stage: bad q, precision or variant");
     set_stage_variant(q, precision, variant);
-    stage_by_hand(q, precision) = variant >= 0;
+    // the default put back (as a caller does with what cmcg_tune_get_stage told it) is no choice
+    stage_by_hand(q, precision) = variant >= 0 && variant != default_stage_variant(q);
     return CMCG_OK;
     CMCG_GUARD_END
 }

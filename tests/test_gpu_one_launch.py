@@ -49,3 +49,21 @@ def test_batch2d_periods_run_as_one_launch(lib, precision):
     b = lib.cmcg_debug_period_counts()
     periods = lib.cmcg_result_stats(res[0])["periods"]
     assert (b[0] - a[0], b[1] - a[1]) == (periods, 0)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("q", [1, 2, 3])
+def test_default_stage_variant_put_back(lib, q, precision):
+    """A variant set by hand keeps periods on its stage launches; the default
+    put back, as read before, gives the one-launch periods back."""
+    print(f"tune q={q} prec={precision}", flush=True)
+    mesh = _mesh3d("shuffled")
+    s, p = _problem(lib, 3, mesh, q, precision, seed=6)
+    K, Np = len(mesh[1]), lib.cmcg_space_info(s)["Np"]
+    saved = lib.cmcg_tune_get_stage(q, precision)
+    try:
+        lib.cmcg_tune_stage(q, precision, 1)
+        assert _period(lib, p, K, 6, Np) == (0, 0)
+    finally:
+        lib.cmcg_tune_stage(q, precision, saved)
+    assert _period(lib, p, K, 6, Np) == (1, 0)
