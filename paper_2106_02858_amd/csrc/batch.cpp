@@ -208,10 +208,10 @@ void run_batch_period(Batch& bt, bool src, bool filt, bool use_graph, hipStream_
     CMCG_HIP(hipGraphLaunch(batch_graph(bt, src, filt), st));
 }
 
-// The period of every active member as one launch; false when it has to run
-// by stage launches.
-bool resident_batch_period(Batch& bt, bool src, bool filt, bool use_graph, hipStream_t st) {
-    if (!use_graph || !bt.resident_ok || (bt.resident && bt.resident->off) || !resident_variant(*bt.sp)) return false;
+// The period of every active member as one launch, where that may be.
+Period resident_batch_period(Batch& bt, bool src, bool filt, bool use_graph, hipStream_t st) {
+    if (!use_graph || !bt.resident_ok || (bt.resident && bt.resident->off) || !resident_variant(*bt.sp))
+        return Period::kRefused;
     if (!bt.resident) bt.resident.reset(new Resident());
     PeriodArgs a{};
     a.U = bt.U.p;
@@ -239,11 +239,11 @@ bool resident_batch_period(Batch& bt, bool src, bool filt, bool use_graph, hipSt
         launch_zero(bt.Fre.p, bt.Fre.bytes, st);
         launch_zero(bt.Fim.p, bt.Fim.bytes, st);
     }
-    if (!run_resident(*bt.resident, *bt.sp, a, bt.nactive, st)) return false;
-    if (filt && bt.scheme == 2)
+    const Period done = run_resident(*bt.resident, *bt.sp, a, bt.nactive, st);
+    if (done == Period::kRan && filt && bt.scheme == 2)
         launch_filter_add_batch(bt.sp->precision, bt.U.p, bt.fw_re.as<double>(), bt.fw_im.as<double>(),
                                 bt.Fre.as<double>(), bt.Fim.as<double>(), bt.n(), bt.B, st);
-    return true;
+    return done;
 }
 
 // Y_b = S^d P_b S^d X_b - sub_b for every member (X == nullptr: zero state)
@@ -261,13 +261,12 @@ void batch_apply(Batch& bt, const cmcg_options* o, const double* X, double* Yo, 
         }
     };
     start();
-    if (!resident_batch_period(bt, src && direction > 0, filt, o->use_graph != 0, st)) {
-        if (bt.resident && bt.resident->off) {  // a launch that gave up left no state
-            start();
-            ++period_counts(s.device).restarted;
-        }
-        run_batch_period(bt, src && direction > 0, filt, o->use_graph != 0, st);
+    const Period done = resident_batch_period(bt, src && direction > 0, filt, o->use_graph != 0, st);
+    if (done == Period::kGaveUp) {
+        start();
+        ++period_counts(s.device).restarted;
     }
+    if (done != Period::kRan) run_batch_period(bt, src && direction > 0, filt, o->use_graph != 0, st);
     if (Yo) from_field_dim(s, bt.U.p, bt.Ulo.p, Yo, sub, N, flip, st);
 }
 

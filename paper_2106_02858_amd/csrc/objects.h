@@ -117,7 +117,13 @@ struct Resident {
     HostPinned failed{1};    // [0]: set by a launch that gave up
     uint32_t epoch = 0;      // the last one used
     int tab_M = 0, tab_scheme = 0;
-    bool off = false;        // does not fit on this device, or a launch has given up
+    int fits = 0, refused = 0;  // members: the most found to fit, the fewest found not to (0: none)
+    bool off = false;        // no room for the exchange, or a launch has given up
+};
+enum class Period {
+    kRan,      // to its end
+    kRefused,  // nothing was launched
+    kGaveUp,   // the launch gave up: its state is void
 };
 
 // One-launch periods of a device since the process started.
@@ -231,11 +237,9 @@ void build_geo(cmcg_problem* p, double alpha);
 // row (step Mmax, stage 0) with its last filter level, into rows
 // [step][stage][member][kMemberParams] of tab (StageArgs::mtab, PeriodArgs::mtab).
 void fill_step_table(std::vector<double>& tab, int B, int b, int Mmax, const StepCfg& c, double omega);
-// One period of a.M steps of n members as one launch on st (PeriodArgs), waited for: true when the
-// launch ran to its end (a.U then holds the result); false when nothing ran
-// or the launch gave up (a.U is then void, r.off is set).  a's exchange
-// fields are filled in here.
-bool run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t st);
+// One period of a.M steps of n members as one launch on st (PeriodArgs), waited
+// for.  a's exchange fields are filled in here.
+Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t st);
 // Whether the current stage variant of a space leaves its periods to
 // run_resident (none chosen by hand, and the arithmetic is the same).
 bool resident_variant(const SpaceData& s);

@@ -718,20 +718,23 @@ static void build_mailboxes(SpaceData& s, hipStream_t st) {
     s.next = n;
 }
 
-bool run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t st) {
-    if (r.off) return false;
+Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t st) {
+    if (r.off || (r.refused && n >= r.refused)) return Period::kRefused;
     const auto launch = [&] {
         return s.dim == 2 ? launch_period2d(s.q, s.precision, a, n, st) : launch_period(s.q, s.precision, a, n, st);
     };
-    if (!r.xch.p && !launch()) {  // does not fit on the device: no mailboxes are numbered
-        r.off = true;
-        return false;
+    if (n > r.fits) {
+        if (!launch()) {  // only whether they fit: no mailboxes are numbered yet
+            r.refused = n;
+            return Period::kRefused;
+        }
+        r.fits = n;
     }
     std::call_once(s.x_once, [&] { build_mailboxes(s, st); });
     const size_t vals = (size_t)a.members * s.next * (s.dim == 2 ? 3 : 6) * s.Nfp;
     if (vals > (size_t)kPeriodMaxValues) {
         r.off = true;
-        return false;
+        return Period::kRefused;
     }
     const size_t pairs = 2 * vals * (s.precision == CMCG_FP64 ? 2 : 1);
     const uint64_t need = (uint64_t)a.M * 4 + 8;
@@ -740,7 +743,7 @@ bool run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t s
             r.xch.alloc(pairs * 8 + 64);
         } catch (const Error&) {
             r.off = true;  // no room for the exchange: stage launches need none
-            return false;
+            return Period::kRefused;
         }
         launch_zero(r.xch.p, r.xch.bytes, st);
         r.epoch = 0;
@@ -765,23 +768,24 @@ bool run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t s
             CMCG_HIP(hipEventCreateWithFlags(&turn.last, hipEventDisableTiming));
         else
             CMCG_HIP(hipStreamWaitEvent(st, turn.last, 0));
-        if (!launch()) {
-            r.off = true;
-            return false;
-        }
+        if (!launch()) fail(CMCG_ERR_STATE, "a period that fitted on the device no longer does");
         CMCG_HIP(hipEventRecord(turn.last, st));
     }
     CMCG_HIP(hipStreamSynchronize(st));
-    r.off = *failed != 0;
-    if (!r.off) ++period_counts(s.device).done;
-    return !r.off;
+    if (*failed) {
+        r.off = true;
+        return Period::kGaveUp;
+    }
+    ++period_counts(s.device).done;
+    return Period::kRan;
 }
 
-// One period of p as one launch; false when it has to run by stage launches.
-static bool resident_period(cmcg_problem* p, const StepCfg& c, bool src, bool filt, bool use_graph, hipStream_t st) {
+// One period of p as one launch, where that may be.
+static Period resident_period(cmcg_problem* p, const StepCfg& c, bool src, bool filt, bool use_graph, hipStream_t st) {
     SpaceData& s = *p->sp;
-    if (!c.resident || !use_graph || p->nharm != 1 || (p->resident && p->resident->off) || !resident_variant(s))
-        return false;
+    if (!c.resident || !use_graph || p->nharm != 1 || (p->resident && (p->resident->off || p->resident->refused)) ||
+        !resident_variant(s))
+        return Period::kRefused;
     if (!p->resident) p->resident.reset(new Resident());
     Resident& r = *p->resident;
     if (r.tab_M != c.M || r.tab_scheme != c.scheme) {
@@ -817,10 +821,10 @@ static bool resident_period(cmcg_problem* p, const StepCfg& c, bool src, bool fi
         launch_zero(p->Fre.p, p->Fre.bytes, st);
         launch_zero(p->Fim.p, p->Fim.bytes, st);
     }
-    if (!run_resident(r, s, a, 1, st)) return false;
-    if (filt && c.scheme == 2)  // last level t_M = T: e^{-i w T} = 1
+    const Period done = run_resident(r, s, a, 1, st);
+    if (done == Period::kRan && filt && c.scheme == 2)  // last level t_M = T: e^{-i w T} = 1
         launch_filter_add(s.precision, p->U.p, 1.0 / c.M, 0.0, p->Fre.as<double>(), p->Fim.as<double>(), s.ndof, st);
-    return true;
+    return done;
 }
 
 // One LTS period (forward with or without source and filter, or the adjoint).
@@ -885,13 +889,12 @@ void apply_period(cmcg_problem* p, const StepCfg& c, const cmcg_options* o, cons
         }
     };
     start();
-    if (!resident_period(p, c, src && direction > 0, filt, o->use_graph != 0, st)) {
-        if (c.resident && p->resident && p->resident->off) {  // a launch that gave up left no state
-            start();
-            ++period_counts(s.device).restarted;
-        }
-        run_period(p, c, src && direction > 0, filt, o->use_graph != 0, st);
+    const Period done = resident_period(p, c, src && direction > 0, filt, o->use_graph != 0, st);
+    if (done == Period::kGaveUp) {
+        start();
+        ++period_counts(s.device).restarted;
     }
+    if (done != Period::kRan) run_period(p, c, src && direction > 0, filt, o->use_graph != 0, st);
     if (Yo) from_field_dim(s, p->U.p, p->Ulo.p, Yo, sub, s.ndof, flip, st);
 }
 

@@ -67,3 +67,35 @@ def test_default_stage_variant_put_back(lib, q, precision):
     finally:
         lib.cmcg_tune_stage(q, precision, saved)
     assert _period(lib, p, K, 6, Np) == (1, 0)
+
+
+def test_mesh_that_does_not_fit_is_not_restarted(lib):
+    """24576 P1 FP64 tets do not fit on the device at once: their periods run
+    by stage launches, each from the one start state written for it."""
+    print("one launch: too large", flush=True)
+    mesh = inputs.cube_mesh(16)
+    s, p = _problem(lib, 3, mesh, 1, 0, seed=2)
+    assert _period(lib, p, len(mesh[1]), 6, 4, n=3, steps=120) == (0, 0)
+
+
+def test_batch_members_left_run_as_one_launch(lib):
+    """24 members of 750 P1 FP64 tets (75 blocks each) do not fit together; the
+    few that are still to converge do."""
+    print("one launch: batch members left", flush=True)
+    xyz, tet, tags = inputs.cube_mesh(5)
+    s = lib.cmcg_space_create(lib.cmcg_mesh_create(xyz, tet, tags), 1, 0)
+    probs = [_member(lib, s, 3, len(tet), 1, np.random.default_rng(b), 4.0 if b < 22 else 30.0) for b in range(24)]
+    o = lib.cmcg_options_default(tol=0.2, max_iter=25)
+    a = lib.cmcg_debug_period_counts()
+    res = [lib.cmcg_result_stats(r) for r in lib.cmcg_solve_batch(probs, o)]
+    b = lib.cmcg_debug_period_counts()
+    alone = [lib.cmcg_result_stats(lib.cmcg_solve(q, lib.cmcg_options_default(tol=0.2, max_iter=25, use_graph=0)))
+             for q in probs]
+    assert [r["iters"] for r in res] == [r["iters"] for r in alone]
+    assert [r["rel_res"] for r in res] == [r["rel_res"] for r in alone]
+    iters = sorted(r["iters"] for r in res)
+    assert iters[0] < iters[-1]  # the members do converge apart
+    print(f"  iterations {iters}, one-launch periods {b[0] - a[0]}")
+    # the members in the last iterations are few enough to fit (3 workgroups per compute unit, 80 slots each)
+    few = sum(1 for i in range(iters[-1]) if sum(1 for r in res if r["iters"] > i) * 80 <= 512)
+    assert b[0] - a[0] >= 2 * few > 0 and b[1] == a[1]
