@@ -100,7 +100,10 @@ typedef struct cmcg_options {
                             problems whose element blocks fit on the device at
                             once, outside the serving engine) or replay it
                             from a captured hipGraph; 0: launch its stages one
-                            by one.  The results are the same, bit for bit      */
+                            by one.  The results are the same, bit for bit.  A
+                            one-launch period that cannot get all of its blocks
+                            onto the device is run by stage launches after 2 s,
+                            and so are the device's periods for a minute then   */
     int residual_refresh;/* > 0: every this many iterations replace R by the
                             true gradient (costs two periods); <= 0 = never.
                             FP32 fields keep the state compensated (FP32 +
@@ -387,6 +390,13 @@ int cmcg_debug_mfma(int precision, const double* a_dev, const double* b_dev, dou
  * process started: *done ran to their end (a batch's period counts once),
  * *restarted were begun again from their start state, by stage launches. */
 int cmcg_debug_period_counts(int64_t* done, int64_t* restarted);
+/* For tests: one-launch periods of p (and of batches whose first member is p)
+ * leave some element blocks out, as if these found no room on the device, and
+ * the others give up after waiting `seconds` (0 < seconds <= 2) for them; the
+ * period then runs by stage launches, and for a minute so do all of the
+ * device's.  0: back to normal.  Either way periods run as one launch again at
+ * once.  Errors: CMCG_ERR_ARG (NULL, seconds, fewer than nine element blocks). */
+int cmcg_debug_period_stall(cmcg_problem* p, double seconds);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the inner

@@ -52,7 +52,7 @@ EXPORTED = [
     "cmcg_problem_create_harmonics", "cmcg_result_harmonics", "cmcg_result_filtered_harmonic_device",
     "cmcg_solve", "cmcg_fw_solve", "cmcg_solve_batch", "cmcg_result_fields", "cmcg_result_filtered_device", "cmcg_result_initial_device",
     "cmcg_result_stats", "cmcg_result_history", "cmcg_result_destroy",
-    "cmcg_debug_rhs", "cmcg_debug_period", "cmcg_debug_step", "cmcg_debug_dot", "cmcg_debug_dot_noalloc", "cmcg_debug_mfma", "cmcg_debug_period_counts", "cmcg_tune_stage", "cmcg_tune_get_stage", "cmcg_tune_resolve_stage",
+    "cmcg_debug_rhs", "cmcg_debug_period", "cmcg_debug_step", "cmcg_debug_dot", "cmcg_debug_dot_noalloc", "cmcg_debug_mfma", "cmcg_debug_period_counts", "cmcg_debug_period_stall", "cmcg_tune_stage", "cmcg_tune_get_stage", "cmcg_tune_resolve_stage",
     "cmcg_autotune_stage", "cmcg_autotune_batch", "cmcg_mesh_locality_order",
     "cmcg_problem_footprint", "cmcg_engine_create", "cmcg_engine_destroy", "cmcg_engine_admit",
     "cmcg_engine_step", "cmcg_engine_poll", "cmcg_engine_collect", "cmcg_engine_cancel", "cmcg_engine_info",
@@ -106,6 +106,7 @@ _sig = {
     "cmcg_debug_dot_noalloc": (C.c_int, [P, P, P, P, P]),
     "cmcg_debug_mfma": (C.c_int, [C.c_int, P, P, P, P]),
     "cmcg_debug_period_counts": (C.c_int, [C.POINTER(C.c_int64)] * 2),
+    "cmcg_debug_period_stall": (C.c_int, [P, C.c_double]),
     "cmcg_problem_lts_fine": (C.c_int, [P, C.POINTER(cmcg_options), P, C.POINTER(C.c_int64)]),
     "cmcg_problem_destroy": (None, [P]),
     "cmcg_problem_steps": (C.c_int, [P, C.POINTER(cmcg_options), C.POINTER(C.c_int), D]),
@@ -468,6 +469,11 @@ def cmcg_debug_period_counts() -> tuple[int, int]:
     c = [C.c_int64(), C.c_int64()]
     _check(_lib.cmcg_debug_period_counts(*map(C.byref, c)))
     return tuple(x.value for x in c)
+
+
+def cmcg_debug_period_stall(p: Problem, seconds: float):
+    """For tests: one-launch periods of p leave blocks out and give up after `seconds` (0: back to normal)."""
+    _check(_lib.cmcg_debug_period_stall(p.h, float(seconds)))
 
 
 def cmcg_tune_stage(q: int, precision: int, variant: int):

@@ -239,7 +239,7 @@ Period resident_batch_period(Batch& bt, bool src, bool filt, bool use_graph, hip
         launch_zero(bt.Fre.p, bt.Fre.bytes, st);
         launch_zero(bt.Fim.p, bt.Fim.bytes, st);
     }
-    const Period done = run_resident(*bt.resident, *bt.sp, a, bt.nactive, st);
+    const Period done = run_resident(*bt.resident, *bt.sp, a, bt.nactive, bt.P[0]->stall, st);
     if (done == Period::kRan && filt && bt.scheme == 2)
         launch_filter_add_batch(bt.sp->precision, bt.U.p, bt.fw_re.as<double>(), bt.fw_im.as<double>(),
                                 bt.Fre.as<double>(), bt.Fim.as<double>(), bt.n(), bt.B, st);

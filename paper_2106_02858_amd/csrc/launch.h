@@ -140,6 +140,7 @@ struct PeriodArgs {
     uint32_t* abort;         // device word: the epoch of a launch that gives up
     int* failed;             // host-visible: set to 1 when the launch gave up (its output is then void)
     unsigned long long limit;  // longest wait for a neighbour, in wall-clock ticks
+    int left_out = 0;          // host: blocks at the end of each XCD's range that are not launched (tests)
 };
 constexpr int64_t kPeriodMaxValues = 1 << 26;  // exchanged values of one buffer (32-bit offsets)
 // Elements of one workgroup of the stage and period kernels.

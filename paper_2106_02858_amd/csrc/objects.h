@@ -118,7 +118,7 @@ struct Resident {
     uint32_t epoch = 0;      // the last one used
     int tab_M = 0, tab_scheme = 0;
     int fits = 0, refused = 0;  // members: the most found to fit, the fewest found not to (0: none)
-    bool off = false;        // no room for the exchange, or a launch has given up
+    bool off = false;        // no room for the exchange
 };
 enum class Period {
     kRan,      // to its end
@@ -164,6 +164,7 @@ struct cmcg_problem {
     std::map<int64_t, hipGraphExec_t> lts_graphs;  // captured LTS periods
     std::unique_ptr<cmcg::HostPinned> pinned;
     std::unique_ptr<cmcg::Resident> resident;
+    double stall = 0;  // cmcg_debug_period_stall
     hipStream_t cap_stream = nullptr;
     std::map<int64_t, hipGraphExec_t> graphs;
     ~cmcg_problem() {
@@ -238,8 +239,9 @@ void build_geo(cmcg_problem* p, double alpha);
 // [step][stage][member][kMemberParams] of tab (StageArgs::mtab, PeriodArgs::mtab).
 void fill_step_table(std::vector<double>& tab, int B, int b, int Mmax, const StepCfg& c, double omega);
 // One period of a.M steps of n members as one launch on st (PeriodArgs), waited
-// for.  a's exchange fields are filled in here.
-Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t st);
+// for.  a's exchange fields are filled in here.  stall > 0 (cmcg_debug_period_stall): blocks
+// are left out, and the others wait that many seconds for them.
+Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stall, hipStream_t st);
 // Whether the current stage variant of a space leaves its periods to
 // run_resident (none chosen by hand, and the arithmetic is the same).
 bool resident_variant(const SpaceData& s);

@@ -673,10 +673,17 @@ namespace {
 struct ResidentTurn {
     std::mutex mu;
     hipEvent_t last = nullptr;
+    std::chrono::steady_clock::time_point resume{};  // no such periods before this time
+    double pause = 0;                                // seconds, the last one
     PeriodCounts counts;
 };
 ResidentTurn g_resident[64];
-constexpr double kResidentWait = 2.0;  // seconds a workgroup waits for a neighbour before it gives up
+// Seconds a workgroup waits for a neighbour before it gives up.  What keeps
+// workgroups off the device (another process, masked compute units) keeps
+// those of every problem off it, so after a launch that gave up the device's
+// periods run by stage launches for a minute, and for twice as long after each
+// further one: the waits cost at most 3 % of the time.
+constexpr double kResidentWait = 2.0, kResidentPause = 60.0, kResidentLongestPause = 3600.0;
 }  // namespace
 
 PeriodCounts& period_counts(int device) { return g_resident[device].counts; }
@@ -718,8 +725,13 @@ static void build_mailboxes(SpaceData& s, hipStream_t st) {
     s.next = n;
 }
 
-Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t st) {
+Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stall, hipStream_t st) {
+    ResidentTurn& turn = g_resident[s.device];
     if (r.off || (r.refused && n >= r.refused)) return Period::kRefused;
+    {
+        std::lock_guard<std::mutex> lk(turn.mu);
+        if (std::chrono::steady_clock::now() < turn.resume) return Period::kRefused;
+    }
     const auto launch = [&] {
         return s.dim == 2 ? launch_period2d(s.q, s.precision, a, n, st) : launch_period(s.q, s.precision, a, n, st);
     };
@@ -759,10 +771,10 @@ Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t
     a.abort = (uint32_t*)(a.xch + pairs);
     a.failed = (int*)r.failed.p;
     a.epoch = r.epoch + 1;
-    a.limit = (unsigned long long)(kResidentWait * 1e3 * khz);
+    a.limit = (unsigned long long)((stall > 0 ? stall : kResidentWait) * 1e3 * khz);
+    a.left_out = stall > 0 ? 1 : 0;
     r.epoch += (uint32_t)need;
     {
-        ResidentTurn& turn = g_resident[s.device];
         std::lock_guard<std::mutex> lk(turn.mu);
         if (!turn.last)
             CMCG_HIP(hipEventCreateWithFlags(&turn.last, hipEventDisableTiming));
@@ -772,11 +784,15 @@ Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, hipStream_t
         CMCG_HIP(hipEventRecord(turn.last, st));
     }
     CMCG_HIP(hipStreamSynchronize(st));
+    std::lock_guard<std::mutex> lk(turn.mu);
     if (*failed) {
-        r.off = true;
+        turn.pause = turn.pause > 0 ? std::min(2 * turn.pause, kResidentLongestPause) : kResidentPause;
+        turn.resume = std::chrono::steady_clock::now() + std::chrono::duration_cast<std::chrono::steady_clock::duration>(
+                                                             std::chrono::duration<double>(turn.pause));
         return Period::kGaveUp;
     }
-    ++period_counts(s.device).done;
+    turn.pause = 0;
+    ++turn.counts.done;
     return Period::kRan;
 }
 
@@ -821,7 +837,7 @@ static Period resident_period(cmcg_problem* p, const StepCfg& c, bool src, bool 
         launch_zero(p->Fre.p, p->Fre.bytes, st);
         launch_zero(p->Fim.p, p->Fim.bytes, st);
     }
-    const Period done = run_resident(r, s, a, 1, st);
+    const Period done = run_resident(r, s, a, 1, p->stall, st);
     if (done == Period::kRan && filt && c.scheme == 2)  // last level t_M = T: e^{-i w T} = 1
         launch_filter_add(s.precision, p->U.p, 1.0 / c.M, 0.0, p->Fre.as<double>(), p->Fim.as<double>(), s.ndof, st);
     return done;
@@ -1802,6 +1818,21 @@ int cmcg_debug_period_counts(int64_t* done, int64_t* restarted) {
     const PeriodCounts& c = period_counts(current_device());
     *done = c.done;
     *restarted = c.restarted;
+    return CMCG_OK;
+    CMCG_GUARD_END
+}
+
+int cmcg_debug_period_stall(cmcg_problem* p, double seconds) {
+    CMCG_GUARD_BEGIN
+    if (!p || !(seconds >= 0) || seconds > kResidentWait)
+        fail(CMCG_ERR_ARG, "debug_period_stall: NULL problem, or seconds outside 0 .. 2");
+    const int nb = (int)((p->sp->K + element_block(p->sp->dim) - 1) / element_block(p->sp->dim));
+    if (seconds > 0 && nb < 9) fail(CMCG_ERR_ARG, "debug_period_stall: the mesh has fewer than nine element blocks");
+    p->stall = seconds;
+    ResidentTurn& turn = g_resident[p->sp->device];
+    std::lock_guard<std::mutex> lk(turn.mu);
+    turn.resume = {};
+    turn.pause = 0;
     return CMCG_OK;
     CMCG_GUARD_END
 }

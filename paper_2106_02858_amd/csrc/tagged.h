@@ -151,7 +151,7 @@ inline bool launch_resident(F kernel, int64_t nblocks, int n, int threads, bool 
     if (!a.xch) return true;
     for (int first = 0; first < n; first += (int)room) {
         a.first = first;
-        const dim3 grid((unsigned)(8 * per), (unsigned)(n - first < room ? n - first : room));
+        const dim3 grid((unsigned)(8 * (per - a.left_out)), (unsigned)(n - first < room ? n - first : room));
         hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a, per);
         CMCG_HIP(hipGetLastError());
     }

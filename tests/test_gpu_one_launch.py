@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from paper_2106_02858_amd import inputs
-from tests.test_gpu_resident import _member, _mesh2d, _mesh3d, _problem
+from tests.test_gpu_resident import _member, _mesh2d, _mesh3d, _periods, _problem
 
 pytestmark = pytest.mark.gpu
 
@@ -99,3 +99,78 @@ def test_batch_members_left_run_as_one_launch(lib):
     # the members in the last iterations are few enough to fit (3 workgroups per compute unit, 80 slots each)
     few = sum(1 for i in range(iters[-1]) if sum(1 for r in res if r["iters"] > i) * 80 <= 512)
     assert b[0] - a[0] >= 2 * few > 0 and b[1] == a[1]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("dim,q", [(2, 1), (2, 3), (3, 1), (3, 2), (3, 3)])
+def test_period_that_gives_up_runs_by_stage_launches(lib, dim, q, precision):
+    """A launch whose blocks are not all there gives up: its period starts
+    again (state and filter) by stage launches, and neither this problem nor
+    another of the device waits for such a launch again while the pause lasts."""
+    import torch
+    print(f"give up dim={dim} q={q} prec={precision}", flush=True)
+    mesh = (_mesh2d if dim == 2 else _mesh3d)("shuffled")
+    s, p = _problem(lib, dim, mesh, q, precision, seed=7)
+    K, Np, comps = len(mesh[1]), lib.cmcg_space_info(s)["Np"], 3 if dim == 2 else 6
+    other = _member(lib, s, dim, K, q, np.random.default_rng(1), 9.0)
+    try:
+        lib.cmcg_debug_period_stall(p, 1e-3)
+        a = lib.cmcg_debug_period_counts()
+        got = _periods(lib, p, K, comps, Np, q, 1)
+        b = lib.cmcg_debug_period_counts()
+        assert (b[0] - a[0], b[1] - a[1]) == (0, 1)
+        assert _period(lib, other, K, comps, Np) == (0, 0)
+    finally:
+        lib.cmcg_debug_period_stall(p, 0)
+    for x, y in zip(got, _periods(lib, p, K, comps, Np, q, 0)):
+        assert torch.isfinite(x).all() and torch.equal(x, y)
+    assert _period(lib, other, K, comps, Np) == (1, 0)
+    assert _period(lib, p, K, comps, Np) == (1, 0)
+
+
+def test_filtered_period_that_gives_up(lib):
+    """The accumulators of a filtered period that gave up are begun again too."""
+    import torch
+    print("give up, filtered", flush=True)
+    mesh = _mesh3d("shuffled")
+    s, p = _problem(lib, 3, mesh, 2, 1, seed=7)
+    U = torch.tensor(np.random.default_rng(3).standard_normal((len(mesh[1]), 6, 10)), device="cuda")
+    out = []
+    for stall, graph in ((1e-3, 1), (0, 0)):
+        lib.cmcg_debug_period_stall(p, stall)
+        V, F, G = (torch.zeros_like(U) for _ in range(3))
+        a = lib.cmcg_debug_period_counts()
+        lib.cmcg_debug_period(p, U, V, 1, True, F, G, opts=lib.cmcg_options_default(use_graph=graph))
+        assert lib.cmcg_debug_period_counts()[1] - a[1] == graph
+        out.append((V, F, G))
+    assert all(torch.equal(x, y) and torch.isfinite(x).all() for x, y in zip(*out))
+
+
+def test_batch_that_gives_up(lib):
+    import torch
+    print("give up, batch", flush=True)
+    xy, tri, tags = inputs.cartesian_triangles(12, 9)
+    K, q = len(tri), 3
+    s = lib.cmcg_space_create(lib.cmcg_mesh2d_create(xy, tri, tags), q, 1)
+    probs = [_member(lib, s, 2, K, q, np.random.default_rng(b), 20.0 + b) for b in range(6)]
+    out = []
+    for stall, graph in ((1e-3, 1), (0, 0)):
+        lib.cmcg_debug_period_stall(probs[0], stall)
+        a = lib.cmcg_debug_period_counts()
+        res = lib.cmcg_solve_batch(probs, lib.cmcg_options_default(fixed_iters=2, use_graph=graph))
+        b = lib.cmcg_debug_period_counts()
+        assert (b[0] - a[0], b[1] - a[1]) == (0, graph)
+        f = [[torch.zeros((K, 3, 10), dtype=torch.float64, device="cuda") for _ in range(2)] for _ in res]
+        for r, (x, y) in zip(res, f):
+            lib.cmcg_result_filtered_device(r, x, y)
+        out.append([x for pair in f for x in pair])
+    assert all(torch.equal(x, y) and torch.isfinite(x).all() for x, y in zip(*out))
+
+
+def test_stall_arguments(lib):
+    mesh = _mesh3d(43)  # five blocks: none can be left out of each range
+    _, p = _problem(lib, 3, mesh, 1, 0, seed=1)
+    for bad in (1e-3, -1.0, 3.0, float("nan")):
+        with pytest.raises(lib.CmcgError) as err:
+            lib.cmcg_debug_period_stall(p, bad)
+        assert err.value.code == lib.CMCG_ERR_ARG
