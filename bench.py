@@ -89,17 +89,17 @@ def parse():
 # FETCH_SIZE / WRITE_SIZE per dispatch (KiB) of the stage kernel on the
 # 48000-tet P3 FP32 problem, with the scales a 1 GiB copy gives each counter;
 # valid only for the kernel source they were taken on (SHA-256 below).
-_SHA_3D = "9466bf79f0c47ef9c5e5fd30209f9997083e961b3aea87feaac99df1e83602fb"
+_SHA_3D = "2c4498974c2f0d043dccbcc0390e9a7c3b585c9c7bb9cd7cce751c9951693fae"
 MEASURED_TRAFFIC = [
     {"kernels_sha256": _SHA_3D, "kernel": "k_stage_col<3,false,false>", "K": 48000,
-     "fetch_kib": 40864.20, "fetch_scale": 2.0000, "write_kib": 42187.53, "write_scale": 1.0000},
+     "fetch_kib": 40859.20, "fetch_scale": 2.0000, "write_kib": 42187.52, "write_scale": 1.0000},
 ]
 
 
 # The same for the FP64 stage kernel of the plain FP64 solve (48000 tets, P3).
 MEASURED_TRAFFIC_FP64 = [
     {"kernels_sha256": _SHA_3D, "kernel": "k_stage_tile<3,false,false>", "K": 48000,
-     "fetch_kib": 72831.93, "fetch_scale": 2.0000, "write_kib": 78750.00, "write_scale": 1.0000},
+     "fetch_kib": 72814.76, "fetch_scale": 2.0000, "write_kib": 78750.00, "write_scale": 1.0000},
 ]
 
 
@@ -110,16 +110,16 @@ MEASURED_TRAFFIC_FP64 = [
 MEASURED_TRAFFIC_Q2 = [
     {"kernels_sha256": _SHA_3D, "kernel": k, "K": K,
      "fetch_kib": fe, "fetch_scale": 2.0000, "write_kib": wr, "write_scale": 1.0000}
-    for k, K, fe, wr in (("k_stage_col<2,false,false>", 1572864, 777450.02, 702543.43),
-                         ("k_stage_col<2,false,false>", 64 * 10368, 247122.28, 297304.35),
-                         ("k_stage<float,2,false,false>", 64 * 10368, 283849.30, 292179.27),
-                         ("k_stage<float,2,true,false>", 64 * 10368, 252566.91, 291656.49))
+    for k, K, fe, wr in (("k_stage_col<2,false,false>", 1572864, 777821.23, 702144.21),
+                         ("k_stage_col<2,false,false>", 64 * 10368, 247441.27, 297147.80),
+                         ("k_stage<float,2,false,false>", 64 * 10368, 284494.56, 292220.96),
+                         ("k_stage<float,2,true,false>", 64 * 10368, 252853.07, 291673.67))
 ]
 
 
 # The same for the 2-D stage kernel on the 22500-triangle disk trap (P3, FP32).
 MEASURED_TRAFFIC_2D = {
-    "kernels_sha256": "176b032d2b818327be767ace09615e0212481100d4fa402fa48930bba752bce1",
+    "kernels_sha256": "d164e1ced27782784e199c6bdbd0a345f0a4c997447bd37c89c82a901bcc7291",
     "kernel": "k_stage2d<float,3,true>", "K": 22500,
     "fetch_kib": 5076.50, "fetch_scale": 2.0000, "write_kib": 4944.12, "write_scale": 1.0000,
 }

@@ -102,8 +102,11 @@ typedef struct cmcg_options {
                             from a captured hipGraph; 0: launch its stages one
                             by one.  The results are the same, bit for bit.  A
                             one-launch period that cannot get all of its blocks
-                            onto the device is run by stage launches after 2 s,
-                            and so are the device's periods for a minute then   */
+                            onto the device is run by stage launches after
+                            0.1 s, and so are the device's periods for some
+                            seconds then.  Beside other solves of the process
+                            only small ones run this way (a third of the
+                            device), and none beside stage launches             */
     int residual_refresh;/* > 0: every this many iterations replace R by the
                             true gradient (costs two periods); <= 0 = never.
                             FP32 fields keep the state compensated (FP32 +
@@ -393,7 +396,7 @@ int cmcg_debug_period_counts(int64_t* done, int64_t* restarted);
 /* For tests: one-launch periods of p (and of batches whose first member is p)
  * leave some element blocks out, as if these found no room on the device, and
  * the others give up after waiting `seconds` (0 < seconds <= 2) for them; the
- * period then runs by stage launches, and for a minute so do all of the
+ * period then runs by stage launches, and for some seconds so do all of the
  * device's.  0: back to normal.  Either way periods run as one launch again at
  * once.  Errors: CMCG_ERR_ARG (NULL, seconds, fewer than nine element blocks). */
 int cmcg_debug_period_stall(cmcg_problem* p, double seconds);

@@ -460,6 +460,9 @@ namespace {
 void solve_prepared(Batch& bt, const cmcg_options* o, hipStream_t st, cmcg_result** out) {
     const int B = bt.B;
     const SpaceData& s = *bt.sp;
+    StepCfg c0 = bt.cfg[0];
+    c0.resident = bt.resident_ok;
+    const DeviceUse use(s.device, resident_small(bt.P[0], c0, o, B));
     const int64_t n = s.ndof, K = s.K;
     std::vector<int> act(B, 1);
     if (o->autotune && s.dim == 3 && !apply_tuned_variant(s.device, s.q, s.precision, K, B)) {

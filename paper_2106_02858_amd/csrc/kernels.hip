@@ -2951,35 +2951,25 @@ void launch_stage(int q, int precision, const StageArgs& a, hipStream_t s) {
     check_launch();
 }
 
-// One-launch periods, whenever all members' blocks are resident at once.  Time
-// per stage, one launch per period against one per stage (us):
-//   FP32 P1 1296 tets 1.1 / 2.9, 10368 2.1 / 3.1, 12790 2.3 / 3.2;
-//   FP32 P2 3072 3.5 / 4.7, 10368 5.2 / 6.8, 15300 6.4 / 8.3;
-//   FP32 P3 384 3.7 / 4.7, 3072 4.4 / 5.8, 7600 5.7 / 8.3;
-//   FP64 P1 1296 1.4 / 3.1, 6000 3.1 / 3.3;
-//   FP64 P2 384 3.8 / 4.5, 1296 4.1 / 4.7, 3072 5.2 / 5.7, but 4374 6.7 / 5.9 and
-//   6000 8.7 / 7.2, so up to 350 blocks only (two FP64 words a value and the
-//   update's copy through LDS cost more than the launches they replace);
-//   FP64 P3 384 5.3 / 7.0, 3072 7.6 / 9.2, 4374 9.5 / 9.8.
-// Members in several groups, one after another, lose to stage launches that run
-// all members at once (FP32 P2, 16 members of 10368 tets: 156 ms a solve against
-// 102; FP64 P1, 16 of 1296: 50 against 27).
 namespace {
-bool period3d_f32(int q, const PeriodArgs& a, int64_t nb, int n, hipStream_t s) {
-    if (q == 1) return launch_resident(k_period_p1<float>, nb, n, 256, false, a, s);
-    if (q == 2) return launch_resident(k_period_col<2, 4>, nb, n, ColDim<2>::NTH, false, a, s);
-    return launch_resident(k_period_col<3, 5>, nb, n, ColDim<3>::NTH, false, a, s);
-}
-bool period3d_f64(int q, const PeriodArgs& a, int64_t nb, int n, hipStream_t s) {
-    if (q == 1) return launch_resident(k_period_p1<double>, nb, n, 256, false, a, s);
-    if (q == 2) return nb * n <= 350 && launch_resident(k_period_tile<2, 3>, nb, n, 256, false, a, s);
-    return launch_resident(k_period_tile<3, 2>, nb, n, 256, false, a, s);
+template <typename F> auto period_kernel(int q, int precision, F f) {
+    if (precision == CMCG_FP64) {
+        if (q == 1) return f(k_period_p1<double>, 256);
+        return q == 2 ? f(k_period_tile<2, 3>, 256) : f(k_period_tile<3, 2>, 256);
+    }
+    if (q == 1) return f(k_period_p1<float>, 256);
+    return q == 2 ? f(k_period_col<2, 4>, ColDim<2>::NTH) : f(k_period_col<3, 5>, ColDim<3>::NTH);
 }
 }  // namespace
 
-bool launch_period(int q, int precision, const PeriodArgs& a, int n, hipStream_t s) {
-    const int64_t nb = (a.K + EPW - 1) / EPW;
-    return precision == CMCG_FP64 ? period3d_f64(q, a, nb, n, s) : period3d_f32(q, a, nb, n, s);
+int64_t period_room(int q, int precision) {
+    return period_kernel(q, precision, [](auto kernel, int threads) { return resident_room(kernel, threads); });
+}
+
+void launch_period(int q, int precision, const PeriodArgs& a, int n, hipStream_t s) {
+    period_kernel(q, precision, [&](auto kernel, int threads) {
+        launch_resident(kernel, (a.K + EPW - 1) / EPW, n, threads, a, s);
+    });
 }
 
 void launch_to_field(int precision, int Np, const double* X, void* U, void* Ulo, int64_t n, int flipH,

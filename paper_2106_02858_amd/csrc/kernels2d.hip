@@ -1076,9 +1076,13 @@ void stage2d(const StageArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((k_stage2d<T, Q, false>), grid, dim3(64), 0, s, a, per);
 }
 
-template <typename T, int Q>
-bool period2d(const PeriodArgs& a, int n, hipStream_t s) {
-    return launch_resident(k_period2d<T, Q>, (a.K + EPB - 1) / EPB, n, 256, true, a, s);
+template <typename F> auto period2d_kernel(int q, int precision, F f) {
+    if (precision == CMCG_FP64) {
+        if (q == 1) return f(k_period2d<double, 1>);
+        return q == 2 ? f(k_period2d<double, 2>) : f(k_period2d<double, 3>);
+    }
+    if (q == 1) return f(k_period2d<float, 1>);
+    return q == 2 ? f(k_period2d<float, 2>) : f(k_period2d<float, 3>);
 }
 
 }  // namespace
@@ -1116,13 +1120,12 @@ void launch_stage2d(int q, int precision, const StageArgs& a, hipStream_t s) {
     check2();
 }
 
-bool launch_period2d(int q, int precision, const PeriodArgs& a, int n, hipStream_t s) {
-    if (precision == CMCG_FP64) {
-        if (q == 1) return period2d<double, 1>(a, n, s);
-        return q == 2 ? period2d<double, 2>(a, n, s) : period2d<double, 3>(a, n, s);
-    }
-    if (q == 1) return period2d<float, 1>(a, n, s);
-    return q == 2 ? period2d<float, 2>(a, n, s) : period2d<float, 3>(a, n, s);
+int64_t period_room2d(int q, int precision) {
+    return period2d_kernel(q, precision, [](auto kernel) { return resident_room(kernel, 256); });
+}
+
+void launch_period2d(int q, int precision, const PeriodArgs& a, int n, hipStream_t s) {
+    period2d_kernel(q, precision, [&](auto kernel) { launch_resident(kernel, (a.K + EPB - 1) / EPB, n, 256, a, s); });
 }
 
 void launch_to_field2d(int precision, int Np, const double* X, void* U, void* Ulo, int64_t n, int flipH,

@@ -230,11 +230,12 @@ void launch_nonfinite(const double* X, int64_t n, int* out_dev, hipStream_t s);
 // member, StageArgs::mtab non-null) as in 3-D, without the source mask.
 void upload_constants2d(int q, const double* D, const double* LIFT, const double* M, const int* fnode);
 void launch_stage2d(int q, int precision, const StageArgs& a, hipStream_t s);
-// One period of the n members of a.order in one launch (triangles: or a launch
-// per group of members that fits on the device at once); false, and nothing
-// launched, when the members do not fit.  Without a.xch: only whether they fit.
-bool launch_period(int q, int precision, const PeriodArgs& a, int n, hipStream_t s);    // tetrahedra
-bool launch_period2d(int q, int precision, const PeriodArgs& a, int n, hipStream_t s);  // triangles
+// One period of n members (a.order from a.first on) in one launch; all of its
+// workgroups have to be on the device at once, and period_room says how many may be.
+int64_t period_room(int q, int precision);    // tetrahedra
+int64_t period_room2d(int q, int precision);  // triangles
+void launch_period(int q, int precision, const PeriodArgs& a, int n, hipStream_t s);
+void launch_period2d(int q, int precision, const PeriodArgs& a, int n, hipStream_t s);
 void launch_to_field2d(int precision, int Np, const double* X, void* U, void* Ulo, int64_t n, int flipH,
                        hipStream_t s);
 void launch_from_field2d(int precision, int Np, const void* U, const void* Ulo, double* Y, const double* sub,

@@ -117,7 +117,7 @@ struct Resident {
     HostPinned failed{1};    // [0]: set by a launch that gave up
     uint32_t epoch = 0;      // the last one used
     int tab_M = 0, tab_scheme = 0;
-    int fits = 0, refused = 0;  // members: the most found to fit, the fewest found not to (0: none)
+    int64_t room = 0;        // workgroups of the period kernel that the device holds (0: not asked yet)
     bool off = false;        // no room for the exchange
 };
 enum class Period {
@@ -132,6 +132,16 @@ struct PeriodCounts {
     std::atomic<int64_t> restarted{0};  // begun again from their start state, by stage launches
 };
 PeriodCounts& period_counts(int device);
+// A call (a solve, an engine slot) whose launches are on the device; small: by
+// one-launch periods that may share it with others like them.
+struct DeviceUse {
+    int device;
+    bool small;
+    DeviceUse(int dev, bool small_);
+    DeviceUse(const DeviceUse&) = delete;
+    DeviceUse& operator=(const DeviceUse&) = delete;
+    ~DeviceUse();
+};
 
 }  // namespace cmcg
 
@@ -195,6 +205,7 @@ struct CgRun {
     hipStream_t st = nullptr;
     const double* u0 = nullptr;
     std::unique_ptr<cmcg_result> res;
+    std::unique_ptr<DeviceUse> use;
     int phase = kDone;
     int64_t n = 0;
     int it = 0, periods = 0, refresh = 0, limit = 0;
@@ -242,6 +253,9 @@ void fill_step_table(std::vector<double>& tab, int B, int b, int Mmax, const Ste
 // for.  a's exchange fields are filled in here.  stall > 0 (cmcg_debug_period_stall): blocks
 // are left out, and the others wait that many seconds for them.
 Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stall, hipStream_t st);
+// Whether the periods of n problems like p are one-launch periods small enough
+// to run beside others.
+bool resident_small(const cmcg_problem* p, const StepCfg& c, const cmcg_options* o, int n);
 // Whether the current stage variant of a space leaves its periods to
 // run_resident (none chosen by hand, and the arithmetic is the same).
 bool resident_variant(const SpaceData& s);

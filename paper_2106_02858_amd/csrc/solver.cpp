@@ -3,6 +3,7 @@
 // filter weights (Section 5.4), the CMCG controller (Section 2.2, Algorithms
 // 1-3) and the extern "C" entry points declared in include/cmcg.h.
 #include <chrono>
+#include <condition_variable>
 #include <cmath>
 #include <complex>
 #include <cstring>
@@ -667,26 +668,75 @@ static void run_period(cmcg_problem* p, const StepCfg& c, bool src, bool filt, b
 
 // ------------------------------------------------- periods as one launch
 namespace {
-// One-launch periods of a device run one after another, whatever streams they
-// are on: each needs all of its workgroups resident at once.  `last` marks
-// the end of the newest.
+// The one-launch periods that are on a device, and the calls that use it.  Each
+// such period needs all of its workgroups there at once: the shares of the
+// device that they take are added up.  A call alone on the device may fill it.
+// Beside others,
+//   * one whose periods take more than kSmallShare of the device runs by stage
+//     launches: these share it better than periods of that size, one after
+//     another (FP32 P1, 10368 tets, share 0.8, four threads: 4.7 ms a solve
+//     against 8.4);
+//   * smaller ones run together, up to two thirds of the device, and wait for
+//     their turn beyond, as long as no call runs by stage launches: the stream
+//     of such launches takes up registers as soon as they come free, and a period
+//     kernel's workgroup, which needs more of them, may wait for its end.
+// ms a solve with one / two / four / eight host threads, each with its own
+// problem, by stage launches, by one-launch periods one after another, and now:
+//   FP64 P1 1296 tets          6.7 3.5 2.0 2.9, 3.2 2.9 2.9, 3.2 2.0 2.0 1.8;
+//   FP32 P2 3072 tets          10.5 6.0 3.4 4.9, 6.8 6.6 6.6, 6.9 4.1 3.3 3.4;
+//   FP32 P3 7056 triangles     84.6 46 28 37, 27 27 27, 27 16.6 17.3 17.4.
+constexpr double kSmallShare = 1.0 / 3, kSharedDevice = 2.0 / 3;
 struct ResidentTurn {
     std::mutex mu;
-    hipEvent_t last = nullptr;
+    std::condition_variable room;
+    double used = 0;               // shares of the device
+    int users = 0, small_users = 0;  // calls; those with small periods
     std::chrono::steady_clock::time_point resume{};  // no such periods before this time
     double pause = 0;                                // seconds, the last one
     PeriodCounts counts;
+    bool enter(double share) {
+        std::unique_lock<std::mutex> lk(mu);
+        const auto refuse = [&] {
+            return std::chrono::steady_clock::now() < resume ||
+                   (users > 1 && (share > kSmallShare || small_users < users));
+        };
+        if (refuse()) return false;
+        if (users > 1) {
+            room.wait(lk, [&] { return used + share <= kSharedDevice; });
+            if (refuse()) return false;
+        }
+        used += share;
+        return true;
+    }
+    void leave(double share) {
+        std::lock_guard<std::mutex> lk(mu);
+        used = used > share ? used - share : 0;
+        room.notify_all();
+    }
 };
 ResidentTurn g_resident[64];
-// Seconds a workgroup waits for a neighbour before it gives up.  What keeps
-// workgroups off the device (another process, masked compute units) keeps
-// those of every problem off it, so after a launch that gave up the device's
-// periods run by stage launches for a minute, and for twice as long after each
-// further one: the waits cost at most 3 % of the time.
-constexpr double kResidentWait = 2.0, kResidentPause = 60.0, kResidentLongestPause = 3600.0;
+// Seconds a workgroup waits for a neighbour before it gives up: a hundred
+// thousand exchanges.  What keeps workgroups off the device (other kernels,
+// another process, masked compute units) keeps those of every problem off it,
+// so after a launch that gave up the device's periods run by stage launches for
+// two seconds, and for twice as long after each further one.
+constexpr double kResidentWait = 0.1, kResidentPause = 2.0, kResidentLongestPause = 3600.0;
 }  // namespace
 
 PeriodCounts& period_counts(int device) { return g_resident[device].counts; }
+
+DeviceUse::DeviceUse(int dev, bool small_) : device(dev), small(small_) {
+    ResidentTurn& turn = g_resident[device];
+    std::lock_guard<std::mutex> lk(turn.mu);
+    ++turn.users;
+    turn.small_users += small;
+}
+DeviceUse::~DeviceUse() {
+    ResidentTurn& turn = g_resident[device];
+    std::lock_guard<std::mutex> lk(turn.mu);
+    --turn.users;
+    turn.small_users -= small;
+}
 
 // whether the variant of (q, precision) was chosen through cmcg_tune_stage (the
 // autotuner's choice between stage launches leaves the one-launch periods on)
@@ -725,23 +775,48 @@ static void build_mailboxes(SpaceData& s, hipStream_t st) {
     s.next = n;
 }
 
+// How the period of n members runs as one launch.
+struct PeriodPlan {
+    int at_once;   // members per launch; 0: not this way
+    double share;  // of the device, per launch
+};
+
+// All members' blocks are on the device at once (triangles: those of one member
+// after the other).  Time per stage, one launch per period against one per
+// stage (us):
+//   FP32 P1 1296 tets 2.2 / 5.8, 3072 2.1 / 5.8, 10368 3.8 / 6.3;
+//   FP32 P2 3072 3.5 / 4.7, 10368 5.2 / 6.8, 15300 6.4 / 8.3;
+//   FP32 P3 384 3.7 / 4.7, 3072 4.4 / 5.8, 7600 5.7 / 8.3;
+//   FP64 P1 1296 2.8 / 6.3, 6000 6.1 / 6.7;
+//   FP64 P2 384 3.8 / 4.5, 1296 4.1 / 4.7, 3072 5.2 / 5.7, but 4374 6.7 / 5.9 and
+//   6000 8.7 / 7.2, so up to 350 blocks only (two FP64 words a value and the
+//   update's copy through LDS cost more than the launches they replace);
+//   FP64 P3 384 5.3 / 7.0, 3072 7.6 / 9.2, 4374 9.5 / 9.8.
+// Members in several groups, one after another, lose to stage launches that run
+// all members at once (FP32 P2, 16 members of 10368 tets: 156 ms a solve against
+// 102; FP64 P1, 16 of 1296: 50 against 27).
+static PeriodPlan plan_period(const SpaceData& s, int64_t room, int n) {
+    const int64_t nb = (s.K + element_block(s.dim) - 1) / element_block(s.dim);
+    const int64_t total = (nb + 7) / 8 * 8;  // workgroups of a member
+    const int64_t most = room / total;
+    PeriodPlan plan{(int)std::min<int64_t>(n, most), 0};
+    if (s.dim == 3 && (plan.at_once < n || (s.precision == CMCG_FP64 && s.q == 2 && nb * n > 350))) plan.at_once = 0;
+    plan.share = (double)(plan.at_once * total) / (double)std::max<int64_t>(room, 1);
+    return plan;
+}
+
+static int64_t room_of(const SpaceData& s) {
+    return s.dim == 2 ? period_room2d(s.q, s.precision) : period_room(s.q, s.precision);
+}
+static PeriodPlan resident_plan(Resident& r, const SpaceData& s, int n) {
+    if (r.off) return {0, 0};
+    if (r.room == 0) r.room = room_of(s);
+    return plan_period(s, r.room, n);
+}
+
 Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stall, hipStream_t st) {
-    ResidentTurn& turn = g_resident[s.device];
-    if (r.off || (r.refused && n >= r.refused)) return Period::kRefused;
-    {
-        std::lock_guard<std::mutex> lk(turn.mu);
-        if (std::chrono::steady_clock::now() < turn.resume) return Period::kRefused;
-    }
-    const auto launch = [&] {
-        return s.dim == 2 ? launch_period2d(s.q, s.precision, a, n, st) : launch_period(s.q, s.precision, a, n, st);
-    };
-    if (n > r.fits) {
-        if (!launch()) {  // only whether they fit: no mailboxes are numbered yet
-            r.refused = n;
-            return Period::kRefused;
-        }
-        r.fits = n;
-    }
+    const PeriodPlan plan = resident_plan(r, s, n);
+    if (plan.at_once == 0) return Period::kRefused;
     std::call_once(s.x_once, [&] { build_mailboxes(s, st); });
     const size_t vals = (size_t)a.members * s.next * (s.dim == 2 ? 3 : 6) * s.Nfp;
     if (vals > (size_t)kPeriodMaxValues) {
@@ -773,15 +848,20 @@ Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stal
     a.epoch = r.epoch + 1;
     a.limit = (unsigned long long)((stall > 0 ? stall : kResidentWait) * 1e3 * khz);
     a.left_out = stall > 0 ? 1 : 0;
+    ResidentTurn& turn = g_resident[s.device];
+    if (!turn.enter(plan.share)) return Period::kRefused;
+    struct Leave {
+        ResidentTurn& turn;
+        double share;
+        ~Leave() { turn.leave(share); }
+    } leave{turn, plan.share};
     r.epoch += (uint32_t)need;
-    {
-        std::lock_guard<std::mutex> lk(turn.mu);
-        if (!turn.last)
-            CMCG_HIP(hipEventCreateWithFlags(&turn.last, hipEventDisableTiming));
+    for (a.first = 0; a.first < n; a.first += plan.at_once) {
+        const int m = std::min(plan.at_once, n - a.first);
+        if (s.dim == 2)
+            launch_period2d(s.q, s.precision, a, m, st);
         else
-            CMCG_HIP(hipStreamWaitEvent(st, turn.last, 0));
-        if (!launch()) fail(CMCG_ERR_STATE, "a period that fitted on the device no longer does");
-        CMCG_HIP(hipEventRecord(turn.last, st));
+            launch_period(s.q, s.precision, a, m, st);
     }
     CMCG_HIP(hipStreamSynchronize(st));
     std::lock_guard<std::mutex> lk(turn.mu);
@@ -796,14 +876,24 @@ Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stal
     return Period::kRan;
 }
 
+// Whether periods of p, or of n problems like it, may run as one launch.
+static bool resident_call(const cmcg_problem* p, const StepCfg& c, const cmcg_options* o) {
+    return c.resident && o->use_graph != 0 && c.lts <= 1 && p->nharm == 1 && resident_variant(*p->sp);
+}
+bool resident_small(const cmcg_problem* p, const StepCfg& c, const cmcg_options* o, int n) {
+    if (!resident_call(p, c, o)) return false;
+    const PeriodPlan plan = plan_period(*p->sp, room_of(*p->sp), n);
+    return plan.at_once > 0 && plan.share <= kSmallShare;
+}
+
 // One period of p as one launch, where that may be.
-static Period resident_period(cmcg_problem* p, const StepCfg& c, bool src, bool filt, bool use_graph, hipStream_t st) {
+static Period resident_period(cmcg_problem* p, const StepCfg& c, const cmcg_options* o, bool src, bool filt,
+                              hipStream_t st) {
     SpaceData& s = *p->sp;
-    if (!c.resident || !use_graph || p->nharm != 1 || (p->resident && (p->resident->off || p->resident->refused)) ||
-        !resident_variant(s))
-        return Period::kRefused;
+    if (!resident_call(p, c, o)) return Period::kRefused;
     if (!p->resident) p->resident.reset(new Resident());
     Resident& r = *p->resident;
+    if (resident_plan(r, s, 1).at_once == 0) return Period::kRefused;
     if (r.tab_M != c.M || r.tab_scheme != c.scheme) {
         const int S = c.scheme == 2 ? 2 : 4;
         std::vector<double> tab((size_t)(c.M + 1) * S * kMemberParams, 0.0);
@@ -905,7 +995,7 @@ void apply_period(cmcg_problem* p, const StepCfg& c, const cmcg_options* o, cons
         }
     };
     start();
-    const Period done = resident_period(p, c, src && direction > 0, filt, o->use_graph != 0, st);
+    const Period done = resident_period(p, c, o, src && direction > 0, filt, st);
     if (done == Period::kGaveUp) {
         start();
         ++period_counts(s.device).restarted;
@@ -1051,6 +1141,7 @@ void CgRun::start(cmcg_problem* pr, const cmcg_options* opt, const double* u0_, 
     if (o.runup < 0) fail(CMCG_ERR_ARG, "options: runup must be >= 0");
     c = step_config(p, &o);
     c.resident = resident;
+    use.reset(new DeviceUse(p->sp->device, resident_small(p, c, &o, 1)));
     prepare(p, c);
     maybe_autotune(p, &o, c, st);
     const SpaceData& s = *p->sp;
@@ -1207,6 +1298,7 @@ void CgRun::complete() {
             S.dof_updates = (double)n * c.M * periods;
             S.status = (stopped || diverged || (!fixed && rel > o.tol)) ? CMCG_NOT_CONVERGED : CMCG_OK;
             phase = kDone;
+            use.reset();
             break;
         }
         default:
@@ -1221,6 +1313,7 @@ void CgRun::complete() {
 cmcg_result* fw_solve(cmcg_problem* p, const cmcg_options* o, const double* u0, hipStream_t st) {
     StepCfg c = step_config(p, o);
     c.resident = true;
+    const DeviceUse use(p->sp->device, resident_small(p, c, o, 1));
     prepare(p, c);
     maybe_autotune(p, o, c, st);
     const SpaceData& s = *p->sp;
@@ -1738,6 +1831,7 @@ int cmcg_debug_period(cmcg_problem* p, const cmcg_options* o, int direction, int
     if (!o) o = &def;
     StepCfg c = step_config(p, o);
     c.resident = true;
+    const DeviceUse use(p->sp->device, resident_small(p, c, o, 1));
     prepare(p, c);
     const bool filt = f_re || f_im;
     apply_period(p, c, o, u0, ut, nullptr, direction, with_source != 0, filt, stream);
@@ -1824,7 +1918,7 @@ int cmcg_debug_period_counts(int64_t* done, int64_t* restarted) {
 
 int cmcg_debug_period_stall(cmcg_problem* p, double seconds) {
     CMCG_GUARD_BEGIN
-    if (!p || !(seconds >= 0) || seconds > kResidentWait)
+    if (!p || !(seconds >= 0) || seconds > 2.0)
         fail(CMCG_ERR_ARG, "debug_period_stall: NULL problem, or seconds outside 0 .. 2");
     const int nb = (int)((p->sp->K + element_block(p->sp->dim) - 1) / element_block(p->sp->dim));
     if (seconds > 0 && nb < 9) fail(CMCG_ERR_ARG, "debug_period_stall: the mesh has fewer than nine element blocks");

@@ -123,17 +123,12 @@ template <typename T, int R, int NTH> struct Inbox {
     }
 };
 
-// Launches a period kernel over nblocks element blocks and n members, with
-// `groups` as many members at a time as fit on the device at once; false
-// (nothing launched) when one member, or without `groups` all of them, do not.
-// Without an exchange buffer (a.xch) it only tells whether they would.
-//
-// Room: what the occupancy query allows.  Blocks whose waves do not divide
-// over the four SIMDs of a compute unit need a free wave slot besides: with five
-// slots per SIMD, four blocks of five waves were not placed (799 blocks of
-// k_period_col<3> waited in vain), three were, and six blocks of three waves.
-template <typename F>
-inline bool launch_resident(F kernel, int64_t nblocks, int n, int threads, bool groups, PeriodArgs a, hipStream_t s) {
+// Workgroups of a period kernel that the device holds at once: what the
+// occupancy query allows.  Blocks whose waves do not divide over the four SIMDs
+// of a compute unit need a free wave slot besides: with five slots per SIMD, four
+// blocks of five waves were not placed (799 blocks of k_period_col<3> waited in
+// vain), three were, and six blocks of three waves.
+template <typename F> inline int64_t resident_room(F kernel, int threads) {
     int dev = 0, cus = 0, fit = 0;
     CMCG_HIP(hipGetDevice(&dev));
     CMCG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -146,16 +141,17 @@ inline bool launch_resident(F kernel, int64_t nblocks, int n, int threads, bool 
         const int limit = (4 * (slots < 8 ? slots : 8) - 1) / waves;
         if (fit > limit) fit = limit;
     }
-    const int64_t per = (nblocks + 7) / 8, room = (int64_t)fit * cus / (8 * per);
-    if (room < (groups ? 1 : n)) return false;
-    if (!a.xch) return true;
-    for (int first = 0; first < n; first += (int)room) {
-        a.first = first;
-        const dim3 grid((unsigned)(8 * (per - a.left_out)), (unsigned)(n - first < room ? n - first : room));
-        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a, per);
-        CMCG_HIP(hipGetLastError());
-    }
-    return true;
+    return (int64_t)fit * cus;
+}
+
+// Launches a period kernel over nblocks element blocks and n members (those of
+// a.order from a.first on).
+template <typename F>
+inline void launch_resident(F kernel, int64_t nblocks, int n, int threads, const PeriodArgs& a, hipStream_t s) {
+    const int64_t per = (nblocks + 7) / 8;
+    const dim3 grid((unsigned)(8 * (per - a.left_out)), (unsigned)n);
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a, per);
+    CMCG_HIP(hipGetLastError());
 }
 
 }  // namespace cmcg

@@ -3,6 +3,9 @@ do not tell (they equal those of stage launches, bit for bit; see
 test_gpu_resident.py), so the tests here ask the counters."""
 from __future__ import annotations
 
+import threading
+import time
+
 import numpy as np
 import pytest
 
@@ -174,3 +177,97 @@ def test_stall_arguments(lib):
         with pytest.raises(lib.CmcgError) as err:
             lib.cmcg_debug_period_stall(p, bad)
         assert err.value.code == lib.CMCG_ERR_ARG
+
+
+def _solves(lib, n, q, precision, count, fixed_iters, repeat, threads):
+    """`count` problems solved `repeat` times each, on a host thread and stream
+    each or one after the other: seconds, filtered fields, results' counts."""
+    import torch
+    xyz, tet, tags = inputs.cube_mesh(n)
+    s = lib.cmcg_space_create(lib.cmcg_mesh_create(xyz, tet, tags), q, precision)
+    K, Np = len(tet), lib.cmcg_space_info(s)["Np"]
+    probs = [_member(lib, s, 3, K, q, np.random.default_rng(b), 9.0 + 0.5 * b) for b in range(count)]
+    streams = [torch.cuda.Stream() for _ in probs]
+    o = lib.cmcg_options_default(fixed_iters=fixed_iters)
+    out, errors = [None] * count, []
+
+    def work(i, times):
+        try:
+            for _ in range(times):
+                r = lib.cmcg_solve(probs[i], o, stream=streams[i])
+            f = [torch.zeros((K, 6, Np), dtype=torch.float64, device="cuda") for _ in range(2)]
+            lib.cmcg_result_filtered_device(r, *f)
+            out[i] = f
+        except Exception as e:  # noqa: BLE001 (reported below)
+            errors.append(e)
+
+    for i in range(count):
+        work(i, 1)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    if threads:
+        th = [threading.Thread(target=work, args=(i, repeat)) for i in range(count)]
+        [t.start() for t in th]
+        [t.join() for t in th]
+    else:
+        for i in range(count):
+            work(i, repeat)
+    torch.cuda.synchronize()
+    seconds = time.perf_counter() - t0
+    assert not errors, errors
+    lib.cmcg_debug_period_stall(probs[0], 0)  # ends a pause, if the threads' first launches met
+    return seconds, out
+
+
+@pytest.mark.parametrize("n,q,precision,fits_together", [(8, 2, 1, True), (6, 1, 0, True), (12, 1, 1, False),
+                                                         (8, 3, 1, False)])
+def test_threads_share_the_device(lib, n, q, precision, fits_together):
+    """Solves on four host threads give what they give one after the other, and
+    small ones take less time together (one after another, each waiting for
+    the others' whole periods, took as long: 0.97 of it; together 0.5)."""
+    import torch
+    print(f"threads n={n} q={q} prec={precision}", flush=True)
+    ratios = []
+    for _ in range(3):
+        a, x = _solves(lib, n, q, precision, 4, 2, 4, threads=False)
+        b, y = _solves(lib, n, q, precision, 4, 2, 4, threads=True)
+        for u, v in zip(x, y):
+            assert all(torch.isfinite(f).all() and torch.equal(f, g) for f, g in zip(u, v))
+        ratios.append(b / a)
+    print(f"  together / one after the other: {ratios}")
+    if fits_together:
+        assert min(ratios) < 0.8
+
+
+def test_small_solve_beside_stage_launches(lib):
+    """Beside a call that runs by stage launches a small solve does too (its
+    workgroups would wait for room behind that call's launches)."""
+    import torch
+    print("small solve beside stage launches", flush=True)
+    big = _problem(lib, 3, inputs.cube_mesh(16), 1, 0, seed=2)[1]
+    mesh = _mesh3d("shuffled")
+    small = _problem(lib, 3, mesh, 2, 1, seed=7)[1]
+    ref = lib.cmcg_solve(small, lib.cmcg_options_default(fixed_iters=2, use_graph=0))
+    o = lib.cmcg_options_default(fixed_iters=400)
+    started, stop = threading.Event(), threading.Event()
+    o.set_progress(lambda it, rel: started.set() or stop.is_set())
+    stream = torch.cuda.Stream()
+    t = threading.Thread(target=lambda: lib.cmcg_solve(big, o, stream=stream))
+    t.start()
+    try:
+        assert started.wait(60)
+        a = lib.cmcg_debug_period_counts()
+        r = lib.cmcg_solve(small, lib.cmcg_options_default(fixed_iters=2))
+        b = lib.cmcg_debug_period_counts()
+        running = t.is_alive()
+    finally:
+        stop.set()
+        t.join()
+    assert running and a == b
+    f = [torch.zeros((len(mesh[1]), 6, 10), dtype=torch.float64, device="cuda") for _ in range(4)]
+    lib.cmcg_result_filtered_device(r, f[0], f[1])
+    lib.cmcg_result_filtered_device(ref, f[2], f[3])
+    assert torch.equal(f[0], f[2]) and torch.equal(f[1], f[3])
+    lib.cmcg_debug_period_stall(small, 0)
+    lib.cmcg_solve(small, lib.cmcg_options_default(fixed_iters=2))
+    assert lib.cmcg_debug_period_counts()[0] > b[0]
