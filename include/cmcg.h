@@ -391,8 +391,9 @@ int cmcg_debug_dot(cmcg_problem* p, const double* u_dev, const double* v_dev, do
 int cmcg_debug_mfma(int precision, const double* a_dev, const double* b_dev, double* d_dev, hipStream_t stream);
 /* Periods run as one launch (use_graph) on the current device since the
  * process started: *done ran to their end (a batch's period counts once),
- * *restarted were begun again from their start state, by stage launches. */
-int cmcg_debug_period_counts(int64_t* done, int64_t* restarted);
+ * *restarted were begun again from their start state, by stage launches;
+ * *launches: a batch of triangles takes one for each group of its members. */
+int cmcg_debug_period_counts(int64_t* done, int64_t* restarted, int64_t* launches);
 /* For tests: one-launch periods of p (and of batches whose first member is p)
  * leave some element blocks out, as if these found no room on the device, and
  * the others give up after waiting `seconds` (0 < seconds <= 2) for them; the

@@ -105,7 +105,7 @@ _sig = {
     "cmcg_debug_step": (C.c_int, [P, C.POINTER(cmcg_options), C.c_int, C.c_int, C.c_int, P, P, P]),
     "cmcg_debug_dot_noalloc": (C.c_int, [P, P, P, P, P]),
     "cmcg_debug_mfma": (C.c_int, [C.c_int, P, P, P, P]),
-    "cmcg_debug_period_counts": (C.c_int, [C.POINTER(C.c_int64)] * 2),
+    "cmcg_debug_period_counts": (C.c_int, [C.POINTER(C.c_int64)] * 3),
     "cmcg_debug_period_stall": (C.c_int, [P, C.c_double]),
     "cmcg_problem_lts_fine": (C.c_int, [P, C.POINTER(cmcg_options), P, C.POINTER(C.c_int64)]),
     "cmcg_problem_destroy": (None, [P]),
@@ -464,11 +464,11 @@ def cmcg_debug_mfma(precision: int, a_dev, b_dev, d_dev, stream=None):
     _check(_lib.cmcg_debug_mfma(int(precision), _ptr(a_dev), _ptr(b_dev), _ptr(d_dev), _stream(stream)))
 
 
-def cmcg_debug_period_counts() -> tuple[int, int]:
-    """Periods run as one launch on the current device so far: (done, restarted by stage launches)."""
-    c = [C.c_int64(), C.c_int64()]
+def cmcg_debug_period_counts(launches: bool = False):
+    """Periods run as one launch on the current device so far: (done, restarted by stage launches[, launches])."""
+    c = [C.c_int64() for _ in range(3)]
     _check(_lib.cmcg_debug_period_counts(*map(C.byref, c)))
-    return tuple(x.value for x in c)
+    return tuple(x.value for x in c[:3 if launches else 2])
 
 
 def cmcg_debug_period_stall(p: Problem, seconds: float):

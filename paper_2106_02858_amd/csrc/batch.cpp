@@ -31,13 +31,16 @@ struct Batch {
     DevBuf U, Y1, Y2, Acc, Fre, Fim, Kbuf;
     DevBuf Ulo;  // FP32 fields: bfloat16 low parts of U
     DevBuf vu, vr, vd, va, vw, vgs, vbest;
+    // active: flags [B], then the active members, longest period first [B], then how
+    // many of these take step m [Mmax], and their number
     DevBuf partial, dots, coefA, coefC, active, msteps, mtab, fw_re, fw_im;
+    int* order() const { return active.as<int>() + B; }
+    int* nlive(int m) const { return active.as<int>() + 2 * B + m; }
     std::unique_ptr<HostPinned> pin;
     hipStream_t cap = nullptr;
     std::map<int, hipGraphExec_t> graphs;
     bool no_capture = false;  // periods without a captured graph run eagerly
     bool resident_ok = false;  // periods may run as one launch
-    DevBuf order, nlive;       // the active members, longest period first; how many take step m (m = Mmax: all)
     int nactive = 0;
     std::unique_ptr<Resident> resident;
     ~Batch() {
@@ -87,7 +90,7 @@ StageArgs batch_args(Batch& bt) {
     a.nmembers = bt.B;
     a.active = bt.active.as<int>();
     a.msteps = bt.msteps.as<int>();
-    a.order = bt.order.as<int>();
+    a.order = bt.order();
     a.bstride = bt.n();
     a.gstride = bt.shared_geo ? 0 : (int64_t)geo_values(*bt.sp) * bt.sp->K;
     a.sstride = bt.n();
@@ -106,7 +109,7 @@ void enqueue_batch_period(Batch& bt, bool src, bool filt, hipStream_t st) {
     auto row = [&](int m, int s) { return tab + ((size_t)m * S + s) * B * kMemberParams; };
     for (int m = 0; m < bt.Mmax; ++m) {
         a.step = m;
-        a.nlive = bt.nlive.as<int>() + m;
+        a.nlive = bt.nlive(m);
         a.nrun = (int)std::count_if(bt.cfg.begin(), bt.cfg.end(), [&](const StepCfg& c) { return c.M > m; });
         if (bt.scheme == 2) {
             a.mode = RK2_S1;
@@ -157,7 +160,7 @@ void enqueue_batch_period(Batch& bt, bool src, bool filt, hipStream_t st) {
         } else {
             a.mode = RHS;
             a.step = -1;
-            a.nlive = bt.nlive.as<int>() + bt.Mmax;
+            a.nlive = bt.nlive(bt.Mmax);
             a.nrun = B;
             a.Y = bt.U.p;
             a.U = bt.U.p;
@@ -210,7 +213,8 @@ void run_batch_period(Batch& bt, bool src, bool filt, bool use_graph, hipStream_
 
 // The period of every active member as one launch, where that may be.
 Period resident_batch_period(Batch& bt, bool src, bool filt, bool use_graph, hipStream_t st) {
-    if (!use_graph || !bt.resident_ok || (bt.resident && bt.resident->off) || !resident_variant(*bt.sp))
+    if (!use_graph || !bt.resident_ok || !resident_variant(*bt.sp) ||
+        (bt.resident ? bt.resident->off : !resident_fits(*bt.sp, bt.nactive)))
         return Period::kRefused;
     if (!bt.resident) bt.resident.reset(new Resident());
     PeriodArgs a{};
@@ -230,7 +234,7 @@ Period resident_batch_period(Batch& bt, bool src, bool filt, bool use_graph, hip
     a.src_rows = src ? bt.src_rows : 0;
     a.filter = filt ? 1 : 0;
     a.msteps = bt.msteps.as<int>();
-    a.order = bt.order.as<int>();
+    a.order = bt.order();
     a.mtab = bt.mtab.as<double>();
     a.bstride = bt.n();
     a.gstride = bt.shared_geo ? 0 : (int64_t)geo_values(*bt.sp) * bt.sp->K;
@@ -299,21 +303,19 @@ void batch_axpby(Batch& bt, const std::vector<double>& a, const double* x, const
 }
 
 void set_active(Batch& bt, const std::vector<int>& act, hipStream_t st) {
-    CMCG_HIP(hipMemcpyAsync(bt.active.p, act.data(), bt.B * sizeof(int), hipMemcpyHostToDevice, st));
     std::vector<int> order;
     for (int b = 0; b < bt.B; ++b)
         if (act[b]) order.push_back(b);
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return bt.cfg[x].M > bt.cfg[y].M; });
     bt.nactive = (int)order.size();
-    std::vector<int> live(bt.Mmax + 1, 0);
+    std::vector<int> all(2 * bt.B + bt.Mmax + 1, 0);
+    std::copy(act.begin(), act.end(), all.begin());
+    std::copy(order.begin(), order.end(), all.begin() + bt.B);
+    int* live = all.data() + 2 * bt.B;
     for (int b : order) ++live[bt.cfg[b].M - 1];
     for (int m = bt.Mmax - 1; m > 0; --m) live[m - 1] += live[m];
     live[bt.Mmax] = bt.nactive;
-    bt.order.alloc(bt.B * sizeof(int));
-    bt.nlive.alloc(live.size() * sizeof(int));
-    if (bt.nactive)
-        CMCG_HIP(hipMemcpyAsync(bt.order.p, order.data(), order.size() * sizeof(int), hipMemcpyHostToDevice, st));
-    CMCG_HIP(hipMemcpyAsync(bt.nlive.p, live.data(), live.size() * sizeof(int), hipMemcpyHostToDevice, st));
+    CMCG_HIP(hipMemcpyAsync(bt.active.p, all.data(), all.size() * sizeof(int), hipMemcpyHostToDevice, st));
     CMCG_HIP(hipStreamSynchronize(st));
 }
 
@@ -405,7 +407,7 @@ void setup_batch(Batch& bt, cmcg_problem* const* probs, int B, const cmcg_option
     bt.dots.alloc(B * 8);
     bt.coefA.alloc(B * 8);
     bt.coefC.alloc(B * 8);
-    bt.active.alloc(B * sizeof(int));
+    bt.active.alloc((2 * B + bt.Mmax + 1) * sizeof(int));
     bt.msteps.alloc(B * sizeof(int));
     bt.pin.reset(new HostPinned(3 * (size_t)B + 16));
     {

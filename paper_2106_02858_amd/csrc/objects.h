@@ -129,6 +129,7 @@ enum class Period {
 // One-launch periods of a device since the process started.
 struct PeriodCounts {
     std::atomic<int64_t> done{0};       // ran to their end
+    std::atomic<int64_t> launches{0};   // a batch of triangles takes one per group of members
     std::atomic<int64_t> restarted{0};  // begun again from their start state, by stage launches
 };
 PeriodCounts& period_counts(int device);
@@ -253,8 +254,9 @@ void fill_step_table(std::vector<double>& tab, int B, int b, int Mmax, const Ste
 // for.  a's exchange fields are filled in here.  stall > 0 (cmcg_debug_period_stall): blocks
 // are left out, and the others wait that many seconds for them.
 Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stall, hipStream_t st);
-// Whether the periods of n problems like p are one-launch periods small enough
-// to run beside others.
+// Whether the period of n problems on s may be one launch; whether those of n
+// problems like p are, and small enough to run beside others.
+bool resident_fits(const SpaceData& s, int n);
 bool resident_small(const cmcg_problem* p, const StepCfg& c, const cmcg_options* o, int n);
 // Whether the current stage variant of a space leaves its periods to
 // run_resident (none chosen by hand, and the arithmetic is the same).

@@ -781,28 +781,53 @@ struct PeriodPlan {
     double share;  // of the device, per launch
 };
 
-// All members' blocks are on the device at once (triangles: those of one member
-// after the other).  Time per stage, one launch per period against one per
-// stage (us):
-//   FP32 P1 1296 tets 2.2 / 5.8, 3072 2.1 / 5.8, 10368 3.8 / 6.3;
-//   FP32 P2 3072 3.5 / 4.7, 10368 5.2 / 6.8, 15300 6.4 / 8.3;
-//   FP32 P3 384 3.7 / 4.7, 3072 4.4 / 5.8, 7600 5.7 / 8.3;
-//   FP64 P1 1296 2.8 / 6.3, 6000 6.1 / 6.7;
-//   FP64 P2 384 3.8 / 4.5, 1296 4.1 / 4.7, 3072 5.2 / 5.7, but 4374 6.7 / 5.9 and
-//   6000 8.7 / 7.2, so up to 350 blocks only (two FP64 words a value and the
-//   update's copy through LDS cost more than the launches they replace);
-//   FP64 P3 384 5.3 / 7.0, 3072 7.6 / 9.2, 4374 9.5 / 9.8.
+// Tetrahedra: all members' blocks are on the device at once.  Time per stage,
+// one launch per period against one per stage (us; cubes numbered cell by cell,
+// in Morton order and at random where three pairs stand):
+//   FP32 P1 3072 tets 2.1 / 5.8, 2.3 / 5.8, 2.8 / 6.3, 10368 3.8 / 6.3, 4.4 / 6.5, 4.8 / 7.4;
+//   FP32 P2 3072 3.5 / 4.7, 3.6 / 4.7, 4.3 / 5.2, 13182 5.9 / 7.6, 6.3 / 7.6, 8.8 / 9.0;
+//   FP32 P3 1296 3.9 / 4.8, 4.0 / 4.8, 4.5 / 5.1, 6000 5.7 / 7.4, 5.9 / 7.3, 7.5 / 8.9;
+//   FP64 P1 1296 2.8 / 6.3, 3.0 / 6.6, 3.3 / 6.8, 6000 6.1 / 6.7, 7.3 / 6.7, 6.7 / 7.8;
+//   FP64 P2 1296 4.1 / 4.7, 4.5 / 4.7, 5.0 / 4.9, 3072 5.3 / 5.7, 5.9 / 5.6, 6.9 / 6.5;
+//     4374 6.7 / 5.9, 6000 8.7 / 7.2;
+//   FP64 P3 1296 5.9 / 7.3, 6.4 / 7.2, 7.2 / 7.8, 3072 7.6 / 9.2, 8.4 / 8.9, 10.6 / 11.0;
+//     4374 9.6 / 9.9, 11.8 / 9.5, 12.9 / 11.2.
+// So FP64 P2 and P3 up to kBlocks64 blocks only (two words a value, and their
+// update's copy through LDS, cost more than the launches they replace).
 // Members in several groups, one after another, lose to stage launches that run
 // all members at once (FP32 P2, 16 members of 10368 tets: 156 ms a solve against
 // 102; FP64 P1, 16 of 1296: 50 against 27).
+//
+// Triangles: members in several groups, up to kGroups of them -- a group takes a
+// stage's exchange however few blocks it has, stage launches get cheaper per
+// member with their number.  ms a solve, stage launches / groups:
+//   P3 FP32 13924 triangles x 4 members (4 groups) 110 / 77, x 12 (12) 236 / 227, 1600 x 100 (7) 87 / 64;
+//   P3 FP64 10816 x 4 (4) 130 / 101, x 12 (12) 269 / 300, 19600 x 8 (8) 413 / 403;
+//   P2 FP32 16900 x 4 (4) 65 / 61, x 8 (8) 101 / 121, 7056 x 32 (8) 92 / 99;
+//   P2 FP64 10816 x 2 (2) 43 / 34, x 3 (3) 50 / 51, 19600 x 2 (2, full) 72.4 / 74.4;
+//   P1 FP32 19600 x 2 (2) 12.6 / 9.8, x 4 (4) 17.8 / 20.4, 1600 x 40 (2, full) 7.4 / 7.8;
+//   P1 FP64 10816 x 2 (1) 10.2 / 7.4, 19600 x 2 (2) 17.0 / 19.5.
+// Two groups that win only while they are not full: up to 13/8 of the device.
+// P1 FP64 alone, us a stage by cells and at random: 13456 3.2 / 5.0, 5.8 / 6.2, 19600 4.4 /
+// 5.2, 7.2 / 6.9, 24336 5.2 / 5.4, 8.5 / 7.3: up to three quarters of the device.
+constexpr int kBlocks64 = 350;
+constexpr int kGroups[kMaxQ + 1][2] = {{0, 0}, {1, 2}, {2, 4}, {6, 12}};  // [order][precision]
 static PeriodPlan plan_period(const SpaceData& s, int64_t room, int n) {
     const int64_t nb = (s.K + element_block(s.dim) - 1) / element_block(s.dim);
     const int64_t total = (nb + 7) / 8 * 8;  // workgroups of a member
-    const int64_t most = room / total;
-    PeriodPlan plan{(int)std::min<int64_t>(n, most), 0};
-    if (s.dim == 3 && (plan.at_once < n || (s.precision == CMCG_FP64 && s.q == 2 && nb * n > 350))) plan.at_once = 0;
-    plan.share = (double)(plan.at_once * total) / (double)std::max<int64_t>(room, 1);
-    return plan;
+    const int64_t most = std::min<int64_t>(n, room / total);
+    if (most == 0) return {0, 0};
+    const int groups = (int)((n + most - 1) / most);
+    const bool f64 = s.precision == CMCG_FP64;
+    if (s.dim == 3) {
+        if (groups > 1 || (f64 && s.q > 1 && nb * n > kBlocks64)) return {0, 0};
+    } else {
+        if (groups > kGroups[s.q][s.precision]) return {0, 0};
+        if (groups > 1 && kGroups[s.q][s.precision] == 2 && 8 * nb * n > 13 * room) return {0, 0};
+        if (f64 && s.q == 1 && n == 1 && 4 * nb > 3 * room) return {0, 0};
+    }
+    const int at_once = (n + groups - 1) / groups;  // groups of one size
+    return {at_once, (double)(at_once * total) / (double)room};
 }
 
 static int64_t room_of(const SpaceData& s) {
@@ -862,6 +887,7 @@ Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stal
             launch_period2d(s.q, s.precision, a, m, st);
         else
             launch_period(s.q, s.precision, a, m, st);
+        ++turn.counts.launches;
     }
     CMCG_HIP(hipStreamSynchronize(st));
     std::lock_guard<std::mutex> lk(turn.mu);
@@ -880,6 +906,7 @@ Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stal
 static bool resident_call(const cmcg_problem* p, const StepCfg& c, const cmcg_options* o) {
     return c.resident && o->use_graph != 0 && c.lts <= 1 && p->nharm == 1 && resident_variant(*p->sp);
 }
+bool resident_fits(const SpaceData& s, int n) { return plan_period(s, room_of(s), n).at_once > 0; }
 bool resident_small(const cmcg_problem* p, const StepCfg& c, const cmcg_options* o, int n) {
     if (!resident_call(p, c, o)) return false;
     const PeriodPlan plan = plan_period(*p->sp, room_of(*p->sp), n);
@@ -1906,12 +1933,13 @@ int cmcg_debug_mfma(int precision, const double* a, const double* b, double* d, 
     CMCG_GUARD_END
 }
 
-int cmcg_debug_period_counts(int64_t* done, int64_t* restarted) {
+int cmcg_debug_period_counts(int64_t* done, int64_t* restarted, int64_t* launches) {
     CMCG_GUARD_BEGIN
-    if (!done || !restarted) fail(CMCG_ERR_ARG, "debug_period_counts: NULL argument");
+    if (!done || !restarted || !launches) fail(CMCG_ERR_ARG, "debug_period_counts: NULL argument");
     const PeriodCounts& c = period_counts(current_device());
     *done = c.done;
     *restarted = c.restarted;
+    *launches = c.launches;
     return CMCG_OK;
     CMCG_GUARD_END
 }

@@ -271,3 +271,42 @@ def test_small_solve_beside_stage_launches(lib):
     lib.cmcg_debug_period_stall(small, 0)
     lib.cmcg_solve(small, lib.cmcg_options_default(fixed_iters=2))
     assert lib.cmcg_debug_period_counts()[0] > b[0]
+
+
+@pytest.mark.parametrize("q,precision,n,B,groups", [
+    (3, 1, 20, 30, 2), (3, 0, 20, 30, 3),   # 77 blocks a member; 1280 and 1024 fit
+    (2, 0, 20, 20, 2), (1, 1, 20, 30, 2),
+    (2, 0, 20, 30, 0), (1, 0, 20, 20, 0), (1, 1, 20, 60, 0),  # as many groups as lose to stage launches
+])
+def test_batch2d_groups(lib, q, precision, n, B, groups):
+    """Batches of triangles run in equal groups of members while these win
+    (groups = 0: they do not, the batch runs by stage launches)."""
+    import torch
+    print(f"groups q={q} prec={precision} B={B}", flush=True)
+    xy, tri, tags = inputs.cartesian_triangles(n, n)
+    K, Np = len(tri), (q + 1) * (q + 2) // 2
+    s = lib.cmcg_space_create(lib.cmcg_mesh2d_create(xy, tri, tags), q, precision)
+    probs = [_member(lib, s, 2, K, q, np.random.default_rng(b), 20.0 + b) for b in range(B)]
+    out = []
+    for g in (1, 0):
+        a = lib.cmcg_debug_period_counts(launches=True)
+        res = lib.cmcg_solve_batch(probs, lib.cmcg_options_default(fixed_iters=1, use_graph=g))
+        b = lib.cmcg_debug_period_counts(launches=True)
+        periods = lib.cmcg_result_stats(res[0])["periods"] if g and groups else 0
+        assert [y - x for x, y in zip(a, b)] == [periods, 0, periods * groups]
+        f = [[torch.zeros((K, 3, Np), dtype=torch.float64, device="cuda") for _ in range(2)] for _ in res]
+        for r, (x, y) in zip(res, f):
+            lib.cmcg_result_filtered_device(r, x, y)
+        out.append([x for pair in f for x in pair])
+    assert all(torch.isfinite(x).all() and torch.equal(x, y) for x, y in zip(*out))
+
+
+@pytest.mark.parametrize("n,one_launch", [(7, True), (8, True), (9, False)])
+@pytest.mark.parametrize("q", [2, 3])
+def test_fp64_block_limit(lib, q, n, one_launch):
+    """FP64 P2 and P3 run as one launch up to 350 blocks (n = 8: 308, n = 9: 438)."""
+    print(f"FP64 limit q={q} n={n}", flush=True)
+    mesh = inputs.cube_mesh(n)
+    s, p = _problem(lib, 3, mesh, q, 0, seed=3)
+    got = _period(lib, p, len(mesh[1]), 6, lib.cmcg_space_info(s)["Np"])
+    assert got == (int(one_launch), 0)
