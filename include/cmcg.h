@@ -427,7 +427,9 @@ int cmcg_debug_dot_noalloc(const cmcg_problem* p, const double* u_dev, const dou
  * filter period), so its result equals the one cmcg_solve returns.
  *
  * cmcg_problem_footprint: device bytes a solve of p keeps resident (problem
- *   data, field / filter / CG vectors, result) -- the admission cost; with
+ *   data, field / filter / CG vectors, result) -- the admission cost -- and,
+ *   where cmcg_solve has run p's periods as one launch, the exchange buffers
+ *   and step table it holds for them, which admission gives back; with
  *   local time stepping (o->lts_ratio > 1) the engine adds 12 field vectors
  *   and the fine-region masks and block lists.
  * cmcg_engine_create: budget = device bytes the engine may hold for admitted

@@ -94,6 +94,12 @@ size_t footprint(const cmcg_problem* p) {
     return b + (size_t)dot_partials() * 8 + 4096;
 }
 
+// Device bytes that one-launch periods of earlier solves of p still hold (the
+// exchange and the step table).  Slots run none, so admission gives them back.
+static size_t period_bytes(const cmcg_problem* p) {
+    return p->resident ? p->resident->xch.bytes + p->resident->mtab.bytes : 0;
+}
+
 // footprint with the work buffers local time stepping adds (Taylor
 // coefficients, frozen coarse terms, adjoint vectors; masks and block lists)
 size_t footprint(const cmcg_problem* p, const cmcg_options* o) {
@@ -150,7 +156,7 @@ extern "C" {
 int cmcg_problem_footprint(const cmcg_problem* p, size_t* bytes) {
     ENGINE_GUARD_BEGIN
     if (!p || !bytes) fail(CMCG_ERR_ARG, "problem_footprint: NULL argument");
-    *bytes = footprint(p);
+    *bytes = footprint(p) + period_bytes(p);
     return CMCG_OK;
     ENGINE_GUARD_END
 }
@@ -197,6 +203,7 @@ int cmcg_engine_admit(cmcg_engine* e, cmcg_problem* p, const cmcg_options* o, in
     auto& s = e->slots[free_slot];
     cmcg_options oe = *o;
     oe.autotune = 0;  // the stage variant is process-wide and slots run concurrently
+    p->resident.reset();
     s.run.reset(new CgRun());
     s.run->start(p, &oe, nullptr, s.st);
     s.state = 1;
@@ -243,6 +250,7 @@ int cmcg_engine_admit_batch(cmcg_engine* e, cmcg_problem* const* problems, int n
     if (free_slot < 0) fail(CMCG_ERR_NOMEM, "engine_admit_batch: no free slot");
     if (e->used + need > e->budget) fail(CMCG_ERR_NOMEM, "engine_admit_batch: over the memory budget");
     auto& s = e->slots[free_slot];
+    for (int b = 0; b < n; ++b) problems[b]->resident.reset();
     std::unique_ptr<BatchJob> job(new BatchJob());
     job->probs.assign(problems, problems + n);
     job->o = *o;

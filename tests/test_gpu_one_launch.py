@@ -310,3 +310,27 @@ def test_fp64_block_limit(lib, q, n, one_launch):
     s, p = _problem(lib, 3, mesh, q, 0, seed=3)
     got = _period(lib, p, len(mesh[1]), 6, lib.cmcg_space_info(s)["Np"])
     assert got == (int(one_launch), 0)
+
+
+def test_footprint_counts_what_one_launch_periods_hold(lib):
+    """A plain solve leaves exchange buffers and a step table with the problem;
+    its footprint says so, and the engine, whose slots run none, gives them back."""
+    print("footprint", flush=True)
+    mesh = _mesh3d("shuffled")
+    s, p = _problem(lib, 3, mesh, 2, 1, seed=8)
+    K = len(mesh[1])
+    before = lib.cmcg_problem_footprint(p)
+    o = lib.cmcg_options_default(fixed_iters=1)
+    lib.cmcg_solve(p, o)
+    M = lib.cmcg_problem_steps(p, o)[0]
+    held = lib.cmcg_problem_footprint(p) - before
+    # two buffers of 8-byte pairs for the 6 x 6 values of every cut face, and 9 scalars per stage
+    assert 2 * 8 * 36 * 2 * K < held - (M + 1) * 4 * 9 * 8 <= 2 * 8 * 36 * 4 * K + 64
+    e = lib.cmcg_engine_create(before, 2)
+    slot = lib.cmcg_engine_admit(e, p, o)
+    assert slot is not None and lib.cmcg_engine_info(e)["used"] == before
+    assert lib.cmcg_problem_footprint(p) == before
+    while lib.cmcg_engine_poll(e, slot) == 1:
+        lib.cmcg_engine_step(e)
+    lib.cmcg_engine_collect(e, slot, p)
+    assert _period(lib, p, K, 6, 10) == (1, 0)
