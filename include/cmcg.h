@@ -500,9 +500,10 @@ int cmcg_engine_collect_batch(cmcg_engine* e, int slot, cmcg_result** results, i
  * (v_mfma_f32_4x4x1, a wave per four nodes of a 10-element block) and one for
  * FP64 fields (v_mfma_f64_16x16x4, a wave per 16 columns), run by 2..5, 8 and 9
  * and for q = 3 by 6 and 7 alike; variants that do not exist for
- * (q, precision) fall back to 0; -1 chooses per launch from its size
- * (workgroups of 10 elements over all members), the form the autotuner's
- * timings favour there.  All compute the same Phi(t, Y) and stage update.
+ * (q, precision) fall back to 0; -1 is the matrix-core kernel, under the
+ * number that cmcg_tune_resolve_stage gives for the launch's size (workgroups
+ * of 10 elements over all members).  All compute the same Phi(t, Y) and stage
+ * update.
  * A whole period may also run as one launch with the stage kernels' arithmetic
  * (use_graph, meshes whose element blocks fit on the device at once) unless a
  * variant other than the default was set here.
@@ -516,12 +517,12 @@ int cmcg_tune_stage(int q, int precision, int variant);
 int cmcg_tune_get_stage(int q, int precision, int* variant);
 int cmcg_tune_resolve_stage(int q, int precision, int64_t K, int members, int* variant);
 
-/* Autotuner: times every stage-kernel variant that applies to p's (q,
- * precision) on p's own launch shape -- up to 8 homogeneous time steps on
+/* Autotuner: times every stage kernel that the variants of p's (q, precision)
+ * stand for on p's own launch shape -- up to 8 homogeneous time steps on
  * its mesh and work buffers (o's scheme and step rule; o may be NULL), one
  * warm-up run and the best of two timed runs (HIP events on `stream`) per
- * variant -- keeps the fastest as the process-wide choice for (q, precision)
- * (as cmcg_tune_stage does) and returns it in *variant.  us_per_launch
+ * kernel -- keeps the fastest as the process-wide choice for (q, precision)
+ * (as cmcg_tune_stage does) and returns its lowest variant in *variant.  us_per_launch
  * (nullable, CMCG_STAGE_VARIANTS entries) receives each variant's average
  * stage-launch time in microseconds, 0 for variants that do not apply.  Overwrites p's work
  * buffers, not its data; must not overlap a solve of p or any solve of the

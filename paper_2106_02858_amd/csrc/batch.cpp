@@ -173,9 +173,8 @@ void enqueue_batch_period(Batch& bt, bool src, bool filt, hipStream_t st) {
 }
 
 int batch_graph_key(const Batch& bt, bool src, bool filt) {
-    // keyed by the stage variant as well: it is read when the launches are enqueued
-    const int variant = bt.sp->dim == 3 ? get_stage_variant(bt.sp->q, bt.sp->precision) : 0;
-    return (variant << 4) | (src ? 2 : 0) | (filt ? 1 : 0);
+    // keyed by the stage kernel as well: it is chosen when the launches are enqueued
+    return (stage_kernel(*bt.sp) << 4) | (src ? 2 : 0) | (filt ? 1 : 0);
 }
 
 // the captured period for (src, filt), captured now if missing

@@ -229,10 +229,14 @@ struct CgRun {
 // best iterate and reports CMCG_NOT_CONVERGED.
 constexpr double kDivergence = 100.0;
 
+// The stage kernel that the current variant of a space stands for (several
+// variants share one): what captured periods are keyed by.
+int stage_kernel(const SpaceData& s);
 // Stage-variant autotuner (solver.cpp): runs `run` (which enqueues
-// `nlaunch` stage launches, the same ones each call) under every variant that
-// applies to (q, precision), keeps the fastest as the process-wide choice and
-// returns it; us[v] = average microseconds per launch, 0 where v does not apply.
+// `nlaunch` stage launches, the same ones each call) with every kernel that the
+// variants of (q, precision) stand for, keeps the fastest as the process-wide
+// choice and returns its lowest variant; us[v] = average microseconds per launch,
+// 0 where v does not apply.
 int time_stage_variants(int q, int precision, hipStream_t st, const std::function<void()>& run, int nlaunch,
                         double* us);
 // Cached choice for (device, q, precision, K, members): applies it and returns

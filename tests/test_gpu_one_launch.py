@@ -334,3 +334,23 @@ def test_footprint_counts_what_one_launch_periods_hold(lib):
         lib.cmcg_engine_step(e)
     lib.cmcg_engine_collect(e, slot, p)
     assert _period(lib, p, K, 6, 10) == (1, 0)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("q", [1, 2, 3])
+def test_autotuner_times_every_kernel_once(lib, q, precision):
+    """Variants that stand for one kernel get one time; the choice is the lowest
+    of the fastest kernel's."""
+    print(f"autotune q={q} prec={precision}", flush=True)
+    mesh = _mesh3d("shuffled")
+    _, p = _problem(lib, 3, mesh, q, precision, seed=9)
+    saved = lib.cmcg_tune_get_stage(q, precision)
+    try:
+        v, us = lib.cmcg_autotune_stage(p)
+    finally:
+        lib.cmcg_tune_stage(q, precision, saved)
+    us = list(us)
+    assert us[0] > 0 and us[1] > 0
+    rest = [x for i, x in enumerate(us) if i > 1 and not (q == 2 and i in (6, 7))]
+    assert len(set(rest)) == 1 and (rest[0] > 0) == (q > 1)
+    assert us[v] == min(x for x in us if x > 0) and v <= 2
