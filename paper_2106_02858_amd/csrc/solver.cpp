@@ -849,7 +849,13 @@ static PeriodPlan resident_plan(Resident& r, const SpaceData& s, int n) {
 Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stall, hipStream_t st) {
     const PeriodPlan plan = resident_plan(r, s, n);
     if (plan.at_once == 0) return Period::kRefused;
-    std::call_once(s.x_once, [&] { build_mailboxes(s, st); });
+    try {
+        std::call_once(s.x_once, [&] { build_mailboxes(s, st); });
+    } catch (const Error& e) {
+        if (e.code != CMCG_ERR_NOMEM) throw;
+        r.off = true;  // no room for the mailboxes: stage launches need none
+        return Period::kRefused;
+    }
     const size_t vals = (size_t)a.members * s.next * (s.dim == 2 ? 3 : 6) * s.Nfp;
     if (vals > (size_t)kPeriodMaxValues) {
         r.off = true;
