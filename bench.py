@@ -88,18 +88,21 @@ def parse():
 
 # FETCH_SIZE / WRITE_SIZE per dispatch (KiB) of the stage kernel on the
 # 48000-tet P3 FP32 problem, with the scales a 1 GiB copy gives each counter;
-# valid only for the kernel source they were taken on (SHA-256 below).
-_SHA_3D = "2c4498974c2f0d043dccbcc0390e9a7c3b585c9c7bb9cd7cce751c9951693fae"
+# valid only for the kernel source they were taken on (SHA-256 below) and the
+# headers its kernels are built from (SHA-256 of these, one after another).
+KERNEL_HEADERS = ("internal.h", "launch.h", "mfma_cols.h", "tagged.h")
+_SHA_HEADERS = "2a54f4821f1ae32eacfed5d8c1fc86662c835ae53faab031d6092915b2ec5604"
+_SHA_3D = "05b464b82922169ce987a2d4ff7f733c3ac843a162eb477ef374f4f0ae4fcda1"
 MEASURED_TRAFFIC = [
-    {"kernels_sha256": _SHA_3D, "kernel": "k_stage_col<3,false,false>", "K": 48000,
-     "fetch_kib": 40859.20, "fetch_scale": 2.0000, "write_kib": 42187.52, "write_scale": 1.0000},
+    {"kernels_sha256": _SHA_3D, "headers_sha256": _SHA_HEADERS, "kernel": "k_stage_col<3,false,false>", "K": 48000,
+     "fetch_kib": 40852.69, "fetch_scale": 2.0000, "write_kib": 42187.53, "write_scale": 1.0000},
 ]
 
 
 # The same for the FP64 stage kernel of the plain FP64 solve (48000 tets, P3).
 MEASURED_TRAFFIC_FP64 = [
-    {"kernels_sha256": _SHA_3D, "kernel": "k_stage_tile<3,false,false>", "K": 48000,
-     "fetch_kib": 72814.76, "fetch_scale": 2.0000, "write_kib": 78750.00, "write_scale": 1.0000},
+    {"kernels_sha256": _SHA_3D, "headers_sha256": _SHA_HEADERS, "kernel": "k_stage_tile<3,false,false>", "K": 48000,
+     "fetch_kib": 72813.59, "fetch_scale": 2.0000, "write_kib": 78750.00, "write_scale": 1.0000},
 ]
 
 
@@ -108,38 +111,45 @@ MEASURED_TRAFFIC_FP64 = [
 # mesh, every member active (K = members x elements; every kernel the batched
 # autotuner times).
 MEASURED_TRAFFIC_Q2 = [
-    {"kernels_sha256": _SHA_3D, "kernel": k, "K": K,
+    {"kernels_sha256": _SHA_3D, "headers_sha256": _SHA_HEADERS, "kernel": k, "K": K,
      "fetch_kib": fe, "fetch_scale": 2.0000, "write_kib": wr, "write_scale": 1.0000}
-    for k, K, fe, wr in (("k_stage_col<2,false,false>", 1572864, 777821.23, 702144.21),
-                         ("k_stage_col<2,false,false>", 64 * 10368, 247441.27, 297147.80),
-                         ("k_stage<float,2,false,false>", 64 * 10368, 284494.56, 292220.96),
-                         ("k_stage<float,2,true,false>", 64 * 10368, 252853.07, 291673.67))
+    for k, K, fe, wr in (("k_stage_col<2,false,false>", 1572864, 777358.74, 703165.36),
+                         ("k_stage_col<2,false,false>", 64 * 10368, 247115.42, 297248.31),
+                         ("k_stage<float,2,false,false>", 64 * 10368, 283493.78, 292155.76),
+                         ("k_stage<float,2,true,false>", 64 * 10368, 251989.94, 291654.83))
 ]
 
 
 # The same for the 2-D stage kernel on the 22500-triangle disk trap (P3, FP32).
 MEASURED_TRAFFIC_2D = {
     "kernels_sha256": "d164e1ced27782784e199c6bdbd0a345f0a4c997447bd37c89c82a901bcc7291",
-    "kernel": "k_stage2d<float,3,true>", "K": 22500,
+    "headers_sha256": _SHA_HEADERS, "kernel": "k_stage2d<float,3,true>", "K": 22500,
     "fetch_kib": 5076.50, "fetch_scale": 2.0000, "write_kib": 4944.12, "write_scale": 1.0000,
 }
 
 
 def measured_traffic(kernel: str, K: int, table=None, source: str = "kernels.hip"):
     """HBM bytes per launch from the committed counter runs (a table or a list
-    of tables, one per measured kernel), or None when the kernel source or
-    the workload differs from every one measured."""
+    of tables, one per measured kernel), or None when the kernel source, one of
+    its headers or the workload differs from every one measured."""
     import hashlib
     tables = MEASURED_TRAFFIC if table is None else table
     tables = tables if isinstance(tables, list) else [tables]
-    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2106_02858_amd", "csrc", source)
+    csrc = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2106_02858_amd", "csrc")
+
+    def digest(names):
+        h = hashlib.sha256()
+        for name in names:
+            with open(os.path.join(csrc, name), "rb") as f:
+                h.update(f.read())
+        return h.hexdigest()
+
     try:
-        with open(src, "rb") as f:
-            digest = hashlib.sha256(f.read()).hexdigest()
+        kernels, headers = digest([source]), digest(KERNEL_HEADERS)
     except OSError:
         return None
     for t in tables:
-        if digest == t["kernels_sha256"] and kernel == t["kernel"] and K == t["K"]:
+        if kernels == t["kernels_sha256"] and headers == t["headers_sha256"] and kernel == t["kernel"] and K == t["K"]:
             return (t["fetch_kib"] * t["fetch_scale"] + t["write_kib"] * t["write_scale"]) * 1024
     return None
 

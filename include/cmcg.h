@@ -384,8 +384,9 @@ int cmcg_debug_dot(cmcg_problem* p, const double* u_dev, const double* v_dev, do
                    hipStream_t stream);
 /* One 16x16x4 matrix-core product D = A B (v_mfma_f64_16x16x4f64 for
  * CMCG_FP64, v_mfma_f32_16x16x4f32 for CMCG_FP32 with the inputs rounded to
- * FP32) through the operand and accumulator lane layout the matrix-core stage
- * kernels assume.  a_dev [16][4], b_dev [4][16], d_dev [16][16]: row-major
+ * FP32) through the operand and accumulator lane layout that the FP64 stage
+ * kernels assume (the FP32 ones run v_mfma_f32_4x4x1 with broadcast matrices;
+ * comparisons of whole right-hand sides with the oracle check those).  a_dev [16][4], b_dev [4][16], d_dev [16][16]: row-major
  * FP64 device arrays; synchronous on return.  Errors: CMCG_ERR_ARG (NULL,
  * unknown precision). */
 int cmcg_debug_mfma(int precision, const double* a_dev, const double* b_dev, double* d_dev, hipStream_t stream);

@@ -5,6 +5,8 @@
     python -m paper_2106_02858_amd.counters --fp64        # FP64 fields (either problem)
     python -m paper_2106_02858_amd.counters --scatterer   # the 1,572,864-tet P2 scatterer, one period
     python -m paper_2106_02858_amd.counters --batched     # 64 members on the 10368-tet P2 mesh
+    python -m paper_2106_02858_amd.counters --trap2d --one-launch   # periods as one launch: triangles
+    python -m paper_2106_02858_amd.counters --n 6 --q 1 --fp64      # and tets (meshes that fit run this way)
 
 Runs whole homogeneous periods (4 M stage launches each) of the large
 single-solve problem (48000 tets, P3, FP32 fields) -- or, with --trap2d, of
@@ -31,6 +33,7 @@ def main() -> int:
     ap.add_argument("--copy-mib", type=int, default=1024)
     ap.add_argument("--copies", type=int, default=4)
     ap.add_argument("--trap2d", action="store_true")
+    ap.add_argument("--one-launch", action="store_true", help="with --trap2d: each period as one launch")
     ap.add_argument("--fp64", action="store_true")
     ap.add_argument("--scatterer", action="store_true",
                     help="one homogeneous period of the 1,572,864-tet P2 scatterer (FP32 fields)")
@@ -58,7 +61,7 @@ def main() -> int:
               flush=True)
         U0 = torch.randn((K, 3, Np), dtype=torch.float64, device=dev) * 1e-3
         UT = torch.empty_like(U0)
-        opts = cmcg.cmcg_options_default(use_graph=0)  # stage launches (with use_graph the period is one launch)
+        opts = cmcg.cmcg_options_default(use_graph=int(a.one_launch))  # 0: stage launches
         for _ in range(a.periods):
             cmcg.cmcg_debug_period(p, U0, UT, 1, False, opts=opts)
         torch.cuda.synchronize()

@@ -789,7 +789,7 @@ template <typename T, int Q, int NTH, bool LTSM, int STREAM> struct MfmaUpdateIn
             if (needA) r1[t] = ldg<STREAM == 2, V>((const T*)a.Acc + gi);
             if constexpr (LTSM) {
                 // all at once: behind one another, at the end, they added up to
-                // four memory latencies to every substep launch (P2 FP64, 12096
+                // four memory latencies to every substep launch (P2 FP64, 12960
                 // tets, four substeps: 107.1 ms a solve against 104.2)
                 if (mode != LTS_CHAIN && !(mode == LTS_ADJ && a.linit)) {
 #pragma unroll
@@ -1877,8 +1877,8 @@ template <typename T, int Q, int NTH, int RS> struct PeriodFaces {
         bool ok;
         if constexpr (Q == 1) {
             // values beyond the tracked ones are requested before those are waited
-            // for (randomly numbered 1296 tets FP64: 1.87 -> 1.59 us a stage; cube
-            // order, where there are none, 1.41 -> 1.35.  P2 and P3, which track
+            // for (randomly numbered 1296 tets FP64: 3.7 -> 3.2 us a stage; cube
+            // order, where there are none, 2.8 -> 2.7.  P2 and P3, which track
             // more: 4.2 -> 4.9 and 5.2 -> 5.8 us)
             constexpr int RX = (8 * CF + NTH - 1) / NTH;
             Inbox<T, RX, NTH> more;
@@ -2397,8 +2397,8 @@ __global__ __launch_bounds__(256) void k_period_p1(PeriodArgs a, int64_t per) {
     }
 }
 
-// One 16x16x4 matrix-core product with the lane layout the stage kernels
-// assume (a single 64-lane wave): lane l takes A[l % 16][l / 16] and
+// One 16x16x4 matrix-core product with the lane layout that k_stage_tile and
+// k_period_tile assume in FP64 (a single 64-lane wave): lane l takes A[l % 16][l / 16] and
 // B[l / 16][l % 16] and returns D[Mfma<T>::row(l / 16, r)][l % 16], r = 0..3.
 template <typename T>
 __global__ __launch_bounds__(64) void k_mfma_probe(const double* __restrict__ A, const double* __restrict__ B,

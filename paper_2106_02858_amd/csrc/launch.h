@@ -169,15 +169,14 @@ void launch_lts_closed(int precision, int64_t n, int np6, int Np, const uint32_t
 //   wbar_close: rows off the mask: wb_j = al_j zbar
 void launch_lts_wbar_close(int precision, int64_t n, int np6, const uint32_t* mask, const void* zbar,
                            void* const* wb, const double* al, int nw, hipStream_t s);
-// D[16][16] = A[16][4] B[4][16] on one matrix-core instruction of the field
-// precision, through the lane layout the stage kernels use (FP64 in and out).
+// D[16][16] = A[16][4] B[4][16] on one 16x16x4 matrix-core instruction of the
+// field precision, through the lane layout the FP64 kernels use (FP64 in and out).
 void launch_mfma_probe(int precision, const double* A, const double* B, double* D, hipStream_t s);
 void set_stage_variant(int q, int precision, int variant);
 int get_stage_variant(int q, int precision);
 // the variant a launch over K elements and `members` members runs
 int resolve_stage_variant(int q, int precision, int64_t K, int members);
-constexpr int kStageVariants = CMCG_STAGE_VARIANTS;  // 2, 3: matrix cores (q >= 2; 3 gathers one face
-                                                     // ahead); 4: as 3 with two waves per block (q >= 2)
+constexpr int kStageVariants = CMCG_STAGE_VARIANTS;  // 0, 1: k_stage; from 2 on, for q >= 2, the matrix cores
 
 // FP64 <-> field precision; flipH negates the magnetic rows (the S of P* = S P S).
 // FP32: Ulo (nullable) receives / contributes the bfloat16 low part.
