@@ -91,18 +91,18 @@ def parse():
 # valid only for the kernel source they were taken on (SHA-256 below) and the
 # headers its kernels are built from (SHA-256 of these, one after another).
 KERNEL_HEADERS = ("internal.h", "launch.h", "mfma_cols.h", "tagged.h")
-_SHA_HEADERS = "2a54f4821f1ae32eacfed5d8c1fc86662c835ae53faab031d6092915b2ec5604"
-_SHA_3D = "05b464b82922169ce987a2d4ff7f733c3ac843a162eb477ef374f4f0ae4fcda1"
+_SHA_HEADERS = "b02d093afcf0e0265bf591f1e0143637e2fae9ccb758f134810cf17f380dd89a"
+_SHA_3D = "447b8000d5a129442370ca1cefb6d194ef0b3d428ca297cf4e8eb3ab16b16538"
 MEASURED_TRAFFIC = [
     {"kernels_sha256": _SHA_3D, "headers_sha256": _SHA_HEADERS, "kernel": "k_stage_col<3,false,false>", "K": 48000,
-     "fetch_kib": 40852.69, "fetch_scale": 2.0000, "write_kib": 42187.53, "write_scale": 1.0000},
+     "fetch_kib": 40867.26, "fetch_scale": 2.0000, "write_kib": 42187.53, "write_scale": 1.0000},
 ]
 
 
 # The same for the FP64 stage kernel of the plain FP64 solve (48000 tets, P3).
 MEASURED_TRAFFIC_FP64 = [
     {"kernels_sha256": _SHA_3D, "headers_sha256": _SHA_HEADERS, "kernel": "k_stage_tile<3,false,false>", "K": 48000,
-     "fetch_kib": 72813.59, "fetch_scale": 2.0000, "write_kib": 78750.00, "write_scale": 1.0000},
+     "fetch_kib": 72833.58, "fetch_scale": 2.0000, "write_kib": 78750.00, "write_scale": 1.0000},
 ]
 
 
@@ -113,16 +113,16 @@ MEASURED_TRAFFIC_FP64 = [
 MEASURED_TRAFFIC_Q2 = [
     {"kernels_sha256": _SHA_3D, "headers_sha256": _SHA_HEADERS, "kernel": k, "K": K,
      "fetch_kib": fe, "fetch_scale": 2.0000, "write_kib": wr, "write_scale": 1.0000}
-    for k, K, fe, wr in (("k_stage_col<2,false,false>", 1572864, 777358.74, 703165.36),
-                         ("k_stage_col<2,false,false>", 64 * 10368, 247115.42, 297248.31),
-                         ("k_stage<float,2,false,false>", 64 * 10368, 283493.78, 292155.76),
-                         ("k_stage<float,2,true,false>", 64 * 10368, 251989.94, 291654.83))
+    for k, K, fe, wr in (("k_stage_col<2,false,false>", 1572864, 777855.63, 702172.48),
+                         ("k_stage_col<2,false,false>", 64 * 10368, 247445.37, 297146.89),
+                         ("k_stage<float,2,false,false>", 64 * 10368, 284351.92, 292229.97),
+                         ("k_stage<float,2,true,false>", 64 * 10368, 252784.25, 291672.70))
 ]
 
 
 # The same for the 2-D stage kernel on the 22500-triangle disk trap (P3, FP32).
 MEASURED_TRAFFIC_2D = {
-    "kernels_sha256": "d164e1ced27782784e199c6bdbd0a345f0a4c997447bd37c89c82a901bcc7291",
+    "kernels_sha256": "ec90df3e7af0847b8a3e48b5249df6d2359dcd719fc4dfeb296af1c360257dcd",
     "headers_sha256": _SHA_HEADERS, "kernel": "k_stage2d<float,3,true>", "K": 22500,
     "fetch_kib": 5076.50, "fetch_scale": 2.0000, "write_kib": 4944.12, "write_scale": 1.0000,
 }

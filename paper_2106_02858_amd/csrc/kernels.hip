@@ -2966,9 +2966,9 @@ int64_t period_room(int q, int precision) {
     return period_kernel(q, precision, [](auto kernel, int threads) { return resident_room(kernel, threads); });
 }
 
-void launch_period(int q, int precision, const PeriodArgs& a, int n, hipStream_t s) {
+void launch_period(int q, int precision, const PeriodArgs& a, int n, int left_out, hipStream_t s) {
     period_kernel(q, precision, [&](auto kernel, int threads) {
-        launch_resident(kernel, (a.K + EPW - 1) / EPW, n, threads, a, s);
+        launch_resident(kernel, (a.K + EPW - 1) / EPW, n, left_out, threads, a, s);
     });
 }
 

@@ -1124,8 +1124,10 @@ int64_t period_room2d(int q, int precision) {
     return period2d_kernel(q, precision, [](auto kernel) { return resident_room(kernel, 256); });
 }
 
-void launch_period2d(int q, int precision, const PeriodArgs& a, int n, hipStream_t s) {
-    period2d_kernel(q, precision, [&](auto kernel) { launch_resident(kernel, (a.K + EPB - 1) / EPB, n, 256, a, s); });
+void launch_period2d(int q, int precision, const PeriodArgs& a, int n, int left_out, hipStream_t s) {
+    period2d_kernel(q, precision, [&](auto kernel) {
+        launch_resident(kernel, (a.K + EPB - 1) / EPB, n, left_out, 256, a, s);
+    });
 }
 
 void launch_to_field2d(int precision, int Np, const double* X, void* U, void* Ulo, int64_t n, int flipH,

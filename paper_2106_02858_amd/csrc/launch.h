@@ -68,8 +68,6 @@ struct StageArgs {
     const int* msteps;      // steps per period of each member
     int step;               // time step of this launch; -1 skips the step check
     int nrun = 0;           // members that take this step (0: all of them)
-    const int* order;       // the active members, those with the most steps first ...
-    const int* nlive;       // ... and how many of them take this step (device memory: it outlives a capture)
     int64_t bstride;        // field elements between consecutive members
     int64_t gstride;        // geometry elements between members (0: shared)
     int64_t sstride;        // source elements between members
@@ -101,6 +99,9 @@ struct StageArgs {
     const uint32_t* lmaskB;
     const uint32_t* lmaskC;
     int linv, linvB, linvC;  // LTS_CHAIN: inversions of lmask, lmaskB, lmaskC
+    // batched launches: the active members, those with the most steps first, and
+    // how many of them take this step (device memory: it outlives a capture)
+    const int *order, *nlive;
 };
 constexpr int kMaxHarm = 8;
 // per-member scalars of a batched stage: cy, ca, cu, scos, ssin, fa_re, fa_im, fb_re, fb_im
@@ -140,7 +141,6 @@ struct PeriodArgs {
     uint32_t* abort;         // device word: the epoch of a launch that gives up
     int* failed;             // host-visible: set to 1 when the launch gave up (its output is then void)
     unsigned long long limit;  // longest wait for a neighbour, in wall-clock ticks
-    int left_out = 0;          // host: blocks at the end of each XCD's range that are not launched (tests)
 };
 constexpr int64_t kPeriodMaxValues = 1 << 26;  // exchanged values of one buffer (32-bit offsets)
 // Elements of one workgroup of the stage and period kernels.
@@ -230,11 +230,12 @@ void launch_nonfinite(const double* X, int64_t n, int* out_dev, hipStream_t s);
 void upload_constants2d(int q, const double* D, const double* LIFT, const double* M, const int* fnode);
 void launch_stage2d(int q, int precision, const StageArgs& a, hipStream_t s);
 // One period of n members (a.order from a.first on) in one launch; all of its
-// workgroups have to be on the device at once, and period_room says how many may be.
+// workgroups have to be on the device at once, and period_room says how many may
+// be.  left_out: blocks at the end of each XCD's range that are not launched (tests).
 int64_t period_room(int q, int precision);    // tetrahedra
 int64_t period_room2d(int q, int precision);  // triangles
-void launch_period(int q, int precision, const PeriodArgs& a, int n, hipStream_t s);
-void launch_period2d(int q, int precision, const PeriodArgs& a, int n, hipStream_t s);
+void launch_period(int q, int precision, const PeriodArgs& a, int n, int left_out, hipStream_t s);
+void launch_period2d(int q, int precision, const PeriodArgs& a, int n, int left_out, hipStream_t s);
 void launch_to_field2d(int precision, int Np, const double* X, void* U, void* Ulo, int64_t n, int flipH,
                        hipStream_t s);
 void launch_from_field2d(int precision, int Np, const void* U, const void* Ulo, double* Y, const double* sub,

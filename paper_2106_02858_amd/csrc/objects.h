@@ -117,7 +117,6 @@ struct Resident {
     HostPinned failed{1};    // [0]: set by a launch that gave up
     uint32_t epoch = 0;      // the last one used
     int tab_M = 0, tab_scheme = 0;
-    int64_t room = 0;        // workgroups of the period kernel that the device holds (0: not asked yet)
     bool off = false;        // no room for the exchange
 };
 enum class Period {

@@ -837,13 +837,15 @@ static PeriodPlan plan_period(const SpaceData& s, int64_t room, int n) {
     return {at_once, (double)(at_once * total) / (double)room};
 }
 
+// Workgroups of the space's period kernel that its device holds (asked once).
 static int64_t room_of(const SpaceData& s) {
-    return s.dim == 2 ? period_room2d(s.q, s.precision) : period_room(s.q, s.precision);
+    static std::atomic<int64_t> room[64][2][kMaxQ + 1][2];
+    std::atomic<int64_t>& r = room[s.device][s.dim - 2][s.q][s.precision];
+    if (r == 0) r = s.dim == 2 ? period_room2d(s.q, s.precision) : period_room(s.q, s.precision);
+    return r;
 }
-static PeriodPlan resident_plan(Resident& r, const SpaceData& s, int n) {
-    if (r.off) return {0, 0};
-    if (r.room == 0) r.room = room_of(s);
-    return plan_period(s, r.room, n);
+static PeriodPlan resident_plan(const Resident& r, const SpaceData& s, int n) {
+    return r.off ? PeriodPlan{0, 0} : plan_period(s, room_of(s), n);
 }
 
 Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stall, hipStream_t st) {
@@ -885,7 +887,6 @@ Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stal
     a.failed = (int*)r.failed.p;
     a.epoch = r.epoch + 1;
     a.limit = (unsigned long long)((stall > 0 ? stall : kResidentWait) * 1e3 * khz);
-    a.left_out = stall > 0 ? 1 : 0;
     ResidentTurn& turn = g_resident[s.device];
     if (!turn.enter(plan.share)) return Period::kRefused;
     struct Leave {
@@ -897,9 +898,9 @@ Period run_resident(Resident& r, SpaceData& s, PeriodArgs& a, int n, double stal
     for (a.first = 0; a.first < n; a.first += plan.at_once) {
         const int m = std::min(plan.at_once, n - a.first);
         if (s.dim == 2)
-            launch_period2d(s.q, s.precision, a, m, st);
+            launch_period2d(s.q, s.precision, a, m, stall > 0 ? 1 : 0, st);
         else
-            launch_period(s.q, s.precision, a, m, st);
+            launch_period(s.q, s.precision, a, m, stall > 0 ? 1 : 0, st);
         ++turn.counts.launches;
     }
     CMCG_HIP(hipStreamSynchronize(st));

@@ -147,9 +147,10 @@ template <typename F> inline int64_t resident_room(F kernel, int threads) {
 // Launches a period kernel over nblocks element blocks and n members (those of
 // a.order from a.first on).
 template <typename F>
-inline void launch_resident(F kernel, int64_t nblocks, int n, int threads, const PeriodArgs& a, hipStream_t s) {
+inline void launch_resident(F kernel, int64_t nblocks, int n, int left_out, int threads, const PeriodArgs& a,
+                            hipStream_t s) {
     const int64_t per = (nblocks + 7) / 8;
-    const dim3 grid((unsigned)(8 * (per - a.left_out)), (unsigned)n);
+    const dim3 grid((unsigned)(8 * (per - left_out)), (unsigned)n);
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, a, per);
     CMCG_HIP(hipGetLastError());
 }
