@@ -1245,7 +1245,7 @@ template <int Q> struct TileIn {
     }
 };
 
-template <int Q, bool MH, bool LTSM, int STREAM>
+template <int Q, bool MH, bool LTSM, int STREAM, bool BATCH = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TileDim<Q>::occ(LTSM), 8)))
 void k_stage_tile(StageArgs args, int64_t per) {
     using TD = TileDim<Q>;
@@ -1254,15 +1254,18 @@ void k_stage_tile(StageArgs args, int64_t per) {
     __shared__ __align__(16) TileShared<Q> sh;
 
     // the workgroup's blocks: index, index + step, .. of its XCD's range, of one
-    // member: a batch's workgroups are dealt out to the members that take the step
-    int index = blockIdx.x >> 3, step = gridDim.x >> 3;
+    // member: a batch's workgroups (BATCH) are dealt out to the members that take
+    // the step.  A form of its own: in one, single launches took 0.4 % longer.  The
+    // test of mtab, which batches always have, keeps the compiler's schedule of
+    // the loop: without it they took 5 % longer.
+    unsigned index = blockIdx.x >> 3, step = gridDim.x >> 3;
     StageArgs a;
-    if constexpr (LOOP) {
+    if constexpr (BATCH) {
         a = args;
         if (args.mtab) {
-            const int live = *args.nlive;
+            const unsigned live = *args.nlive;
             if (live == 0) return;
-            const int m = index % live;
+            const unsigned m = index % live;
             step = (step - m + live - 1) / live;
             index /= live;
             member_offsets<double>(args, args.order[m], a);
@@ -2775,8 +2778,12 @@ template <int Q, bool MH, int STREAM>
 void stage_launch_mfma(const StageArgs& a, dim3 grid, int64_t per, int precision, hipStream_t s) {
     if (precision == CMCG_FP32)
         hipLaunchKernelGGL((k_stage_col<Q, MH, false, STREAM>), grid, dim3(ColDim<Q>::NTH), 0, s, a, per);
+    else if (TileDim<Q>::LOOP && !MH && a.mtab)  // batches have one frequency
+        hipLaunchKernelGGL((k_stage_tile<Q, MH, false, STREAM, TileDim<Q>::LOOP && !MH>),
+                           tile_grid<Q>(per, grid.y, TileDim<Q>::occ(false)), dim3(256), 0, s, a, per);
     else
-        hipLaunchKernelGGL((k_stage_tile<Q, MH, false, STREAM>), tile_grid<Q>(per, grid.y, TileDim<Q>::occ(false)), dim3(256), 0, s, a, per);
+        hipLaunchKernelGGL((k_stage_tile<Q, MH, false, STREAM>), tile_grid<Q>(per, grid.y, TileDim<Q>::occ(false)),
+                           dim3(256), 0, s, a, per);
 }
 
 template <typename T, int Q, bool MH>
