@@ -204,8 +204,9 @@ int cmcg_engine_admit(cmcg_engine* e, cmcg_problem* p, const cmcg_options* o, in
     cmcg_options oe = *o;
     oe.autotune = 0;  // the stage variant is process-wide and slots run concurrently
     p->resident.reset();
-    s.run.reset(new CgRun());
-    s.run->start(p, &oe, nullptr, s.st);
+    std::unique_ptr<CgRun> run(new CgRun());  // a start that fails leaves no call on the device
+    run->start(p, &oe, nullptr, s.st);
+    s.run = std::move(run);
     s.state = 1;
     s.p = p;
     s.bytes = need;

@@ -354,3 +354,31 @@ def test_autotuner_times_every_kernel_once(lib, q, precision):
     rest = [x for i, x in enumerate(us) if i > 1 and not (q == 2 and i in (6, 7))]
     assert len(set(rest)) == 1 and (rest[0] > 0) == (q > 1)
     assert us[v] == min(x for x in us if x > 0) and v <= 2
+
+
+def test_engine_slots_leave_the_device_when_done(lib):
+    """While a slot runs, plain solves beside it run by stage launches; when it
+    has finished, failed or been cancelled -- collected or not -- they do not."""
+    print("engine slots", flush=True)
+    mesh = _mesh3d("shuffled")
+    s, p = _problem(lib, 3, mesh, 2, 1, seed=8)
+    K = len(mesh[1])
+    rng = np.random.default_rng(3)
+    slots = [_member(lib, s, 3, K, 2, rng, 9.0) for _ in range(3)]
+    e = lib.cmcg_engine_create(1 << 30, 4)
+
+    def run(slot):
+        while lib.cmcg_engine_poll(e, slot) == 1:
+            lib.cmcg_engine_step(e)
+
+    a = lib.cmcg_engine_admit(e, slots[0], lib.cmcg_options_default(fixed_iters=2))
+    assert _period(lib, p, K, 6, 10) == (0, 0)
+    run(a)
+    assert lib.cmcg_engine_poll(e, a) == 2 and _period(lib, p, K, 6, 10) == (1, 0)
+    b = lib.cmcg_engine_admit(e, slots[1], lib.cmcg_options_default(fixed_iters=2, steps=3))  # far too few steps
+    run(b)
+    assert lib.cmcg_engine_poll(e, b) == 3 and _period(lib, p, K, 6, 10) == (1, 0)
+    c = lib.cmcg_engine_admit(e, slots[2], lib.cmcg_options_default(fixed_iters=50))
+    assert _period(lib, p, K, 6, 10) == (0, 0)
+    lib.cmcg_engine_cancel(e, c)
+    assert _period(lib, p, K, 6, 10) == (1, 0)
